@@ -131,19 +131,19 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
 /*
  * fsa_mean_bwd with a caller workspace (same arguments, same result within the same tolerance).
  * The atomic backward is bound by the L2 atomic unit (one 4-byte add per channel and clock), and
- * that cost grows with the row width.  Given a workspace, 2-hop calls with wide rows
- * (at least 1024 bytes, at most 8 x 64 chunks of 16 / 8 / 4 bytes -- the widest the row size and
- * the pointers' alignment allow -- and at least 32 MiB of row updates per call), and calls with
- * rows of 256 .. 1023 bytes and at least 393,216 leaf slots (B*k1*k2), take another route: the
- * leaf entries are binned by destination row, each bin is sorted in LDS, the gradients that reach
- * one row are summed in registers and the row is updated once with plain loads and stores by the
- * one workgroup that owns it (Sec. 3.3 only fixes WHICH rows receive gradient; how is ours).
- * Without overflow of a bin (rows sampled thousands of times in one batch) that route is
- * bit-reproducible.  Calls that are not eligible, a NULL workspace, one that is too small or not
- * 256-byte aligned: the call behaves exactly as fsa_mean_bwd.
+ * that cost grows with the row width.  Given a workspace, 2-hop calls that move enough row bytes
+ * update every destination row once, with plain loads and stores by one wave that owns it (Sec. 3.3
+ * only fixes WHICH rows receive gradient; how is ours), by one of two routes: large calls with wide
+ * rows bin the leaf entries by row, sort each bin in LDS and sum a row's gradients in registers; other
+ * calls (rows of 384 bytes and more, at least 48 MiB of row updates, 32 MiB from 1024 bytes on) look
+ * every leaf's row up in hashed buckets.  Without overflow of a bin, and unless a row is sampled more
+ * than 16 times in a call that takes the second route, the result is bit-reproducible.  Calls that are
+ * not eligible, a NULL workspace, one that is too small or not 256-byte aligned: the call behaves
+ * exactly as fsa_mean_bwd.
  *   workspace        device memory, contents irrelevant on entry, overwritten
- *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what the call can
- *                    use (0: this shape always takes the atomic route)
+ *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what rows of at least
+ *                    1024 bytes (32 MiB of row updates) and calls of at least 393,216 leaf slots can
+ *                    use, 0 for other shapes; fsa_bwd_workspace_bytes below covers all of them
  */
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D);
 int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
@@ -151,6 +151,14 @@ int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
                     int64_t B, int32_t k1, int32_t k2, int64_t D,
                     float* grad_x, int64_t num_nodes,
                     void* workspace, int64_t workspace_bytes, void* stream);
+
+/*
+ * The backward entry points below with `_ws` take a workspace the same way (contents irrelevant on
+ * entry, overwritten; NULL, too small or not 256-byte aligned: the call takes the atomics).  One
+ * size serves all of them: fsa_bwd_workspace_bytes(B,k1,k2,D,grad_x_dtype), 0 where the atomics are
+ * the better route whatever the workspace.  Three hops: (B*k1, k2, k3, D, FSA_F32).
+ */
+int64_t fsa_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int grad_x_dtype);
 
 /*
  * Reduced-precision backward (the paper lists FP32-only kernels as a limitation, Sec. 5
@@ -177,6 +185,12 @@ int fsa_mean_bwd_lp(const void* grad_out, const void* grad_h1, int grad_dtype,
                     const int32_t* ids1, const int32_t* ids2,
                     int64_t B, int32_t k1, int32_t k2, int64_t D,
                     void* grad_x, int grad_x_dtype, int64_t num_nodes, void* stream);
+/* ... given a workspace: a row owned by one wave is added to once, in fp32, and rounded once. */
+int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype,
+                       const int32_t* ids1, const int32_t* ids2,
+                       int64_t B, int32_t k1, int32_t k2, int64_t D,
+                       void* grad_x, int grad_x_dtype, int64_t num_nodes,
+                       void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
  * Layer-wise two-hop forward: fsa_sample_mean_fwd for fanouts (k1,k2) that ALSO emits the plain
@@ -244,6 +258,11 @@ int fsa_mean3_bwd(const float* grad_out, const float* grad_h1, const float* grad
                   const int32_t* ids1, const int32_t* ids2, const int32_t* ids3,
                   int64_t B, int32_t k1, int32_t k2, int32_t k3, int64_t D,
                   float* grad_x, int64_t num_nodes, float* work, void* stream);
+int fsa_mean3_bwd_ws(const float* grad_out, const float* grad_h1, const float* grad_h2, const float* grad_m1,
+                     const int32_t* ids1, const int32_t* ids2, const int32_t* ids3,
+                     int64_t B, int32_t k1, int32_t k2, int32_t k3, int64_t D,
+                     float* grad_x, int64_t num_nodes, float* work,
+                     void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
  * fsa_mean3_bwd for callers that cannot allocate device memory or hand over a workspace: code
@@ -304,6 +323,12 @@ int fsa_wmean_bwd(const float* grad_out, const float* grad_h1,
                   const float* w1, const float* w2,
                   int64_t B, int32_t k1, int32_t k2, int64_t D,
                   float* grad_x, int64_t num_nodes, void* stream);
+int fsa_wmean_bwd_ws(const float* grad_out, const float* grad_h1,
+                     const int32_t* ids1, const int32_t* ids2,
+                     const float* w1, const float* w2,
+                     int64_t B, int32_t k1, int32_t k2, int64_t D,
+                     float* grad_x, int64_t num_nodes,
+                     void* workspace, int64_t workspace_bytes, void* stream);
 
 /* Static, never-freed description of a status code. */
 const char* fsa_status_string(int status);

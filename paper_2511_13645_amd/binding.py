@@ -1,6 +1,7 @@
 """Thin ctypes binding of the C-ABI HIP library (include/fsa.h), same names as the C entry
 points.  Argument marshalling only: every step of the path runs inside the library's
-kernels.  PyTorch is used for device memory and the current stream, nothing else.
+kernels.  PyTorch is used for device memory (outputs, and the backward's workspace where the
+caller brings none) and the current stream, nothing else.
 
 The library must have been built (``python -m paper_2511_13645_amd.build`` or
 ``__graft_entry__.build()``); there is no CPU fallback -- a missing library raises.
@@ -25,6 +26,7 @@ FSA_SCRATCH_FLOATS = 8 * 1024 * 1024
 EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_lp", "fsa_status_string",
            "fsa_sample_mean_layerwise_fwd", "fsa_sample_mean3_fwd", "fsa_mean3_replay_fwd", "fsa_mean3_bwd",
            "fsa_mean3_bwd_noalloc", "fsa_mean_bwd_ws", "fsa_mean_bwd_workspace_bytes",
+           "fsa_bwd_workspace_bytes", "fsa_mean_bwd_lp_ws", "fsa_mean3_bwd_ws", "fsa_wmean_bwd_ws",
            "fsa_sample_wmean_fwd", "fsa_wmean_replay_fwd", "fsa_wmean_bwd")
 
 _lib: Optional[ctypes.CDLL] = None
@@ -76,6 +78,14 @@ def lib() -> ctypes.CDLL:
         L.fsa_mean3_bwd.restype = ci
         L.fsa_mean3_bwd_noalloc.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i64, vp, i64, vp]
         L.fsa_mean3_bwd_noalloc.restype = ci
+        L.fsa_bwd_workspace_bytes.argtypes = [i64, i32, i32, i64, ci]
+        L.fsa_bwd_workspace_bytes.restype = i64
+        L.fsa_mean_bwd_lp_ws.argtypes = [vp, vp, ci, vp, vp, i64, i32, i32, i64, vp, ci, i64, vp, i64, vp]
+        L.fsa_mean_bwd_lp_ws.restype = ci
+        L.fsa_wmean_bwd_ws.argtypes = [vp, vp, vp, vp, vp, vp, i64, i32, i32, i64, vp, i64, vp, i64, vp]
+        L.fsa_wmean_bwd_ws.restype = ci
+        L.fsa_mean3_bwd_ws.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i64, vp, i64, vp, vp, i64, vp]
+        L.fsa_mean3_bwd_ws.restype = ci
         L.fsa_status_string.argtypes = [ci]
         L.fsa_status_string.restype = ctypes.c_char_p
         _lib = L
@@ -132,6 +142,23 @@ def _stream(stream: Optional[torch.cuda.Stream], like: torch.Tensor) -> int:
     """The stream to launch on: the caller's, else the current stream of the device that holds `like`."""
     s = torch.cuda.current_stream(like.device) if stream is None else stream
     return s.cuda_stream
+
+
+def _scratch(B: int, k1: int, k2: int, D: int, grad_dtype: int, like: torch.Tensor,
+             stream: Optional[torch.cuda.Stream]) -> Tuple[Optional[torch.Tensor], int]:
+    """Workspace of one backward call from torch's caching allocator, allocated on the stream the call
+    runs on so that the block may be reused, in that stream's order, as soon as the call returns.
+    (None, 0) where the call has no use for one, or when memory is short: the call then takes the atomics."""
+    need = lib().fsa_bwd_workspace_bytes(B, k1, k2, D, grad_dtype) if k2 else 0
+    if not need:
+        return None, 0
+    try:
+        if stream is None:
+            return torch.empty(need, dtype=torch.uint8, device=like.device), need
+        with torch.cuda.stream(stream):
+            return torch.empty(need, dtype=torch.uint8, device=like.device), need
+    except torch.cuda.OutOfMemoryError:
+        return None, 0
 
 
 def fsa_sample_mean_fwd(indptr: torch.Tensor, indices: torch.Tensor, x: torch.Tensor,
@@ -229,15 +256,16 @@ def fsa_mean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
         _need(grad_h1, "grad_h1", torch.float32)
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
-    rc = lib().fsa_mean_bwd(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
-                            _ptr(grad_x), N, _stream(stream, grad_x))
+    ws, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
+    rc = lib().fsa_mean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
+                               _ptr(grad_x), N, _ptr(ws), ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd")
     return grad_x
 
 
 def fsa_mean_bwd_workspace_bytes(B: int, k1: int, k2: int, D: int) -> int:
-    """Workspace bytes fsa_mean_bwd_ws can use for this shape (0: it always takes the atomic route)."""
+    """Workspace bytes a caller may keep for fsa_mean_bwd_ws at this shape (0: not worth keeping one)."""
     return int(lib().fsa_mean_bwd_workspace_bytes(B, k1, k2, D))
 
 
@@ -246,7 +274,7 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
                     workspace: Optional[torch.Tensor] = None,
                     stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """fsa_mean_bwd with a caller workspace (any contiguous GPU tensor; torch allocations are
-    256-byte aligned): wide-row 2-hop calls then update every destination row once, without atomics."""
+    256-byte aligned) instead of one from torch's allocator for the length of the call."""
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -267,6 +295,8 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
     if workspace is not None:
         _need(workspace, "workspace")
         ws_bytes = workspace.numel() * workspace.element_size()
+    else:
+        workspace, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"), (workspace, "workspace"))
     rc = lib().fsa_mean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
                                _ptr(grad_x), N, _ptr(workspace), ws_bytes, _stream(stream, grad_x))
@@ -296,8 +326,10 @@ def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
         _need(grad_h1, "grad_h1", grad_out.dtype)
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
-    rc = lib().fsa_mean_bwd_lp(_ptr(grad_out), _ptr(grad_h1), _x_dtype(grad_out), _ptr(ids1), _ptr(ids2),
-                               B, k1, k2, D, _ptr(grad_x), _x_dtype(grad_x), N, _stream(stream, grad_x))
+    g_type, x_type = _x_dtype(grad_out), _x_dtype(grad_x)
+    ws, ws_bytes = _scratch(B, k1, k2, D, x_type, grad_x, stream)
+    rc = lib().fsa_mean_bwd_lp_ws(_ptr(grad_out), _ptr(grad_h1), g_type, _ptr(ids1), _ptr(ids2),
+                                  B, k1, k2, D, _ptr(grad_x), x_type, N, _ptr(ws), ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd_lp")
     return grad_x
@@ -416,8 +448,10 @@ def fsa_mean3_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: torch.Tensor
         work = torch.empty((B, k1, D), dtype=torch.float32, device=grad_x.device)
     elif work.numel() < B * k1 * D or work.dtype != torch.float32 or not work.is_cuda or not work.is_contiguous():
         raise ValueError("work must be a contiguous GPU tensor that holds B*k1*D floats")
-    rc = lib().fsa_mean3_bwd(_ptr(grad_out), _ptr(grad_h1), _ptr(grad_h2), _ptr(grad_m1), _ptr(ids1), _ptr(ids2), _ptr(ids3),
-                             B, k1, k2, k3, D, _ptr(grad_x), grad_x.shape[0], _ptr(work), _stream(stream, grad_x))
+    ws, ws_bytes = _scratch(B * k1, k2, k3, D, FSA_F32, grad_x, stream)
+    rc = lib().fsa_mean3_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(grad_h2), _ptr(grad_m1), _ptr(ids1), _ptr(ids2), _ptr(ids3),
+                                B, k1, k2, k3, D, _ptr(grad_x), grad_x.shape[0], _ptr(work), _ptr(ws), ws_bytes,
+                                _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean3_bwd")
     return grad_x
@@ -511,8 +545,9 @@ def fsa_wmean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
         _need(grad_h1, "grad_h1", torch.float32)
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"), (w1, "w1"), (w2, "w2"))
-    rc = lib().fsa_wmean_bwd(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), _ptr(w1), _ptr(w2),
-                             B, k1, k2, D, _ptr(grad_x), grad_x.shape[0], _stream(stream, grad_x))
+    ws, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
+    rc = lib().fsa_wmean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), _ptr(w1), _ptr(w2),
+                                B, k1, k2, D, _ptr(grad_x), grad_x.shape[0], _ptr(ws), ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_wmean_bwd")
     return grad_x

@@ -163,8 +163,37 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
 
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D) {
     if (B <= 0 || D <= 0 || !fanout_ok(k1) || !fanout_ok(k2)) return 0;
-    return (int64_t)fsa::sorted_workspace_bytes(B, k1, k2, D);
+    const int64_t s = (int64_t)fsa::sorted_workspace_bytes(B, k1, k2, D);
+    if (s == 0) return 0;
+    const int64_t o = (int64_t)fsa::owned_workspace_bytes(B, k1, k2, D, 4);   // one of the two routes takes the call
+    return s > o ? s : o;
 }
+
+int64_t fsa_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int grad_x_dtype) {
+    if (B <= 0 || D <= 0 || !fanout_ok(k1) || !fanout_ok(k2)) return 0;
+    if (grad_x_dtype != FSA_F32 && grad_x_dtype != FSA_BF16 && grad_x_dtype != FSA_F16) return 0;
+    const int64_t o = (int64_t)fsa::owned_workspace_bytes(B, k1, k2, D, elem_bytes(grad_x_dtype));
+    if (grad_x_dtype != FSA_F32) return o;
+    const int64_t s = (int64_t)fsa::sorted_workspace_bytes(B, k1, k2, D);
+    return s > o ? s : o;
+}
+
+namespace {
+
+// The unweighted backward: the owning route that suits the call if there is one and the workspace
+// serves it, else the atomics.
+hipError_t backward_any(const fsa::BwdArgs& a, void* workspace, int64_t workspace_bytes, hipStream_t st) {
+    if (workspace) {
+        bool used = false;
+        if (hipError_t e = fsa::launch_backward_sorted(a, workspace, (size_t)workspace_bytes, st, &used)) return e;
+        if (used) return hipSuccess;
+        if (hipError_t e = fsa::launch_backward_owned(a, nullptr, workspace, (size_t)workspace_bytes, st, &used)) return e;
+        if (used) return hipSuccess;
+    }
+    return fsa::launch_backward(a, st);
+}
+
+}  // namespace
 
 int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
                     const int32_t* ids1, const int32_t* ids2,
@@ -185,17 +214,22 @@ int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
     fsa::BwdArgs a{};
     a.grad_out = grad_out; a.grad_h1 = grad_h1; a.ids1 = ids1; a.ids2 = ids2;
     a.B = B; a.k1 = k1; a.k2 = ids2 ? k2 : 0; a.D = D; a.grad_x = grad_x;
-    bool used = false;
-    if (hipError_t e = fsa::launch_backward_sorted(a, workspace, (size_t)workspace_bytes, static_cast<hipStream_t>(stream), &used))
-        return status_of(e);
-    if (used) return FSA_OK;
-    return status_of(fsa::launch_backward(a, static_cast<hipStream_t>(stream)));
+    return status_of(backward_any(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream)));
 }
 
 int fsa_mean_bwd_lp(const void* grad_out, const void* grad_h1, int grad_dtype,
                     const int32_t* ids1, const int32_t* ids2,
                     int64_t B, int32_t k1, int32_t k2, int64_t D,
                     void* grad_x, int grad_x_dtype, int64_t num_nodes, void* stream) {
+    return fsa_mean_bwd_lp_ws(grad_out, grad_h1, grad_dtype, ids1, ids2, B, k1, k2, D, grad_x, grad_x_dtype, num_nodes,
+                              nullptr, 0, stream);
+}
+
+int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype,
+                       const int32_t* ids1, const int32_t* ids2,
+                       int64_t B, int32_t k1, int32_t k2, int64_t D,
+                       void* grad_x, int grad_x_dtype, int64_t num_nodes,
+                       void* workspace, int64_t workspace_bytes, void* stream) {
     if (!grad_x) return FSA_ERR_NULL;
     if (B != 0 && (!grad_out || !ids1)) return FSA_ERR_NULL;
     if (int rc = check_common(grad_dtype, D, num_nodes, B)) return rc;
@@ -204,6 +238,7 @@ int fsa_mean_bwd_lp(const void* grad_out, const void* grad_h1, int grad_dtype,
     if (grad_x_dtype != FSA_F32 && grad_dtype != FSA_F32 && grad_dtype != grad_x_dtype) return FSA_ERR_DTYPE;
     if (!fanout_ok(k1) || (ids2 && !fanout_ok(k2))) return FSA_ERR_ARG;
     if (!ids2 && grad_h1) return FSA_ERR_ARG;
+    if (workspace_bytes < 0) return FSA_ERR_ARG;
     const bool pairs = grad_x_dtype != FSA_F32;                // lanes own element pairs
     if (pairs && (D & 1)) return FSA_ERR_ARG;
     const uintptr_t g_align = pairs ? 4 : (uintptr_t)elem_bytes(grad_dtype);
@@ -217,7 +252,7 @@ int fsa_mean_bwd_lp(const void* grad_out, const void* grad_h1, int grad_dtype,
     a.grad_out = grad_out; a.grad_h1 = grad_h1; a.ids1 = ids1; a.ids2 = ids2;
     a.B = B; a.k1 = k1; a.k2 = ids2 ? k2 : 0; a.D = D; a.grad_x = grad_x;
     a.grad_kind = grad_dtype; a.grad_x_kind = grad_x_dtype;
-    return status_of(fsa::launch_backward(a, static_cast<hipStream_t>(stream)));
+    return status_of(backward_any(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream)));
 }
 
 int fsa_sample_wmean_fwd(const void* indptr, int indptr_type, const int32_t* indices,
@@ -289,7 +324,17 @@ int fsa_wmean_bwd(const float* grad_out, const float* grad_h1,
                   const float* w1, const float* w2,
                   int64_t B, int32_t k1, int32_t k2, int64_t D,
                   float* grad_x, int64_t num_nodes, void* stream) {
+    return fsa_wmean_bwd_ws(grad_out, grad_h1, ids1, ids2, w1, w2, B, k1, k2, D, grad_x, num_nodes, nullptr, 0, stream);
+}
+
+int fsa_wmean_bwd_ws(const float* grad_out, const float* grad_h1,
+                     const int32_t* ids1, const int32_t* ids2,
+                     const float* w1, const float* w2,
+                     int64_t B, int32_t k1, int32_t k2, int64_t D,
+                     float* grad_x, int64_t num_nodes,
+                     void* workspace, int64_t workspace_bytes, void* stream) {
     if (!grad_x) return FSA_ERR_NULL;
+    if (workspace_bytes < 0) return FSA_ERR_ARG;
     if (B != 0 && (!grad_out || !ids1 || !w1 || (ids2 && !w2))) return FSA_ERR_NULL;
     if (int rc = check_common(FSA_F32, D, num_nodes, B)) return rc;
     if (!fanout_ok(k1) || (ids2 && !fanout_ok(k2))) return FSA_ERR_ARG;
@@ -305,6 +350,10 @@ int fsa_wmean_bwd(const float* grad_out, const float* grad_h1,
     a.B = B; a.k1 = k1; a.k2 = ids2 ? k2 : 0; a.D = D; a.grad_x = grad_x;
     fsa::WeightArgs w{};
     w.w1 = w1; w.w2 = w2;
+    bool used = false;
+    if (hipError_t e = fsa::launch_backward_owned(a, &w, workspace, (size_t)workspace_bytes, static_cast<hipStream_t>(stream), &used))
+        return status_of(e);
+    if (used) return FSA_OK;
     return status_of(fsa::launch_backward_weighted(a, w, static_cast<hipStream_t>(stream)));
 }
 
@@ -445,14 +494,14 @@ int mean3_bwd_checked(const float* grad_out, const float* grad_h1, const float* 
 int mean3_bwd_launch(const float* grad_out, const float* grad_h1, const float* grad_h2, const float* grad_m1,
                      const int32_t* ids1, const int32_t* ids2, const int32_t* ids3,
                      int64_t B, int32_t k1, int32_t k2, int32_t k3, int64_t D,
-                     float* grad_x, float* work, hipStream_t st) {
+                     float* grad_x, float* work, void* workspace, int64_t workspace_bytes, hipStream_t st) {
     drop_stale_hip_error();
     if (hipError_t e = fsa::launch_deep_grad(grad_out, grad_h1, ids1, ids2, ids3, work, B, k1, k2, k3, D, st)) return status_of(e);
     {
         fsa::BwdArgs a{};
         a.grad_out = work; a.grad_h1 = grad_h2; a.ids1 = ids2; a.ids2 = ids3; a.root_valid = ids1;
         a.B = B * k1; a.k1 = k2; a.k2 = k3; a.D = D; a.grad_x = grad_x;
-        if (hipError_t e = fsa::launch_backward(a, st)) return status_of(e);
+        if (hipError_t e = backward_any(a, workspace, workspace_bytes, st)) return status_of(e);
     }
     if (grad_m1) {
         fsa::BwdArgs a{};
@@ -468,13 +517,23 @@ int fsa_mean3_bwd(const float* grad_out, const float* grad_h1, const float* grad
                   const int32_t* ids1, const int32_t* ids2, const int32_t* ids3,
                   int64_t B, int32_t k1, int32_t k2, int32_t k3, int64_t D,
                   float* grad_x, int64_t num_nodes, float* work, void* stream) {
+    return fsa_mean3_bwd_ws(grad_out, grad_h1, grad_h2, grad_m1, ids1, ids2, ids3, B, k1, k2, k3, D, grad_x, num_nodes, work,
+                            nullptr, 0, stream);
+}
+
+int fsa_mean3_bwd_ws(const float* grad_out, const float* grad_h1, const float* grad_h2, const float* grad_m1,
+                     const int32_t* ids1, const int32_t* ids2, const int32_t* ids3,
+                     int64_t B, int32_t k1, int32_t k2, int32_t k3, int64_t D,
+                     float* grad_x, int64_t num_nodes, float* work,
+                     void* workspace, int64_t workspace_bytes, void* stream) {
     if (B != 0 && !work) return FSA_ERR_NULL;
     if (int rc = mean3_bwd_checked(grad_out, grad_h1, grad_h2, grad_m1, ids1, ids2, ids3, B, k1, k2, k3, D, grad_x, num_nodes))
         return rc;
+    if (workspace_bytes < 0) return FSA_ERR_ARG;
     if (!aligned(work, 4)) return FSA_ERR_ALIGN;
     if (B == 0) return FSA_OK;
     return mean3_bwd_launch(grad_out, grad_h1, grad_h2, grad_m1, ids1, ids2, ids3, B, k1, k2, k3, D, grad_x, work,
-                            static_cast<hipStream_t>(stream));
+                            workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 int fsa_mean3_bwd_noalloc(const float* grad_out, const float* grad_h1, const float* grad_h2, const float* grad_m1,
@@ -488,7 +547,7 @@ int fsa_mean3_bwd_noalloc(const float* grad_out, const float* grad_h1, const flo
     float* work = scratch_pointer();
     if (!work) return FSA_ERR_HIP;
     return mean3_bwd_launch(grad_out, grad_h1, grad_h2, grad_m1, ids1, ids2, ids3, B, k1, k2, k3, D, grad_x, work,
-                            static_cast<hipStream_t>(stream));
+                            nullptr, 0, static_cast<hipStream_t>(stream));
 }
 
 

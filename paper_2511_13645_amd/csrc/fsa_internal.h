@@ -74,6 +74,11 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t stream);
 size_t sorted_workspace_bytes(int64_t B, int k1, int k2, int64_t D);
 hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t workspace_bytes, hipStream_t stream,
                                   bool* used);
+// Backward that owns each destination row for every element type, weighted or not: needs a caller
+// workspace; `*used` as above.
+size_t owned_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int x_bytes);
+hipError_t launch_backward_owned(const BwdArgs& a, const WeightArgs* w, void* workspace, size_t workspace_bytes,
+                                 hipStream_t stream, bool* used);
 hipError_t launch_backward1_weighted(const BwdArgs& a, const float* w1, hipStream_t stream);   // 1-hop, fp32
 // work[b,j,:] = (slot j took part ? grad_out[b,:] / #such slots : 0) + grad_h1[b,j,:]  (grad_h1 nullable)
 hipError_t launch_deep_grad(const float* grad_out, const float* grad_h1, const int32_t* ids1, const int32_t* ids2,
