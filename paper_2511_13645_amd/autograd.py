@@ -35,13 +35,13 @@ class _FusedSampleMean(torch.autograd.Function):
         ctx.hops = len(fan)
         ctx.master_grad = master_grad
         ctx.workspace = workspace
-        ctx.save_for_backward(*(t for t in (ids1, ids2) if t is not None))
-        ctx.mark_non_differentiable(*(t for t in (ids1, ids2) if t is not None))
-        empty = x.new_empty(0)
-        return (out,
-                h1 if h1 is not None else empty,
-                ids1 if ids1 is not None else empty.to(torch.int32),
-                ids2 if ids2 is not None else empty.to(torch.int32))
+        # gradients of outputs that the loss does not use stay None: the IDs' (and an unused out_h1's) would
+        # each be an allocation and a fill launch
+        ctx.set_materialize_grads(False)
+        ids = tuple(t for t in (ids1, ids2) if t is not None)
+        ctx.save_for_backward(*ids)
+        ctx.mark_non_differentiable(*ids)
+        return out, h1, ids1, ids2
 
     @staticmethod
     def backward(ctx, g_out, g_h1, _g_ids1, _g_ids2):
@@ -53,6 +53,8 @@ class _FusedSampleMean(torch.autograd.Function):
         gh = None
         if ctx.hops == 2 and g_h1 is not None and g_h1.numel() > 0:
             gh = g_h1.contiguous()
+        if g_out is None:                       # only out_h1 was used
+            g_out = ids1.new_zeros((ids1.shape[0], ctx.shape[1]), dtype=ctx.x_dtype)
         g_out = g_out.contiguous()
         if ctx.master_grad is not None:
             binding.fsa_mean_bwd_lp(g_out, ids1, ids2, gh, grad_x=ctx.master_grad)
@@ -82,5 +84,4 @@ def fused_sample_mean(x: torch.Tensor, indptr: torch.Tensor, indices: torch.Tens
         raise ValueError("master_grad must be an fp32 tensor of the table's shape")
     out, h1, ids1, ids2 = _FusedSampleMean.apply(x, indptr, indices, seeds, tuple(fanouts), int(seed),
                                                  bool(want_h1), bool(save_indices), master_grad, workspace)
-    return (out, h1 if h1.numel() or (want_h1 and len(fanouts) == 2 and seeds.numel() == 0) else None,
-            ids1 if ids1.numel() else None, ids2 if ids2.numel() else None)
+    return (out, h1, ids1 if ids1 is not None and ids1.numel() else None, ids2 if ids2 is not None and ids2.numel() else None)

@@ -9,6 +9,7 @@ The library must have been built (``python -m paper_2511_13645_amd.build`` or
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence, Tuple
 
@@ -96,18 +97,21 @@ def status_string(status: int) -> str:
     return lib().fsa_status_string(int(status)).decode()
 
 
+# The per-call checks and lookups below sit on the latency path of small calls (a call of a few seeds is
+# bound by its host side), so the common case costs one comparison or one dictionary lookup.
+_raw_stream = torch._C._cuda_getCurrentRawStream               # the current stream's handle, without a Stream object
+_FLOAT_TYPE = {torch.float32: FSA_F32, torch.bfloat16: FSA_BF16, torch.float16: FSA_F16}
+
+
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
 def _x_dtype(x: torch.Tensor) -> int:
-    if x.dtype == torch.float32:
-        return FSA_F32
-    if x.dtype == torch.bfloat16:
-        return FSA_BF16
-    if x.dtype == torch.float16:
-        return FSA_F16
-    raise TypeError("expected float32, bfloat16 or float16, got %s" % x.dtype)
+    code = _FLOAT_TYPE.get(x.dtype)
+    if code is None:
+        raise TypeError("expected float32, bfloat16 or float16, got %s" % x.dtype)
+    return code
 
 
 def _indptr_type(indptr: torch.Tensor) -> int:
@@ -119,29 +123,36 @@ def _indptr_type(indptr: torch.Tensor) -> int:
 
 
 def _need(t: torch.Tensor, name: str, dtype=None) -> None:
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype):
+        return
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if dtype is not None and t.dtype != dtype:
-        raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
+    raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
 
 
 def _shape(t: Optional[torch.Tensor], name: str, shape) -> None:
-    if t is not None and tuple(t.shape) != tuple(shape):
+    if t is not None and t.shape != shape:
         raise ValueError("%s must be %s, got %s" % (name, tuple(shape), tuple(t.shape)))
 
 
 def _same_device(ref: torch.Tensor, *named) -> None:
+    dev = ref.device
     for t, name in named:
-        if t is not None and t.device != ref.device:
-            raise ValueError("%s lives on %s, expected %s" % (name, t.device, ref.device))
+        if t is not None and t.device != dev:
+            raise ValueError("%s lives on %s, expected %s" % (name, t.device, dev))
 
 
 def _stream(stream: Optional[torch.cuda.Stream], like: torch.Tensor) -> int:
     """The stream to launch on: the caller's, else the current stream of the device that holds `like`."""
-    s = torch.cuda.current_stream(like.device) if stream is None else stream
-    return s.cuda_stream
+    return _raw_stream(like.get_device()) if stream is None else stream.cuda_stream
+
+
+@functools.lru_cache(maxsize=256)
+def _host_ints(values: Tuple[int, ...]) -> ctypes.Array:
+    """A host array of these int32 values; the library reads it during the call and never writes it."""
+    return (ctypes.c_int32 * max(1, len(values)))(*values)
 
 
 def _scratch(B: int, k1: int, k2: int, D: int, grad_dtype: int, like: torch.Tensor,
@@ -177,28 +188,28 @@ def fsa_sample_mean_fwd(indptr: torch.Tensor, indices: torch.Tensor, x: torch.Te
     B, (N, D) = seeds.shape[0], x.shape
     if indptr.shape[0] != N + 1:
         raise ValueError("indptr must have num_nodes+1 entries")
-    dev = x.device
     k1 = fan[0] if hops >= 1 else 0
     k2 = fan[1] if hops >= 2 else 0
+    if out is not None or out_h1 is not None or out_ids1 is not None or out_ids2 is not None:
+        for t, n, dt, shp in ((out, "out", x.dtype, (B, D)), (out_h1, "out_h1", x.dtype, (B, k1, D)),
+                              (out_ids1, "out_ids1", torch.int32, (B, k1)), (out_ids2, "out_ids2", torch.int32, (B, k1, k2))):
+            if t is not None:
+                _need(t, n, dt)
+                _shape(t, n, shp)
+                _same_device(x, (t, n))
+    _same_device(x, (indptr, "indptr"), (indices, "indices"), (seeds, "seeds"))
     if out is None:
-        out = torch.empty((B, D), dtype=x.dtype, device=dev)
+        out = x.new_empty((B, D))
     if hops == 2 and emit_h1 and out_h1 is None:
-        out_h1 = torch.empty((B, k1, D), dtype=x.dtype, device=dev)
+        out_h1 = x.new_empty((B, k1, D))
     if emit_ids and out_ids1 is None:
-        out_ids1 = torch.empty((B, k1), dtype=torch.int32, device=dev)
+        out_ids1 = seeds.new_empty((B, k1))
     if emit_ids and hops == 2 and out_ids2 is None:
-        out_ids2 = torch.empty((B, k1, k2), dtype=torch.int32, device=dev)
-    for t, n, dt, shp in ((out, "out", x.dtype, (B, D)), (out_h1, "out_h1", x.dtype, (B, k1, D)),
-                          (out_ids1, "out_ids1", torch.int32, (B, k1)), (out_ids2, "out_ids2", torch.int32, (B, k1, k2))):
-        if t is not None:
-            _need(t, n, dt)
-            _shape(t, n, shp)
-    _same_device(x, (indptr, "indptr"), (indices, "indices"), (seeds, "seeds"), (out, "out"), (out_h1, "out_h1"),
-                 (out_ids1, "out_ids1"), (out_ids2, "out_ids2"))
-    fan_host = (ctypes.c_int32 * max(1, hops))(*fan)
+        out_ids2 = seeds.new_empty((B, k1, k2))
+    fan_host = _host_ints(tuple(fan))
     rc = lib().fsa_sample_mean_fwd(_ptr(indptr), _indptr_type(indptr), _ptr(indices), N,
                                    _ptr(x), _x_dtype(x), D, _ptr(seeds), B,
-                                   ctypes.cast(fan_host, ctypes.c_void_p), hops, seed & (2**64 - 1),
+                                   fan_host, hops, seed & (2**64 - 1),
                                    _ptr(out), _ptr(out_h1), _ptr(out_ids1), _ptr(out_ids2), _stream(stream, x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_sample_mean_fwd")
@@ -219,15 +230,15 @@ def fsa_mean_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
         if ids2.shape[0] != B or ids2.shape[1] != k1:
             raise ValueError("ids2 must be [B,k1,k2]")
         k2 = ids2.shape[2]
-    if out is None:
-        out = torch.empty((B, D), dtype=x.dtype, device=x.device)
-    if ids2 is not None and emit_h1 and out_h1 is None:
-        out_h1 = torch.empty((B, k1, D), dtype=x.dtype, device=x.device)
     for t, n, shp in ((out, "out", (B, D)), (out_h1, "out_h1", (B, k1, D))):
         if t is not None:
             _need(t, n, x.dtype)
             _shape(t, n, shp)
     _same_device(x, (ids1, "ids1"), (ids2, "ids2"), (out, "out"), (out_h1, "out_h1"))
+    if out is None:
+        out = x.new_empty((B, D))
+    if ids2 is not None and emit_h1 and out_h1 is None:
+        out_h1 = x.new_empty((B, k1, D))
     rc = lib().fsa_mean_replay_fwd(_ptr(x), _x_dtype(x), D, N, _ptr(ids1), _ptr(ids2), B, k1, k2,
                                    _ptr(out), _ptr(out_h1), _stream(stream, x))
     if rc != FSA_OK:
@@ -344,18 +355,18 @@ def fsa_sample_mean_layerwise_fwd(indptr: torch.Tensor, indices: torch.Tensor, x
     if len(fan) != 2:
         raise ValueError("two fanouts expected")
     k1, k2 = fan
-    B, (N, D), dev = seeds.shape[0], x.shape, x.device
+    B, (N, D) = seeds.shape[0], x.shape
     if indptr.shape[0] != N + 1:
         raise ValueError("indptr must have num_nodes+1 entries")
     _same_device(x, (indptr, "indptr"), (indices, "indices"), (seeds, "seeds"))
-    out = torch.empty((B, D), dtype=x.dtype, device=dev)
-    out_m1 = torch.empty((B, D), dtype=x.dtype, device=dev)
-    out_h1 = torch.empty((B, k1, D), dtype=x.dtype, device=dev) if emit_h1 else None
-    ids1 = torch.empty((B, k1), dtype=torch.int32, device=dev) if emit_ids else None
-    ids2 = torch.empty((B, k1, k2), dtype=torch.int32, device=dev) if emit_ids else None
-    fan_host = (ctypes.c_int32 * 2)(*fan)
+    out = x.new_empty((B, D))
+    out_m1 = x.new_empty((B, D))
+    out_h1 = x.new_empty((B, k1, D)) if emit_h1 else None
+    ids1 = seeds.new_empty((B, k1)) if emit_ids else None
+    ids2 = seeds.new_empty((B, k1, k2)) if emit_ids else None
+    fan_host = _host_ints(tuple(fan))
     rc = lib().fsa_sample_mean_layerwise_fwd(_ptr(indptr), _indptr_type(indptr), _ptr(indices), N, _ptr(x), _x_dtype(x), D,
-                                             _ptr(seeds), B, ctypes.cast(fan_host, ctypes.c_void_p), int(seed) & (2**64 - 1),
+                                             _ptr(seeds), B, fan_host, int(seed) & (2**64 - 1),
                                              _ptr(out), _ptr(out_h1), _ptr(out_m1), _ptr(ids1), _ptr(ids2), _stream(stream, x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_sample_mean_layerwise_fwd")
@@ -371,21 +382,21 @@ def fsa_sample_mean3_fwd(indptr: torch.Tensor, indices: torch.Tensor, x: torch.T
     if len(fan) != 3:
         raise ValueError("three fanouts expected")
     k1, k2, k3 = fan
-    B, (N, D), dev = seeds.shape[0], x.shape, x.device
+    B, (N, D) = seeds.shape[0], x.shape
     if indptr.shape[0] != N + 1:
         raise ValueError("indptr must have num_nodes+1 entries")
     _same_device(x, (indptr, "indptr"), (indices, "indices"), (seeds, "seeds"))
-    r = {"out": torch.empty((B, D), dtype=x.dtype, device=dev),
-         "out_h1": torch.empty((B, k1, D), dtype=x.dtype, device=dev),
-         "out_h2": torch.empty((B, k1, k2, D), dtype=x.dtype, device=dev) if emit_h2 else None,
-         "out_m1": torch.empty((B, D), dtype=x.dtype, device=dev),
-         "ids1": torch.empty((B, k1), dtype=torch.int32, device=dev),
-         "ids2": torch.empty((B, k1, k2), dtype=torch.int32, device=dev) if emit_ids else None,
-         "ids3": torch.empty((B, k1, k2, k3), dtype=torch.int32, device=dev) if emit_ids else None,
-         "cnt2": torch.empty((B, k1), dtype=torch.int32, device=dev)}
-    fan_host = (ctypes.c_int32 * 3)(*fan)
+    r = {"out": x.new_empty((B, D)),
+         "out_h1": x.new_empty((B, k1, D)),
+         "out_h2": x.new_empty((B, k1, k2, D)) if emit_h2 else None,
+         "out_m1": x.new_empty((B, D)),
+         "ids1": seeds.new_empty((B, k1)),
+         "ids2": seeds.new_empty((B, k1, k2)) if emit_ids else None,
+         "ids3": seeds.new_empty((B, k1, k2, k3)) if emit_ids else None,
+         "cnt2": seeds.new_empty((B, k1))}
+    fan_host = _host_ints(tuple(fan))
     rc = lib().fsa_sample_mean3_fwd(_ptr(indptr), _indptr_type(indptr), _ptr(indices), N, _ptr(x), _x_dtype(x), D,
-                                    _ptr(seeds), B, ctypes.cast(fan_host, ctypes.c_void_p), int(seed) & (2**64 - 1),
+                                    _ptr(seeds), B, fan_host, int(seed) & (2**64 - 1),
                                     _ptr(r["out"]), _ptr(r["out_h1"]), _ptr(r["out_h2"]), _ptr(r["out_m1"]),
                                     _ptr(r["ids1"]), _ptr(r["ids2"]), _ptr(r["ids3"]), _ptr(r["cnt2"]), _stream(stream, x))
     if rc != FSA_OK:
@@ -401,13 +412,12 @@ def fsa_mean3_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, ids2: torch.Tensor
     if tuple(ids1.shape) != (B, k1) or tuple(ids2.shape) != (B, k1, k2):
         raise ValueError("ids1 / ids2 / ids3 shapes do not nest")
     N, D = x.shape
-    dev = x.device
     _same_device(x, (ids1, "ids1"), (ids2, "ids2"), (ids3, "ids3"))
-    r = {"out": torch.empty((B, D), dtype=x.dtype, device=dev),
-         "out_h1": torch.empty((B, k1, D), dtype=x.dtype, device=dev),
-         "out_h2": torch.empty((B, k1, k2, D), dtype=x.dtype, device=dev) if emit_h2 else None,
-         "out_m1": torch.empty((B, D), dtype=x.dtype, device=dev) if emit_m1 else None,
-         "cnt2": torch.empty((B, k1), dtype=torch.int32, device=dev)}
+    r = {"out": x.new_empty((B, D)),
+         "out_h1": x.new_empty((B, k1, D)),
+         "out_h2": x.new_empty((B, k1, k2, D)) if emit_h2 else None,
+         "out_m1": x.new_empty((B, D)) if emit_m1 else None,
+         "cnt2": seeds.new_empty((B, k1))}
     rc = lib().fsa_mean3_replay_fwd(_ptr(x), _x_dtype(x), D, N, _ptr(ids1), _ptr(ids2), _ptr(ids3), B, k1, k2, k3,
                                     _ptr(r["out"]), _ptr(r["out_h1"]), _ptr(r["out_h2"]), _ptr(r["out_m1"]),
                                     _ptr(r["cnt2"]), _stream(stream, x))
@@ -476,16 +486,16 @@ def fsa_sample_wmean_fwd(indptr: torch.Tensor, indices: torch.Tensor, edge_weigh
     _same_device(x, (indptr, "indptr"), (indices, "indices"), (edge_weight, "edge_weight"), (seeds, "seeds"))
     k1 = fan[0] if hops >= 1 else 0
     k2 = fan[1] if hops >= 2 else 0
-    out = torch.empty((B, D), dtype=x.dtype, device=dev)
-    out_h1 = torch.empty((B, k1, D), dtype=x.dtype, device=dev) if (hops == 2 and emit_h1) else None
-    ids1 = torch.empty((B, k1), dtype=torch.int32, device=dev) if emit_ids else None
+    out = x.new_empty((B, D))
+    out_h1 = x.new_empty((B, k1, D)) if (hops == 2 and emit_h1) else None
+    ids1 = seeds.new_empty((B, k1)) if emit_ids else None
     w1 = torch.empty((B, k1), dtype=torch.float32, device=dev) if emit_ids else None
-    ids2 = torch.empty((B, k1, k2), dtype=torch.int32, device=dev) if (emit_ids and hops == 2) else None
+    ids2 = seeds.new_empty((B, k1, k2)) if (emit_ids and hops == 2) else None
     w2 = torch.empty((B, k1, k2), dtype=torch.float32, device=dev) if (emit_ids and hops == 2) else None
-    fan_host = (ctypes.c_int32 * max(1, hops))(*fan)
+    fan_host = _host_ints(tuple(fan))
     rc = lib().fsa_sample_wmean_fwd(_ptr(indptr), _indptr_type(indptr), _ptr(indices), _ptr(edge_weight), N,
                                     _ptr(x), _x_dtype(x), D, _ptr(seeds), B,
-                                    ctypes.cast(fan_host, ctypes.c_void_p), hops, seed & (2**64 - 1),
+                                    fan_host, hops, seed & (2**64 - 1),
                                     _ptr(out), _ptr(out_h1), _ptr(ids1), _ptr(ids2), _ptr(w1), _ptr(w2),
                                     _stream(stream, x))
     if rc != FSA_OK:
@@ -511,8 +521,8 @@ def fsa_wmean_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
         k2 = ids2.shape[2]
         _shape(w2, "w2", (B, k1, k2))
     _same_device(x, (ids1, "ids1"), (w1, "w1"), (ids2, "ids2"), (w2, "w2"))
-    out = torch.empty((B, D), dtype=x.dtype, device=x.device)
-    out_h1 = torch.empty((B, k1, D), dtype=x.dtype, device=x.device) if (ids2 is not None and emit_h1) else None
+    out = x.new_empty((B, D))
+    out_h1 = x.new_empty((B, k1, D)) if (ids2 is not None and emit_h1) else None
     rc = lib().fsa_wmean_replay_fwd(_ptr(x), _x_dtype(x), D, N, _ptr(ids1), _ptr(ids2), _ptr(w1), _ptr(w2),
                                     B, k1, k2, _ptr(out), _ptr(out_h1), _stream(stream, x))
     if rc != FSA_OK:

@@ -102,3 +102,24 @@ def test_autograd_with_16bit_tables(orc, dtype, fan, D):
     torch.cuda.synchronize()
     assert x2.grad is None
     assert_close(to_f64(master), ref, mag, 1e-5, "master gradient %s fan=%s" % (dtype, fan))
+
+
+def test_gradient_through_out_h1_alone_and_through_an_unused_output(orc):
+    """Outputs that the loss leaves out bring no gradient: out_h1 alone, then out alone with out_h1 wanted."""
+    from paper_2511_13645_amd.autograd import fused_sample_mean
+    n, D, B, fan = 500, 24, 60, [6, 5]
+    rng = np.random.default_rng(8)
+    deg = rng.integers(0, 12, n)
+    indptr = torch.from_numpy(np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)).cuda()
+    indices = torch.from_numpy(rng.integers(0, n, int(deg.sum())).astype(np.int32)).cuda()
+    seeds = torch.from_numpy(rng.integers(0, n, B).astype(np.int32)).cuda()
+    for which in ("h1", "out"):
+        x = torch.nn.Parameter(torch.from_numpy(rng.standard_normal((n, D)).astype(np.float32)).cuda())
+        out, h1, ids1, ids2 = fused_sample_mean(x, indptr, indices, seeds, fan, 3, want_h1=True)
+        part = h1 if which == "h1" else out
+        g = torch.from_numpy(rng.standard_normal(tuple(part.shape)).astype(np.float32)).cuda()
+        part.backward(g)
+        g64 = g.double().cpu().numpy()
+        go = np.zeros((B, D)) if which == "h1" else g64
+        want = orc.mean_bwd(go, ids1.cpu().numpy(), ids2.cpu().numpy(), g64 if which == "h1" else None, num_nodes=n)
+        assert np.abs(x.grad.double().cpu().numpy() - want).max() <= 1e-5 * max(1.0, np.abs(want).max())
