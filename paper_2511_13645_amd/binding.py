@@ -417,7 +417,7 @@ def fsa_mean3_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, ids2: torch.Tensor
          "out_h1": x.new_empty((B, k1, D)),
          "out_h2": x.new_empty((B, k1, k2, D)) if emit_h2 else None,
          "out_m1": x.new_empty((B, D)) if emit_m1 else None,
-         "cnt2": seeds.new_empty((B, k1))}
+         "cnt2": ids1.new_empty((B, k1))}
     rc = lib().fsa_mean3_replay_fwd(_ptr(x), _x_dtype(x), D, N, _ptr(ids1), _ptr(ids2), _ptr(ids3), B, k1, k2, k3,
                                     _ptr(r["out"]), _ptr(r["out_h1"]), _ptr(r["out_h2"]), _ptr(r["out_m1"]),
                                     _ptr(r["cnt2"]), _stream(stream, x))
