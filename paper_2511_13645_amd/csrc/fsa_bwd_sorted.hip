@@ -54,6 +54,7 @@ struct SortedParams {
     const float* grad_out; const float* grad_h1; const int32_t* ids1; const int32_t* ids2;
     float* grad_x; int64_t B; int64_t D; int k1, k2;
     SortedWs ws;
+    float* slot_grad;                      // [B*k1,D] in the workspace, or NULL: what a leaf of each slot receives
     int chunks;                            // row chunks of VB bytes
 };
 
@@ -65,7 +66,7 @@ static int sorted_log_p(int64_t B, int k1, int k2, int64_t D) {
     return lp;
 }
 
-static void sorted_layout(int64_t B, int k1, int k2, int64_t D, size_t off[5], size_t& total, int& log_p) {
+static void sorted_layout(int64_t B, int k1, int k2, int64_t D, size_t off[6], size_t& total, int& log_p) {
     log_p = sorted_log_p(B, k1, k2, D);
     const size_t P = (size_t)1 << log_p;
     auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
@@ -75,6 +76,7 @@ static void sorted_layout(int64_t B, int k1, int k2, int64_t D, size_t off[5], s
     off[2] = o; o += up((size_t)B * k1 * sizeof(float2));                  // coef
     off[3] = o; o += up(P * kBucketCap * sizeof(unsigned long long));      // pairs
     off[4] = o; o += up((size_t)B * k1 * k2 * sizeof(unsigned long long)); // overflow
+    off[5] = o; o += up((size_t)B * k1 * D * sizeof(float));               // slot_grad
     total = o;
 }
 
@@ -88,11 +90,34 @@ __global__ __launch_bounds__(256) void sorted_clear_kernel(int* cursor, int n_bu
     if (i == 0) *overflow_count = 0;
 }
 
-// One workgroup per root: slot counts, coefficients, entries into buckets.
+template <int VB> struct FloatChunk;
+template <> struct FloatChunk<16> { using T = float4; static constexpr int VE = 4; };
+template <> struct FloatChunk<8>  { using T = float2; static constexpr int VE = 2; };
+template <> struct FloatChunk<4>  { using T = float;  static constexpr int VE = 1; };
+
+template <int VE, typename T> __device__ __forceinline__ void fma_chunk(float (&acc)[VE], const T& v, float w) {
+    if constexpr (VE == 4) { acc[0] = fmaf(w, v.x, acc[0]); acc[1] = fmaf(w, v.y, acc[1]); acc[2] = fmaf(w, v.z, acc[2]); acc[3] = fmaf(w, v.w, acc[3]); }
+    else if constexpr (VE == 2) { acc[0] = fmaf(w, v.x, acc[0]); acc[1] = fmaf(w, v.y, acc[1]); }
+    else { acc[0] = fmaf(w, v, acc[0]); }
+}
+template <int VE, typename T> __device__ __forceinline__ T add_chunk(const T& v, const float (&acc)[VE]) {
+    T r = v;
+    if constexpr (VE == 4) { r.x += acc[0]; r.y += acc[1]; r.z += acc[2]; r.w += acc[3]; }
+    else if constexpr (VE == 2) { r.x += acc[0]; r.y += acc[1]; }
+    else { r += acc[0]; }
+    return r;
+}
+
+// One workgroup per root: slot counts, coefficients, entries into buckets; and, with gradients into the
+// per-slot means, the one row that every leaf of a slot receives, so that the reduce kernel gathers one
+// row per leaf instead of two (it is bound by what it gathers; writing the rows here goes on beside the
+// appends' latency).
+template <int VB>
 __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
     __shared__ int u[64];
     __shared__ int cnt[64];
     __shared__ int c1_shared;
+    __shared__ float2 cf_shared[64];
     const int64_t b = blockIdx.x;
     const int k1 = p.k1, k2 = p.k2;
     const int tid = threadIdx.x;
@@ -118,6 +143,7 @@ __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
         float2 cf = make_float2(0.0f, 0.0f);
         if (c2 > 0) cf = make_float2(1.0f / ((float)c1 * (float)c2), 1.0f / (float)c2);
         p.ws.coef[b * k1 + tid] = cf;
+        cf_shared[tid] = cf;
     }
     for (int e = tid; e < n_ent; e += blockDim.x) {
         const int j = e / k2;
@@ -133,24 +159,26 @@ __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
             p.ws.overflow[o] = key;
         }
     }
-}
-
-template <int VB> struct FloatChunk;
-template <> struct FloatChunk<16> { using T = float4; static constexpr int VE = 4; };
-template <> struct FloatChunk<8>  { using T = float2; static constexpr int VE = 2; };
-template <> struct FloatChunk<4>  { using T = float;  static constexpr int VE = 1; };
-
-template <int VE, typename T> __device__ __forceinline__ void fma_chunk(float (&acc)[VE], const T& v, float w) {
-    if constexpr (VE == 4) { acc[0] = fmaf(w, v.x, acc[0]); acc[1] = fmaf(w, v.y, acc[1]); acc[2] = fmaf(w, v.z, acc[2]); acc[3] = fmaf(w, v.w, acc[3]); }
-    else if constexpr (VE == 2) { acc[0] = fmaf(w, v.x, acc[0]); acc[1] = fmaf(w, v.y, acc[1]); }
-    else { acc[0] = fmaf(w, v, acc[0]); }
-}
-template <int VE, typename T> __device__ __forceinline__ T add_chunk(const T& v, const float (&acc)[VE]) {
-    T r = v;
-    if constexpr (VE == 4) { r.x += acc[0]; r.y += acc[1]; r.z += acc[2]; r.w += acc[3]; }
-    else if constexpr (VE == 2) { r.x += acc[0]; r.y += acc[1]; }
-    else { r += acc[0]; }
-    return r;
+    if (p.slot_grad) {                                                // grid-uniform
+        using T = typename FloatChunk<VB>::T;
+        constexpr int VE = FloatChunk<VB>::VE;
+        __syncthreads();                                              // cf_shared
+        const T* go = reinterpret_cast<const T*>(p.grad_out + b * p.D);
+        for (int j = tid >> 6; j < k1; j += (int)(blockDim.x >> 6)) { // a wave per slot
+            const float2 cf = cf_shared[j];
+            if (!(cf.y > 0.0f)) continue;                             // no leaf names an empty slot
+            const T* gh = reinterpret_cast<const T*>(p.grad_h1 + (b * k1 + j) * p.D);
+            T* dst = reinterpret_cast<T*>(p.slot_grad + (b * k1 + j) * p.D);
+            for (int chunk = tid & 63; chunk < p.chunks; chunk += kWave) {
+                float v[VE];
+#pragma unroll
+                for (int c = 0; c < VE; ++c) v[c] = 0.0f;
+                fma_chunk<VE>(v, go[chunk], cf.x);
+                fma_chunk<VE>(v, gh[chunk], cf.y);
+                dst[chunk] = add_chunk<VE>(T{}, v);
+            }
+        }
+    }
 }
 
 // Loads bucket `bucket`'s entries into `keys`, sorts them ascending -- (row, slot) order fixes the
@@ -216,7 +244,8 @@ __device__ __forceinline__ void add_overflow_entries(const SortedParams& p, int 
 }
 
 // One workgroup (4 waves) per bucket.  MT: row tiles of 64 lanes x VB bytes kept in registers.
-template <int VB, int MT>
+// SLOT: a leaf receives its slot's row of slot_grad as it stands.
+template <int VB, int MT, bool SLOT>
 __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_kernel(const SortedParams p) {
     using T = typename FloatChunk<VB>::T;
     constexpr int VE = FloatChunk<VB>::VE;
@@ -258,9 +287,16 @@ __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_kernel(const Sor
             }
             for (int i = i0; i < n && (uint32_t)(keys[i] >> 32) == row; ++i) {    // wave-uniform
                 const uint32_t s = (uint32_t)keys[i];
-                const float2 cf = p.ws.coef[s];                   // travels with the row loads below
-                const T* go = reinterpret_cast<const T*>(p.grad_out + (int64_t)(s / (uint32_t)k1) * p.D);
-                const T* gh = p.grad_h1 ? reinterpret_cast<const T*>(p.grad_h1 + (int64_t)s * p.D) : nullptr;
+                float2 cf = make_float2(1.0f, 0.0f);
+                const T* go;
+                const T* gh = nullptr;
+                if constexpr (SLOT) {
+                    go = reinterpret_cast<const T*>(p.slot_grad + (int64_t)s * p.D);
+                } else {
+                    cf = p.ws.coef[s];                            // travels with the row loads below
+                    go = reinterpret_cast<const T*>(p.grad_out + (int64_t)(s / (uint32_t)k1) * p.D);
+                    if (p.grad_h1) gh = reinterpret_cast<const T*>(p.grad_h1 + (int64_t)s * p.D);
+                }
                 T a[MT], c[MT];
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
@@ -315,7 +351,7 @@ __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_kernel(const Sor
 // distinct row each, so a workgroup works on 4 .. 64 rows at a time, and a row's old value is
 // requested before its gradients are summed: with rows this short the kernel is bound by the
 // number of dependent memory round trips per wave, not by bytes.
-template <int VB>
+template <int VB, bool SLOT>
 __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_narrow_kernel(const SortedParams p, int sub_shift) {
     using T = typename FloatChunk<VB>::T;
     constexpr int VE = FloatChunk<VB>::VE;
@@ -343,15 +379,19 @@ __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_narrow_kernel(co
             for (int e = 0; e < VE; ++e) acc[e] = 0.0f;
             for (int i = i0; i < n && (uint32_t)(keys[i] >> 32) == row; ++i) {
                 const uint32_t s = (uint32_t)keys[i];
-                const float2 cf = p.ws.coef[s];
-                if (live) {
-                    const T a = reinterpret_cast<const T*>(p.grad_out + (int64_t)(s / (uint32_t)p.k1) * p.D)[sl];
-                    if (p.grad_h1) {
-                        const T c = reinterpret_cast<const T*>(p.grad_h1 + (int64_t)s * p.D)[sl];
-                        fma_chunk<VE>(acc, a, cf.x);
-                        fma_chunk<VE>(acc, c, cf.y);
-                    } else {
-                        fma_chunk<VE>(acc, a, cf.x);
+                if constexpr (SLOT) {
+                    if (live) fma_chunk<VE>(acc, reinterpret_cast<const T*>(p.slot_grad + (int64_t)s * p.D)[sl], 1.0f);
+                } else {
+                    const float2 cf = p.ws.coef[s];
+                    if (live) {
+                        const T a = reinterpret_cast<const T*>(p.grad_out + (int64_t)(s / (uint32_t)p.k1) * p.D)[sl];
+                        if (p.grad_h1) {
+                            const T c = reinterpret_cast<const T*>(p.grad_h1 + (int64_t)s * p.D)[sl];
+                            fma_chunk<VE>(acc, a, cf.x);
+                            fma_chunk<VE>(acc, c, cf.y);
+                        } else {
+                            fma_chunk<VE>(acc, a, cf.x);
+                        }
                     }
                 }
             }
@@ -407,7 +447,7 @@ bool sorted_backward_shape_ok(int64_t B, int k1, int k2, int64_t D) {
 
 size_t sorted_workspace_bytes(int64_t B, int k1, int k2, int64_t D) {
     if (!sorted_backward_shape_ok(B, k1, k2, D)) return 0;
-    size_t off[5], total;
+    size_t off[6], total;
     int lp;
     sorted_layout(B, k1, k2, D, off, total, lp);
     return total;
@@ -422,10 +462,10 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
     if (!sorted_backward_shape_ok(a.B, a.k1, a.k2, a.D)) return hipSuccess;
     if (a.B * a.k1 * a.k2 < kSortedWideMinEntries) return hipSuccess;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return hipSuccess;
-    size_t off[5], total;
+    size_t off[6], total;
     int lp;
     sorted_layout(a.B, a.k1, a.k2, a.D, off, total, lp);
-    if (workspace_bytes < total) return hipSuccess;
+    if (workspace_bytes < off[5]) return hipSuccess;                  // slot_grad is the part that may be missing
     const int vb = sorted_vec_bytes(a);
     const int chunks = (int)(a.D * 4 / vb);
     const int tiles = (chunks + kWave - 1) / kWave;
@@ -442,15 +482,28 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
     p.ws.pairs = reinterpret_cast<unsigned long long*>(w + off[3]);
     p.ws.overflow = reinterpret_cast<unsigned long long*>(w + off[4]);
     p.ws.log_p = lp;
+    // One gathered row per leaf instead of two, against a pass over the slots' rows.  Forward and backward:
+    // 400-byte rows at 614 k leaf slots 287 -> 241 us, 2408-byte rows at 256 k 346 -> 329 us; 1200-byte rows at
+    // 180 k (22 MB of slot rows) 204 -> 210 us, so wide rows from 32 MiB of slot rows on.
+    const bool combine = a.D * 4 < kSortedMinRowBytes || a.B * a.k1 * a.D * 4 >= (32ll << 20);
+    p.slot_grad = a.grad_h1 && combine && workspace_bytes >= total ? reinterpret_cast<float*>(w + off[5]) : nullptr;
     const int P = 1 << lp;
     hipLaunchKernelGGL(sorted_clear_kernel, dim3((P + 255) / 256), dim3(256), 0, stream, p.ws.cursor, P, p.ws.overflow_count);
-    hipLaunchKernelGGL(sorted_bin_kernel, dim3((unsigned)a.B), dim3(256), 0, stream, p);
+    if (vb == 16)     hipLaunchKernelGGL(sorted_bin_kernel<16>, dim3((unsigned)a.B), dim3(256), 0, stream, p);
+    else if (vb == 8) hipLaunchKernelGGL(sorted_bin_kernel<8>, dim3((unsigned)a.B), dim3(256), 0, stream, p);
+    else              hipLaunchKernelGGL(sorted_bin_kernel<4>, dim3((unsigned)a.B), dim3(256), 0, stream, p);
     if (a.D * 4 < kSortedMinRowBytes && chunks <= kWave) {
         int sub_shift = 2;
         while ((1 << sub_shift) < chunks) ++sub_shift;                // 4 .. 64 lanes per row
-        if (vb == 16)     hipLaunchKernelGGL((sorted_reduce_narrow_kernel<16>), dim3(P), dim3(kSortedThreads), 0, stream, p, sub_shift);
-        else if (vb == 8) hipLaunchKernelGGL((sorted_reduce_narrow_kernel<8>), dim3(P), dim3(kSortedThreads), 0, stream, p, sub_shift);
-        else              hipLaunchKernelGGL((sorted_reduce_narrow_kernel<4>), dim3(P), dim3(kSortedThreads), 0, stream, p, sub_shift);
+#define FSA_LAUNCH_NARROW(VB_)                                                                              \
+    do {                                                                                                    \
+        if (p.slot_grad) hipLaunchKernelGGL((sorted_reduce_narrow_kernel<VB_, true>), dim3(P), dim3(kSortedThreads), 0, stream, p, sub_shift); \
+        else hipLaunchKernelGGL((sorted_reduce_narrow_kernel<VB_, false>), dim3(P), dim3(kSortedThreads), 0, stream, p, sub_shift); \
+    } while (0)
+        if (vb == 16) FSA_LAUNCH_NARROW(16);
+        else if (vb == 8) FSA_LAUNCH_NARROW(8);
+        else FSA_LAUNCH_NARROW(4);
+#undef FSA_LAUNCH_NARROW
         *used = true;
         return hipGetLastError();
     }
@@ -458,17 +511,23 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
     // per SIMD -- it is bound by dependent round trips per wave, which only more waves hide
     const int mt_t = tune_int("FSA_SORTED_MT", kSortedMaxTiles);
     const int mt = tiles < mt_t ? tiles : mt_t;
-#define FSA_LAUNCH_SORTED(VB_)                                                                              \
+#define FSA_LAUNCH_SORTED(VB_, MT_)                                                                         \
     do {                                                                                                    \
-        if (mt <= 1)      hipLaunchKernelGGL((sorted_reduce_kernel<VB_, 1>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
-        else if (mt <= 2) hipLaunchKernelGGL((sorted_reduce_kernel<VB_, 2>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
-        else if (mt <= 4) hipLaunchKernelGGL((sorted_reduce_kernel<VB_, 4>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
-        else if (mt <= 6) hipLaunchKernelGGL((sorted_reduce_kernel<VB_, 6>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
-        else              hipLaunchKernelGGL((sorted_reduce_kernel<VB_, 8>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
+        if (p.slot_grad) hipLaunchKernelGGL((sorted_reduce_kernel<VB_, MT_, true>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
+        else hipLaunchKernelGGL((sorted_reduce_kernel<VB_, MT_, false>), dim3(P), dim3(kSortedThreads), 0, stream, p); \
     } while (0)
-    if (vb == 16) FSA_LAUNCH_SORTED(16);
-    else if (vb == 8) FSA_LAUNCH_SORTED(8);
-    else FSA_LAUNCH_SORTED(4);
+#define FSA_LAUNCH_SORTED_MT(VB_)                                                                           \
+    do {                                                                                                    \
+        if (mt <= 1)      FSA_LAUNCH_SORTED(VB_, 1);                                                        \
+        else if (mt <= 2) FSA_LAUNCH_SORTED(VB_, 2);                                                        \
+        else if (mt <= 4) FSA_LAUNCH_SORTED(VB_, 4);                                                        \
+        else if (mt <= 6) FSA_LAUNCH_SORTED(VB_, 6);                                                        \
+        else              FSA_LAUNCH_SORTED(VB_, 8);                                                        \
+    } while (0)
+    if (vb == 16) FSA_LAUNCH_SORTED_MT(16);
+    else if (vb == 8) FSA_LAUNCH_SORTED_MT(8);
+    else FSA_LAUNCH_SORTED_MT(4);
+#undef FSA_LAUNCH_SORTED_MT
 #undef FSA_LAUNCH_SORTED
     *used = true;
     return hipGetLastError();
