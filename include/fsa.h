@@ -133,17 +133,19 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
  * The atomic backward is bound by the L2 atomic unit (one 4-byte add per channel and clock), and
  * that cost grows with the row width.  Given a workspace, 2-hop calls that move enough row bytes
  * update every destination row once, with plain loads and stores by one wave that owns it (Sec. 3.3
- * only fixes WHICH rows receive gradient; how is ours), by one of two routes: large calls with wide
- * rows bin the leaf entries by row, sort each bin in LDS and sum a row's gradients in registers; other
- * calls (rows of 384 bytes and more, at least 48 MiB of row updates, 32 MiB from 1024 bytes on) look
- * every leaf's row up in hashed buckets.  Without overflow of a bin, and unless a row is sampled more
- * than 16 times in a call that takes the second route, the result is bit-reproducible.  Calls that are
- * not eligible, a NULL workspace, one that is too small or not 256-byte aligned: the call behaves
+ * only fixes WHICH rows receive gradient; how is ours), by one of two routes: wide rows (at least 1024
+ * bytes, at most 8 x 64 chunks of 16 / 8 / 4 bytes -- the widest the row size and the pointers'
+ * alignment allow -- and at least 32 MiB of row updates per call), and rows of 256 .. 1023 bytes with
+ * at least 393,216 leaf slots (B*k1*k2): the leaf entries are binned by destination row, each bin is
+ * sorted in LDS and the gradients that reach one row are summed in registers; without overflow of a
+ * bin (rows sampled thousands of times in one batch) this route is bit-reproducible.  Other calls
+ * (rows of 384 bytes and more, at least 48 MiB of row updates, 32 MiB from 1024 bytes on) look every
+ * leaf's row up in hashed buckets, bit-reproducibly unless a row is sampled more than 16 times or many
+ * fall into one bucket.  Calls that are not eligible, a NULL workspace, one that is too small or not 256-byte aligned: the call behaves
  * exactly as fsa_mean_bwd.
  *   workspace        device memory, contents irrelevant on entry, overwritten
- *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what rows of at least
- *                    1024 bytes (32 MiB of row updates) and calls of at least 393,216 leaf slots can
- *                    use, 0 for other shapes; fsa_bwd_workspace_bytes below covers all of them
+ *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what the first route can
+ *                    use, 0 for shapes it does not take; fsa_bwd_workspace_bytes below covers all of them
  */
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D);
 int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,

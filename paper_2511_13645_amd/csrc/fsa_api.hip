@@ -163,10 +163,7 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
 
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D) {
     if (B <= 0 || D <= 0 || !fanout_ok(k1) || !fanout_ok(k2)) return 0;
-    const int64_t s = (int64_t)fsa::sorted_workspace_bytes(B, k1, k2, D);
-    if (s == 0) return 0;
-    const int64_t o = (int64_t)fsa::owned_workspace_bytes(B, k1, k2, D, 4);   // one of the two routes takes the call
-    return s > o ? s : o;
+    return (int64_t)fsa::sorted_workspace_bytes(B, k1, k2, D);
 }
 
 int64_t fsa_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int grad_x_dtype) {

@@ -418,11 +418,6 @@ __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_narrow_kernel(co
 // 614 k leaves, 237 -> 210 us; but 154 k leaves, 64 -> 75 us.
 constexpr int64_t kSortedMinRowBytes = kSortedWideRowBytes;
 constexpr int64_t kSortedMinPayload = 32ll << 20;
-// With fewer leaf slots than this the leaf-major owning route (fsa_bwd_owned.hip) is ahead, whose look-ups
-// cost less than the sort but which gathers more once most rows are shared: 1024-byte rows 38 against
-// 30 us at 38 k leaf slots, 56 against 51 us at 77 k, 86 against 85 us at 154 k; 1200-byte rows of a dense
-// graph 115 against 125 us at 180 k, 2408-byte rows 230 against 312 us at 256 k.
-constexpr int64_t kSortedWideMinEntries = 160 * 1000;
 constexpr int64_t kSortedNarrowMinRowBytes = 256;
 constexpr int64_t kSortedNarrowMinEntries = 384 * 1024;
 
@@ -460,7 +455,6 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
     *used = false;
     if (!a.ids2 || a.grad_kind != 0 || a.grad_x_kind != 0 || a.root_valid || !workspace) return hipSuccess;
     if (!sorted_backward_shape_ok(a.B, a.k1, a.k2, a.D)) return hipSuccess;
-    if (a.B * a.k1 * a.k2 < kSortedWideMinEntries) return hipSuccess;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return hipSuccess;
     size_t off[6], total;
     int lp;

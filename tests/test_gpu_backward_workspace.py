@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from parity_util import assert_close, to_f64
+from parity_util import assert_close, marked_workspace, to_f64, workspace_route
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,27 @@ def test_wide_rows_take_the_owning_route(fsa, orc, D):
     while B * k1 * k2 * D * 4 < (36 << 20):
         B *= 2
     _check(fsa, orc, B, k1, k2, D, 20000, D, with_h1=(D != 1000), reproducible=(D != 513))
+
+
+def test_wide_rows_sampled_dozens_of_times_stay_reproducible(fsa):
+    """The promise of the sorted route holds from its smallest calls on: 38,400 leaf slots of 1 KB rows, each row
+    sampled about 60 times, no bin over its 256 entries."""
+    rng = np.random.default_rng(7)
+    dev = "cuda:0"
+    B, k1, k2, D, n = 256, 15, 10, 256, 600
+    ids1, ids2 = (torch.from_numpy(a).to(dev) for a in _ids(rng, B, k1, k2, n, dup=False))
+    g = torch.from_numpy(rng.standard_normal((B, D)).astype(np.float32)).to(dev)
+    need = fsa.fsa_mean_bwd_workspace_bytes(B, k1, k2, D)
+    assert need > 0
+    ws = marked_workspace(need)
+    got = []
+    for _ in range(4):
+        gx = torch.zeros((n, D), device=dev)
+        fsa.fsa_mean_bwd_ws(g, ids1, ids2, grad_x=gx, workspace=ws)
+        got.append(gx)
+    torch.cuda.synchronize()
+    assert workspace_route(ws) == "sorted"
+    assert all(torch.equal(got[0], t) for t in got[1:]), "runs of the sorted route differ"
 
 
 def test_social_like_shape_with_shared_rows(fsa, orc):
