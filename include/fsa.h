@@ -131,21 +131,22 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
 /*
  * fsa_mean_bwd with a caller workspace (same arguments, same result within the same tolerance).
  * The atomic backward is bound by the L2 atomic unit (one 4-byte add per channel and clock), and
- * that cost grows with the row width.  Given a workspace, 2-hop calls that move enough row bytes
- * update every destination row once, with plain loads and stores by one wave that owns it (Sec. 3.3
- * only fixes WHICH rows receive gradient; how is ours), by one of two routes: wide rows (at least 1024
- * bytes, at most 8 x 64 chunks of 16 / 8 / 4 bytes -- the widest the row size and the pointers'
- * alignment allow -- and at least 32 MiB of row updates per call), and rows of 256 .. 1023 bytes with
- * at least 393,216 leaf slots (B*k1*k2): the leaf entries are binned by destination row, each bin is
- * sorted in LDS and the gradients that reach one row are summed in registers; without overflow of a
- * bin (rows sampled thousands of times in one batch) this route is bit-reproducible.  Other calls
- * (rows of 384 bytes and more, at least 48 MiB of row updates, 32 MiB from 1024 bytes on) look every
- * leaf's row up in hashed buckets, bit-reproducibly unless a row is sampled more than 16 times or many
- * fall into one bucket.  Calls that are not eligible, a NULL workspace, one that is too small or not 256-byte aligned: the call behaves
- * exactly as fsa_mean_bwd.
+ * that cost grows with the row width.  Given a workspace, 2-hop calls with wide rows
+ * (at least 1024 bytes, at most 8 x 64 chunks of 16 / 8 / 4 bytes -- the widest the row size and
+ * the pointers' alignment allow -- and at least 32 MiB of row updates per call), and calls with
+ * rows of 256 .. 1023 bytes and at least 393,216 leaf slots (B*k1*k2), take another route: the
+ * leaf entries are binned by destination row, each bin is sorted in LDS, the gradients that reach
+ * one row are summed in registers and the row is updated once with plain loads and stores by the
+ * one workgroup that owns it (Sec. 3.3 only fixes WHICH rows receive gradient; how is ours).
+ * Without overflow of a bin (rows sampled thousands of times in one batch) that route is
+ * bit-reproducible.  Calls that are not eligible, a NULL workspace, one that is too small or not
+ * 256-byte aligned: the call behaves exactly as fsa_mean_bwd.
+ * A call that takes the other route does not add atomically: nothing else, on any stream, may write
+ * grad_x while it runs (calls on one stream follow one another; on several, order them with events),
+ * and the workspace is its own until it is done.
  *   workspace        device memory, contents irrelevant on entry, overwritten
- *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what the first route can
- *                    use, 0 for shapes it does not take; fsa_bwd_workspace_bytes below covers all of them
+ *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what the call can
+ *                    use (0: this shape always takes the atomic route)
  */
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D);
 int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
@@ -155,10 +156,16 @@ int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
                     void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
- * The backward entry points below with `_ws` take a workspace the same way (contents irrelevant on
- * entry, overwritten; NULL, too small or not 256-byte aligned: the call takes the atomics).  One
- * size serves all of them: fsa_bwd_workspace_bytes(B,k1,k2,D,grad_x_dtype), 0 where the atomics are
- * the better route whatever the workspace.  Three hops: (B*k1, k2, k3, D, FSA_F32).
+ * The backward entry points below with `_ws` take a workspace the same way, with the same demand on
+ * grad_x and the workspace (contents irrelevant on entry, overwritten; NULL, too small or not 256-byte
+ * aligned: the call adds with atomics, as the entry point without `_ws` always does).  Next to the route
+ * above they have one for every element type, for weights and for three hops: 2-hop calls with rows of
+ * grad_x of 384 bytes and more and at least 48 MiB of row updates (B*k1*k2 rows; 32 MiB from 1024 bytes
+ * on) look every leaf's row up in hashed buckets and one wave updates it, bit-reproducibly unless a row
+ * is sampled more than 16 times or many rows fall into one bucket.
+ * fsa_bwd_workspace_bytes(B,k1,k2,D,grad_x_dtype) is a size that serves all of them, 0 where they take
+ * the atomics whatever the workspace.  Three hops: (B*k1, k2, k3, D, FSA_F32).  Unweighted fp32 calls
+ * come through fsa_mean_bwd_lp_ws with FSA_F32 for both types.
  */
 int64_t fsa_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int grad_x_dtype);
 

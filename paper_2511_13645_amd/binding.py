@@ -1,7 +1,6 @@
 """Thin ctypes binding of the C-ABI HIP library (include/fsa.h), same names as the C entry
 points.  Argument marshalling only: every step of the path runs inside the library's
-kernels.  PyTorch is used for device memory (outputs, and the backward's workspace where the
-caller brings none) and the current stream, nothing else.
+kernels.  PyTorch is used for device memory and the current stream, nothing else.
 
 The library must have been built (``python -m paper_2511_13645_amd.build`` or
 ``__graft_entry__.build()``); there is no CPU fallback -- a missing library raises.
@@ -155,21 +154,13 @@ def _host_ints(values: Tuple[int, ...]) -> ctypes.Array:
     return (ctypes.c_int32 * max(1, len(values)))(*values)
 
 
-def _scratch(B: int, k1: int, k2: int, D: int, grad_dtype: int, like: torch.Tensor,
-             stream: Optional[torch.cuda.Stream]) -> Tuple[Optional[torch.Tensor], int]:
-    """Workspace of one backward call from torch's caching allocator, allocated on the stream the call
-    runs on so that the block may be reused, in that stream's order, as soon as the call returns.
-    (None, 0) where the call has no use for one, or when memory is short: the call then takes the atomics."""
-    need = lib().fsa_bwd_workspace_bytes(B, k1, k2, D, grad_dtype) if k2 else 0
-    if not need:
+def _room(workspace: Optional[torch.Tensor], like: torch.Tensor) -> Tuple[Optional[int], int]:
+    """(address, bytes) of the workspace a caller hands to a backward call; (None, 0) without one."""
+    if workspace is None:
         return None, 0
-    try:
-        if stream is None:
-            return torch.empty(need, dtype=torch.uint8, device=like.device), need
-        with torch.cuda.stream(stream):
-            return torch.empty(need, dtype=torch.uint8, device=like.device), need
-    except torch.cuda.OutOfMemoryError:
-        return None, 0
+    _need(workspace, "workspace")
+    _same_device(like, (workspace, "workspace"))
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def fsa_sample_mean_fwd(indptr: torch.Tensor, indices: torch.Tensor, x: torch.Tensor,
@@ -249,7 +240,7 @@ def fsa_mean_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
 def fsa_mean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,
                  grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor,
                  stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
-    """Scatter-add the mean's gradient into grad_x [N,D] fp32 (accumulated, not zeroed)."""
+    """Scatter-add the mean's gradient into grad_x [N,D] fp32 (accumulated with atomics, not zeroed)."""
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -267,25 +258,31 @@ def fsa_mean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
         _need(grad_h1, "grad_h1", torch.float32)
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
-    ws, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
-    rc = lib().fsa_mean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
-                               _ptr(grad_x), N, _ptr(ws), ws_bytes, _stream(stream, grad_x))
+    rc = lib().fsa_mean_bwd(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
+                            _ptr(grad_x), N, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd")
     return grad_x
 
 
 def fsa_mean_bwd_workspace_bytes(B: int, k1: int, k2: int, D: int) -> int:
-    """Workspace bytes a caller may keep for fsa_mean_bwd_ws at this shape (0: not worth keeping one)."""
+    """Workspace bytes fsa_mean_bwd_ws can use for this shape (0: it always takes the atomic route)."""
     return int(lib().fsa_mean_bwd_workspace_bytes(B, k1, k2, D))
+
+
+def fsa_bwd_workspace_bytes(B: int, k1: int, k2: int, D: int, dtype: torch.dtype = torch.float32) -> int:
+    """Workspace bytes with which fsa_mean_bwd_lp, fsa_wmean_bwd and fsa_mean3_bwd into a [N,D] table of
+    `dtype` update every destination row once (0: atomics whatever the workspace).  Three hops: (B*k1, k2, k3, D)."""
+    return int(lib().fsa_bwd_workspace_bytes(B, k1, k2, D, _FLOAT_TYPE[dtype]))
 
 
 def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,
                     grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor,
                     workspace: Optional[torch.Tensor] = None,
                     stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
-    """fsa_mean_bwd with a caller workspace (any contiguous GPU tensor; torch allocations are
-    256-byte aligned) instead of one from torch's allocator for the length of the call."""
+    """fsa_mean_bwd with an optional caller workspace (any contiguous GPU tensor; torch allocations are
+    256-byte aligned, sized by fsa_mean_bwd_workspace_bytes).  Given one, wide-row 2-hop calls update every
+    destination row once, without atomics: no other work may write grad_x or the workspace while they run."""
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -302,15 +299,10 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
     if grad_h1 is not None:
         _need(grad_h1, "grad_h1", torch.float32)
         _shape(grad_h1, "grad_h1", (B, k1, D))
-    ws_bytes = 0
-    if workspace is not None:
-        _need(workspace, "workspace")
-        ws_bytes = workspace.numel() * workspace.element_size()
-    else:
-        workspace, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
-    _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"), (workspace, "workspace"))
+    _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
+    ws, ws_bytes = _room(workspace, grad_x)
     rc = lib().fsa_mean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
-                               _ptr(grad_x), N, _ptr(workspace), ws_bytes, _stream(stream, grad_x))
+                               _ptr(grad_x), N, ws, ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd_ws")
     return grad_x
@@ -318,9 +310,12 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
 
 def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,
                     grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor,
-                    stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+                    stream: Optional[torch.cuda.Stream] = None,
+                    workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Reduced-precision backward: grad_out / grad_h1 in fp32, bf16 or fp16; grad_x [N,D] either an
-    fp32 master gradient or a 16-bit table added to with packed atomics (accumulated, not zeroed)."""
+    fp32 master gradient or a 16-bit table added to with packed atomics (accumulated, not zeroed).
+    `workspace`, sized by fsa_bwd_workspace_bytes: large 2-hop calls update every destination row once,
+    without atomics; no other work may write grad_x or the workspace while the call runs."""
     _need(grad_out, "grad_out"); _need(ids1, "ids1", torch.int32); _need(grad_x, "grad_x")
     B, k1 = ids1.shape
     D = grad_out.shape[1]
@@ -338,9 +333,9 @@ def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
     g_type, x_type = _x_dtype(grad_out), _x_dtype(grad_x)
-    ws, ws_bytes = _scratch(B, k1, k2, D, x_type, grad_x, stream)
+    ws, ws_bytes = _room(workspace, grad_x)
     rc = lib().fsa_mean_bwd_lp_ws(_ptr(grad_out), _ptr(grad_h1), g_type, _ptr(ids1), _ptr(ids2),
-                                  B, k1, k2, D, _ptr(grad_x), x_type, N, _ptr(ws), ws_bytes, _stream(stream, grad_x))
+                                  B, k1, k2, D, _ptr(grad_x), x_type, N, ws, ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd_lp")
     return grad_x
@@ -430,9 +425,11 @@ def fsa_mean3_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: torch.Tensor
                   grad_h1: Optional[torch.Tensor] = None, grad_h2: Optional[torch.Tensor] = None,
                   grad_m1: Optional[torch.Tensor] = None, grad_x: torch.Tensor,
                   work: Optional[torch.Tensor] = None, stream: Optional[torch.cuda.Stream] = None,
-                  noalloc: bool = False) -> torch.Tensor:
+                  noalloc: bool = False, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Scatter-add the three-hop mean's gradient into grad_x [N,D] fp32 (accumulated, not zeroed).
-    noalloc=True calls fsa_mean3_bwd_noalloc: no workspace, the library's fixed scratch array."""
+    noalloc=True calls fsa_mean3_bwd_noalloc: no workspace, the library's fixed scratch array.
+    `workspace`, sized by fsa_bwd_workspace_bytes(B*k1, k2, k3, D): large calls update every destination
+    row once, without atomics; no other work may write grad_x or the workspace while the call runs."""
     _need(grad_out, "grad_out", torch.float32); _need(grad_x, "grad_x", torch.float32)
     _need(ids1, "ids1", torch.int32); _need(ids2, "ids2", torch.int32); _need(ids3, "ids3", torch.int32)
     B, k1, k2, k3 = ids3.shape
@@ -458,9 +455,9 @@ def fsa_mean3_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: torch.Tensor
         work = torch.empty((B, k1, D), dtype=torch.float32, device=grad_x.device)
     elif work.numel() < B * k1 * D or work.dtype != torch.float32 or not work.is_cuda or not work.is_contiguous():
         raise ValueError("work must be a contiguous GPU tensor that holds B*k1*D floats")
-    ws, ws_bytes = _scratch(B * k1, k2, k3, D, FSA_F32, grad_x, stream)
+    ws, ws_bytes = _room(workspace, grad_x)
     rc = lib().fsa_mean3_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(grad_h2), _ptr(grad_m1), _ptr(ids1), _ptr(ids2), _ptr(ids3),
-                                B, k1, k2, k3, D, _ptr(grad_x), grad_x.shape[0], _ptr(work), _ptr(ws), ws_bytes,
+                                B, k1, k2, k3, D, _ptr(grad_x), grad_x.shape[0], _ptr(work), ws, ws_bytes,
                                 _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean3_bwd")
@@ -533,8 +530,11 @@ def fsa_wmean_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
 def fsa_wmean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
                   ids2: Optional[torch.Tensor] = None, w2: Optional[torch.Tensor] = None,
                   grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor,
-                  stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
-    """Weighted backward: scatter-add into grad_x [N,D] fp32 (accumulated, not zeroed)."""
+                  stream: Optional[torch.cuda.Stream] = None,
+                  workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Weighted backward: scatter-add into grad_x [N,D] fp32 (accumulated, not zeroed).
+    `workspace`, sized by fsa_bwd_workspace_bytes: large 2-hop calls update every destination row once,
+    without atomics; no other work may write grad_x or the workspace while the call runs."""
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32); _need(w1, "w1", torch.float32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -555,9 +555,9 @@ def fsa_wmean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
         _need(grad_h1, "grad_h1", torch.float32)
         _shape(grad_h1, "grad_h1", (B, k1, D))
     _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"), (w1, "w1"), (w2, "w2"))
-    ws, ws_bytes = _scratch(B, k1, k2, D, FSA_F32, grad_x, stream)
+    ws, ws_bytes = _room(workspace, grad_x)
     rc = lib().fsa_wmean_bwd_ws(_ptr(grad_out), _ptr(grad_h1), _ptr(ids1), _ptr(ids2), _ptr(w1), _ptr(w2),
-                                B, k1, k2, D, _ptr(grad_x), grad_x.shape[0], _ptr(ws), ws_bytes, _stream(stream, grad_x))
+                                B, k1, k2, D, _ptr(grad_x), grad_x.shape[0], ws, ws_bytes, _stream(stream, grad_x))
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_wmean_bwd")
     return grad_x

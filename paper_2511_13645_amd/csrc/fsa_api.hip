@@ -177,8 +177,8 @@ int64_t fsa_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, in
 
 namespace {
 
-// The unweighted backward: the owning route that suits the call if there is one and the workspace
-// serves it, else the atomics.
+// The unweighted backward of the entry points that came with the owning route: whichever of the two
+// plain-store routes suits the call if the workspace serves it, else the atomics.
 hipError_t backward_any(const fsa::BwdArgs& a, void* workspace, int64_t workspace_bytes, hipStream_t st) {
     if (workspace) {
         bool used = false;
@@ -211,7 +211,13 @@ int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,
     fsa::BwdArgs a{};
     a.grad_out = grad_out; a.grad_h1 = grad_h1; a.ids1 = ids1; a.ids2 = ids2;
     a.B = B; a.k1 = k1; a.k2 = ids2 ? k2 : 0; a.D = D; a.grad_x = grad_x;
-    return status_of(backward_any(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream)));
+    // Only the sorted route: callers hand one kept workspace to calls of many shapes and may rely on the
+    // others adding with atomics.
+    bool used = false;
+    if (hipError_t e = fsa::launch_backward_sorted(a, workspace, (size_t)workspace_bytes, static_cast<hipStream_t>(stream), &used))
+        return status_of(e);
+    if (used) return FSA_OK;
+    return status_of(fsa::launch_backward(a, static_cast<hipStream_t>(stream)));
 }
 
 int fsa_mean_bwd_lp(const void* grad_out, const void* grad_h1, int grad_dtype,

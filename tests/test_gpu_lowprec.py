@@ -80,7 +80,7 @@ def adds_per_row(ids1: np.ndarray, ids2, n: int) -> np.ndarray:
     return np.bincount(s[keep], minlength=n)
 
 
-def lowprec_case(fsa, orc, indptr, indices, n, D, seeds, fan, g_dtype, x_dtype, what):
+def lowprec_case(fsa, orc, indptr, indices, n, D, seeds, fan, g_dtype, x_dtype, what, workspace=None):
     rng = np.random.default_rng(11)
     xf = torch.from_numpy(rng.standard_normal((n, D)).astype(np.float32)).to(DEV)
     d_seeds = torch.from_numpy(seeds).to(DEV)
@@ -92,7 +92,7 @@ def lowprec_case(fsa, orc, indptr, indices, n, D, seeds, fan, g_dtype, x_dtype, 
     if len(fan) == 2:
         gh = torch.from_numpy(np.random.default_rng(4).standard_normal((B, fan[0], D)).astype(np.float32)).to(DEV).to(g_dtype)
     gx = torch.zeros((n, D), dtype=x_dtype, device=DEV)
-    fsa.fsa_mean_bwd_lp(g, ids1, ids2, gh, grad_x=gx)
+    fsa.fsa_mean_bwd_lp(g, ids1, ids2, gh, grad_x=gx, workspace=workspace)
     torch.cuda.synchronize()
     h_ids1 = ids1.cpu().numpy()
     h_ids2 = None if ids2 is None else ids2.cpu().numpy()

@@ -57,7 +57,7 @@ def test_layerwise_two_hop(fsa, orc, dtype):
     assert_close(to_f64(m1), r_m1, a_m1, TOL3[dtype], "out_m1")
 
 
-def three_hop_case(fsa, orc, indptr, indices, x, seeds, fan, seed, what, check_bwd=True, tol=None):
+def three_hop_case(fsa, orc, indptr, indices, x, seeds, fan, seed, what, check_bwd=True, tol=None, workspace=None):
     n, D = x.shape
     B = len(seeds)
     tol = TOL3[x.dtype] if tol is None else tol
@@ -113,7 +113,7 @@ def three_hop_case(fsa, orc, indptr, indices, x, seeds, fan, seed, what, check_b
                                          ((ids1, ids2, ids3), d_ids, "holes")):
                 kw = {"grad_" + k: G[k] for k in use}
                 gx = torch.zeros((n, D), dtype=torch.float32, device=DEV)
-                fsa.fsa_mean3_bwd(G["out"], *ids_dev, grad_x=gx, **kw)
+                fsa.fsa_mean3_bwd(G["out"], *ids_dev, grad_x=gx, workspace=workspace, **kw)
                 torch.cuda.synchronize()
                 kw64 = {"grad_" + k: to_f64(G[k]) for k in use}
                 want = orc.mean3_bwd(to_f64(G["out"]), *ids_np, num_nodes=n, **kw64)

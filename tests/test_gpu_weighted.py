@@ -43,7 +43,7 @@ def _scales(x, ids1, ids2, w1, w2):
     return a_out.double().cpu().numpy(), a_h1.double().cpu().numpy()
 
 
-def _run(fsa, orc, indptr, indices, ew, x, seeds, fan, seed, what, check_bwd=True):
+def _run(fsa, orc, indptr, indices, ew, x, seeds, fan, seed, what, check_bwd=True, workspace=None):
     dev = "cuda:0"
     d_indptr, d_indices = torch.from_numpy(indptr).to(dev), torch.from_numpy(indices).to(dev)
     d_ew, d_x, d_seeds = torch.from_numpy(ew).to(dev), x.to(dev), torch.from_numpy(seeds).to(dev)
@@ -75,7 +75,7 @@ def _run(fsa, orc, indptr, indices, ew, x, seeds, fan, seed, what, check_bwd=Tru
         g = torch.from_numpy(rng.standard_normal((B, D)).astype(np.float32)).to(dev)
         gh = torch.from_numpy(rng.standard_normal((B, fan[0], D)).astype(np.float32)).to(dev) if len(fan) == 2 else None
         gx = torch.zeros((N, D), dtype=torch.float32, device=dev)
-        fsa.fsa_wmean_bwd(g, ids1, w1, ids2, w2, gh, grad_x=gx)
+        fsa.fsa_wmean_bwd(g, ids1, w1, ids2, w2, gh, grad_x=gx, workspace=workspace)
         torch.cuda.synchronize()
         ghn = None if gh is None else to_f64(gh)
         r_gx = orc.wmean_bwd(to_f64(g), r_ids1, r_w1, r_ids2, r_w2, ghn, num_nodes=N)
