@@ -437,11 +437,19 @@ hipError_t launch_deep_grad(const float* grad_out, const float* grad_h1, const i
                             const int32_t* ids3, float* work, int64_t B, int k1, int k2, int k3, int64_t D,
                             hipStream_t stream) {
     auto al = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
-    const dim3 grid((unsigned)B), block(256);
-    if (D % 4 == 0 && al(grad_out) && al(grad_h1) && al(work))
-        hipLaunchKernelGGL(deep_grad_kernel<4>, grid, block, 0, stream, grad_out, grad_h1, ids1, ids2, ids3, work, k1, k2, k3, D);
-    else
-        hipLaunchKernelGGL(deep_grad_kernel<1>, grid, block, 0, stream, grad_out, grad_h1, ids1, ids2, ids3, work, k1, k2, k3, D);
+    const bool quads = D % 4 == 0 && al(grad_out) && al(grad_h1) && al(work);
+    const int64_t most = 1 << 23;                                    // roots of a launch, which takes fewer than 2^32 threads
+    for (int64_t b = 0; b < B; b += most) {
+        const dim3 grid((unsigned)(B - b < most ? B - b : most)), block(256);
+        const float* go = grad_out + b * D;
+        const float* gh = grad_h1 ? grad_h1 + b * k1 * D : nullptr;
+        const int32_t* q1 = ids1 + b * k1;
+        const int32_t* q2 = ids2 + b * k1 * k2;
+        const int32_t* q3 = ids3 + b * k1 * k2 * k3;
+        float* w = work + b * k1 * D;
+        if (quads) hipLaunchKernelGGL(deep_grad_kernel<4>, grid, block, 0, stream, go, gh, q1, q2, q3, w, k1, k2, k3, D);
+        else       hipLaunchKernelGGL(deep_grad_kernel<1>, grid, block, 0, stream, go, gh, q1, q2, q3, w, k1, k2, k3, D);
+    }
     return hipGetLastError();
 }
 

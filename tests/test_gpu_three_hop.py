@@ -188,3 +188,23 @@ def test_three_hop_empty_batch_and_degenerate_graph(fsa, orc):
     e = torch.zeros(0, dtype=torch.int32, device=DEV)
     r = fsa.fsa_sample_mean3_fwd(d_indptr, d_indices, x.to(DEV), e, [4, 3, 2], 1)
     assert r["out"].shape == (0, D)
+
+
+@pytest.mark.parametrize("B", [(1 << 23) + 1, (1 << 24) + 3])
+def test_backward_of_more_roots_than_one_launch_takes(fsa, B):
+    """A workgroup per root of 256 threads: 2^24 roots would be 2^32 threads.  One leaf per root, so grad_x is a
+    histogram weighted by grad_out: about 170 additions into an element, 1e-5 of their magnitudes."""
+    n = 100_000
+    gen = torch.Generator(device=DEV).manual_seed(B)
+    ids = torch.randint(0, n, (B,), generator=gen, device=DEV, dtype=torch.int32)
+    ids[::5] = -1
+    g = torch.randn((B, 1), generator=gen, device=DEV)
+    one = torch.zeros((B, 1), dtype=torch.int32, device=DEV)
+    gx = torch.zeros((n, 1), device=DEV)
+    fsa.fsa_mean3_bwd(g, one, one.view(B, 1, 1), ids.view(B, 1, 1, 1), grad_x=gx)
+    torch.cuda.synchronize()
+    leaf, w = ids.cpu().numpy(), to_f64(g)[:, 0]
+    live = leaf >= 0
+    want = np.bincount(leaf[live], weights=w[live], minlength=n)[:, None]
+    mag = np.bincount(leaf[live], weights=np.abs(w[live]), minlength=n)[:, None]
+    assert_close(to_f64(gx), want, mag, 1e-5, "grad_x of %d roots" % B)
