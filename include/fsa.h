@@ -147,6 +147,8 @@ int fsa_mean_bwd(const float* grad_out, const float* grad_h1,
  *   workspace        device memory, contents irrelevant on entry, overwritten
  *   workspace_bytes  its size; fsa_mean_bwd_workspace_bytes(B,k1,k2,D) returns what the call can
  *                    use (0: this shape always takes the atomic route)
+ *                    It may end in B*k1*D floats for rows that calls with grad_h1 combine per slot;
+ *                    a workspace without them serves too, and the call gathers both rows per leaf.
  */
 int64_t fsa_mean_bwd_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D);
 int fsa_mean_bwd_ws(const float* grad_out, const float* grad_h1,

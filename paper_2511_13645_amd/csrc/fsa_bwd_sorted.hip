@@ -66,6 +66,13 @@ static int sorted_log_p(int64_t B, int k1, int k2, int64_t D) {
     return lp;
 }
 
+// One gathered row per leaf instead of two (grad_h1 given), against a pass over the slots' rows.  Forward and
+// backward: 400-byte rows at 614 k leaf slots 287 -> 241 us, 2408-byte rows at 256 k 346 -> 329 us; 1200-byte rows
+// at 180 k (22 MB of slot rows) 204 -> 210 us, so wide rows from 32 MiB of slot rows on.
+static bool sorted_combines(int64_t B, int k1, int64_t D) {
+    return D * 4 < kSortedWideRowBytes || B * k1 * D * 4 >= (32ll << 20);
+}
+
 static void sorted_layout(int64_t B, int k1, int k2, int64_t D, size_t off[6], size_t& total, int& log_p) {
     log_p = sorted_log_p(B, k1, k2, D);
     const size_t P = (size_t)1 << log_p;
@@ -76,7 +83,8 @@ static void sorted_layout(int64_t B, int k1, int k2, int64_t D, size_t off[6], s
     off[2] = o; o += up((size_t)B * k1 * sizeof(float2));                  // coef
     off[3] = o; o += up(P * kBucketCap * sizeof(unsigned long long));      // pairs
     off[4] = o; o += up((size_t)B * k1 * k2 * sizeof(unsigned long long)); // overflow
-    off[5] = o; o += up((size_t)B * k1 * D * sizeof(float));               // slot_grad
+    off[5] = o;                                                            // slot_grad
+    if (sorted_combines(B, k1, D)) o += up((size_t)B * k1 * D * sizeof(float));
     total = o;
 }
 
@@ -476,11 +484,7 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
     p.ws.pairs = reinterpret_cast<unsigned long long*>(w + off[3]);
     p.ws.overflow = reinterpret_cast<unsigned long long*>(w + off[4]);
     p.ws.log_p = lp;
-    // One gathered row per leaf instead of two, against a pass over the slots' rows.  Forward and backward:
-    // 400-byte rows at 614 k leaf slots 287 -> 241 us, 2408-byte rows at 256 k 346 -> 329 us; 1200-byte rows at
-    // 180 k (22 MB of slot rows) 204 -> 210 us, so wide rows from 32 MiB of slot rows on.
-    const bool combine = a.D * 4 < kSortedMinRowBytes || a.B * a.k1 * a.D * 4 >= (32ll << 20);
-    p.slot_grad = a.grad_h1 && combine && workspace_bytes >= total ? reinterpret_cast<float*>(w + off[5]) : nullptr;
+    p.slot_grad = a.grad_h1 && sorted_combines(a.B, a.k1, a.D) && workspace_bytes >= total ? reinterpret_cast<float*>(w + off[5]) : nullptr;
     const int P = 1 << lp;
     hipLaunchKernelGGL(sorted_clear_kernel, dim3((P + 255) / 256), dim3(256), 0, stream, p.ws.cursor, P, p.ws.overflow_count);
     if (vb == 16)     hipLaunchKernelGGL(sorted_bin_kernel<16>, dim3((unsigned)a.B), dim3(256), 0, stream, p);

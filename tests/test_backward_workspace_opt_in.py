@@ -63,3 +63,16 @@ def test_the_callers_workspace_reaches_the_library(library, name):
     entry, args = library.calls[-1]
     assert entry == (name if name.endswith("_ws") else name + "_ws")
     assert args[-3] == ws.data_ptr() and args[-2] == 600
+
+
+@pytest.mark.parametrize("b,k1,k2,d,slot_rows", [(1200, 15, 10, 300, False), (256, 15, 10, 256, False),       # wide, under 32 MiB of them
+                                                 (1024, 25, 10, 602, True), (4096, 15, 10, 100, True)])
+def test_room_for_slot_rows_only_where_a_call_writes_them(b, k1, k2, d, slot_rows):
+    leaves, up = b * k1 * k2, lambda v: (v + 255) // 256 * 256
+    buckets = 1
+    while buckets * (32 if d * 4 >= 1024 else 64) < leaves:
+        buckets *= 2
+    need = up(buckets * 128) + 256 + up(b * k1 * 8) + up(buckets * 256 * 8) + up(leaves * 8)
+    if slot_rows:
+        need += up(b * k1 * d * 4)
+    assert binding.fsa_mean_bwd_workspace_bytes(b, k1, k2, d) == need
