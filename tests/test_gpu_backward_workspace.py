@@ -34,7 +34,8 @@ def _ids(rng, B, k1, k2, n, holes=0.1, dup=True, targets=None):
     return ids1, ids2
 
 
-def _check(fsa, orc, B, k1, k2, D, n, seed, with_h1=True, targets=None, expect_route=True, reproducible=True):
+def _check(fsa, orc, B, k1, k2, D, n, seed, with_h1=True, targets=None, expect_route=True, reproducible=True,
+           route=None, without_slot_rows=False):
     rng = np.random.default_rng(seed)
     dev = "cuda:0"
     ids1, ids2 = _ids(rng, B, k1, k2, n, targets=targets)
@@ -42,13 +43,15 @@ def _check(fsa, orc, B, k1, k2, D, n, seed, with_h1=True, targets=None, expect_r
     gh = rng.standard_normal((B, k1, D)).astype(np.float32) if with_h1 else None
     need = fsa.fsa_mean_bwd_workspace_bytes(B, k1, k2, D)
     assert (need > 0) == expect_route, (need, expect_route)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
+    ws = marked_workspace(need - (B * k1 * D * 4 if without_slot_rows else 0))
     d = dict(g=torch.from_numpy(g).to(dev), gh=None if gh is None else torch.from_numpy(gh).to(dev),
              i1=torch.from_numpy(ids1).to(dev), i2=torch.from_numpy(ids2).to(dev))
     base = rng.standard_normal((n, D)).astype(np.float32)               # grad_x is accumulated into
     gx = torch.from_numpy(base.copy()).to(dev)
     fsa.fsa_mean_bwd_ws(d["g"], d["i1"], d["i2"], d["gh"], grad_x=gx, workspace=ws)
     fsa.fsa_mean_bwd_ws(d["g"], d["i1"], d["i2"], d["gh"], grad_x=gx, workspace=ws)      # twice: the workspace is reusable
+    torch.cuda.synchronize()
+    assert workspace_route(ws) == (route or ("sorted" if expect_route else "atomic"))
     gx_at = torch.from_numpy(base.copy()).to(dev)
     fsa.fsa_mean_bwd(d["g"], d["i1"], d["i2"], d["gh"], grad_x=gx_at)
     torch.cuda.synchronize()
@@ -65,6 +68,7 @@ def _check(fsa, orc, B, k1, k2, D, n, seed, with_h1=True, targets=None, expect_r
         torch.cuda.synchronize()
         if targets is None and reproducible:
             assert torch.equal(gx2, gx3), "two runs of the owning route differ"
+    return ws
 
 
 @pytest.mark.parametrize("D", [256, 260, 602, 1000, 513, 2048])
@@ -74,7 +78,19 @@ def test_wide_rows_take_the_owning_route(fsa, orc, D):
     B, k1, k2 = 256, 7, 10
     while B * k1 * k2 * D * 4 < (36 << 20):
         B *= 2
-    _check(fsa, orc, B, k1, k2, D, 20000, D, with_h1=(D != 1000), reproducible=(D != 513))
+    _check(fsa, orc, B, k1, k2, D, 20000, D, with_h1=(D != 1000), reproducible=(D != 513),
+           route="atomic" if D == 513 else "sorted")
+
+
+# with gradients into the slot means and at least 32 MiB of slot rows (any number for narrow rows) the binning kernel
+# writes one row per slot: 16-byte chunks, 4 and 8 tiles; 8-byte chunks; narrow rows, one and several per wave.  A
+# workspace that ends before these rows leaves the reduce kernels with both gradient rows.
+@pytest.mark.parametrize("without_slot_rows", [False, True])
+@pytest.mark.parametrize("B,k1,k2,D", [(400, 25, 4, 1024), (300, 14, 4, 2048), (600, 24, 3, 602), (4096, 10, 10, 100), (4100, 12, 8, 255)])
+def test_slot_rows_and_a_workspace_without_them(fsa, orc, B, k1, k2, D, without_slot_rows):
+    ws = _check(fsa, orc, B, k1, k2, D, 20000, D, without_slot_rows=without_slot_rows)
+    if not without_slot_rows:
+        assert bool((ws[-B * k1 * D * 4:] != 0xAB).any()), "no slot row was written"
 
 
 def test_wide_rows_sampled_dozens_of_times_stay_reproducible(fsa):
@@ -156,10 +172,48 @@ def test_missing_small_or_misaligned_workspace_falls_back(fsa, orc):
     assert need > 0
     ref = orc.mean_bwd(g.astype(np.float64), ids1, ids2, num_nodes=n)
     mag = orc.mean_bwd(np.abs(g).astype(np.float64), ids1, ids2, num_nodes=n)
-    big = torch.empty(need + 512, dtype=torch.uint8, device=dev)
+    big = marked_workspace(need + 512)
     for ws in (None, big[:need // 2], big[1:need + 1]):
         gx = torch.zeros((n, D), device=dev)
         fsa.fsa_mean_bwd_ws(torch.from_numpy(g).to(dev), torch.from_numpy(ids1).to(dev), torch.from_numpy(ids2).to(dev),
                             grad_x=gx, workspace=ws)
         torch.cuda.synchronize()
         assert_close(to_f64(gx), ref, mag, 1e-5, "fallback")
+    assert workspace_route(big) == "atomic"
+
+
+def test_a_missing_small_or_misaligned_workspace_falls_back_in_every_entry_point(fsa, orc):
+    """fp32 through the mixed-type call, 16-bit tables, weights and three hops: the atomics, whatever came as a workspace."""
+    rng = np.random.default_rng(12)
+    dev = "cuda:0"
+    B, k1, k2, k3, D, n = 300, 10, 10, 5, 128, 4000
+    f = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(dev)
+    i1, i2 = _ids(rng, B * 5, k1, k2, n)
+    j1, j2 = i1[:B], i2[:B]
+    j3 = rng.integers(-1, n, (B, k1, k2, k3)).astype(np.int32)
+    g, gh, w1, w2 = f(B * 5, D), f(B * 5, k1, D), f(B * 5, k1).abs(), f(B * 5, k1, k2).abs()
+    t = lambda a: torch.from_numpy(a).to(dev)
+    cases = [
+        (fsa.fsa_bwd_workspace_bytes(B * 5, k1, k2, D), torch.float32, lambda gx, ws: fsa.fsa_mean_bwd_lp(g, t(i1), t(i2), gh, grad_x=gx, workspace=ws),
+         lambda a: orc.mean_bwd(a(g), i1, i2, a(gh), num_nodes=n)),
+        (fsa.fsa_bwd_workspace_bytes(B * 5, k1, k2, D), torch.float32, lambda gx, ws: fsa.fsa_wmean_bwd(g, t(i1), w1, t(i2), w2, gh, grad_x=gx, workspace=ws),
+         lambda a: orc.wmean_bwd(a(g), i1, w1.cpu().numpy(), i2, w2.cpu().numpy(), a(gh), num_nodes=n)),
+        (fsa.fsa_bwd_workspace_bytes(B * k1, k2, k3, D), torch.float32,
+         lambda gx, ws: fsa.fsa_mean3_bwd(g[:B], t(j1), t(j2), t(j3), grad_h1=gh[:B], grad_x=gx, workspace=ws),
+         lambda a: orc.mean3_bwd(a(g[:B]), j1, j2, j3, num_nodes=n, grad_h1=a(gh[:B]))),
+    ]
+    for need, dtype, call, oracle in cases:
+        assert need > 0
+        ref, mag = oracle(to_f64), oracle(lambda v: np.abs(to_f64(v)))
+        big = marked_workspace(need + 512)
+        for ws in (None, big[:256], big[1:need + 1]):
+            gx = torch.zeros((n, D), dtype=dtype, device=dev)
+            call(gx, ws)
+            torch.cuda.synchronize()
+            assert_close(to_f64(gx), ref, mag, 1e-5, "fallback")
+        assert workspace_route(big) == "atomic"
+        gx = torch.zeros((n, D), dtype=dtype, device=dev)
+        call(gx, big)
+        torch.cuda.synchronize()
+        assert_close(to_f64(gx), ref, mag, 1e-5, "with the workspace")
+        assert workspace_route(big) == "owned"
