@@ -9,7 +9,8 @@ paper's optional flag.
 
 A bf16 / fp16 table gets its gradient in its own type, added with packed 16-bit atomics, or --
 when the caller passes ``master_grad``, an fp32 [N,D] tensor -- the backward accumulates into
-that master gradient instead and leaves ``x.grad`` unset.  ``workspace`` (any contiguous GPU
+that master gradient instead and leaves ``x.grad`` unset.  A master gradient is added to with
+atomics, so backward passes on several streams may share one.  ``workspace`` (any contiguous GPU
 tensor, optional) goes to ``fsa_mean_bwd_ws``: wide-row 2-hop backward passes over an fp32 table
 then update every destination row once instead of once per sampled leaf.
 """

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(512) void bwd2_kernel(const BwdParams p) {
 // One workgroup per root; the two-hop backward then runs over the B*k1 slots as its roots.  Bound by the
 // IDs' latency, then by the rows written: all threads look at IDs side by side, four of each level in
 // flight per thread, where a wave that went through the slots one after the other waited once per slot
-// (products, 15/10/5, B=1024, the whole training step: 323 -> 306 us).
+// (products, 15/10/5, B=1024: 21.1 -> 5.5 us).
 // ---------------------------------------------------------------------------------------
 template <int VE>
 __global__ __launch_bounds__(256) void deep_grad_kernel(const float* __restrict__ grad_out,

@@ -1,5 +1,6 @@
 // 2-hop backward without atomics on the feature rows, for wide rows (or large batches of rows
-// of 256 bytes and more) and a caller workspace (fsa_mean_bwd_ws).  The paper describes no backward kernel (Sec. 3.3 "Reproducibility" only
+// of 256 bytes and more) and a caller workspace (fsa_mean_bwd_ws): such a call may not share grad_x
+// with other work while it runs.  The paper describes no backward kernel (Sec. 3.3 "Reproducibility" only
 // asks that the saved IDs are replayed); this is the second design of this library.
 //
 // Why: a hardware fp32 atomic is one 4-byte operation per L2 channel and clock, so the atomic
