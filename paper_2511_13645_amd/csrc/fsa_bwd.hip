@@ -438,9 +438,8 @@ hipError_t launch_deep_grad(const float* grad_out, const float* grad_h1, const i
                             hipStream_t stream) {
     auto al = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
     const bool quads = D % 4 == 0 && al(grad_out) && al(grad_h1) && al(work);
-    const int64_t most = 1 << 23;                                    // roots of a launch, which takes fewer than 2^32 threads
-    for (int64_t b = 0; b < B; b += most) {
-        const dim3 grid((unsigned)(B - b < most ? B - b : most)), block(256);
+    for (int64_t b = 0; b < B; b += kMostRoots) {
+        const dim3 grid((unsigned)(B - b < kMostRoots ? B - b : kMostRoots)), block(256);
         const float* go = grad_out + b * D;
         const float* gh = grad_h1 ? grad_h1 + b * k1 * D : nullptr;
         const int32_t* q1 = ids1 + b * k1;
@@ -492,6 +491,11 @@ static hipError_t launch_backward_typed(const BwdArgs& a, const BwdParams& p, hi
 }
 
 hipError_t launch_backward(const BwdArgs& a, hipStream_t stream) {
+    if (a.ids2 && a.B > kMostRoots) {
+        for (int64_t b = 0; b < a.B; b += kMostRoots)
+            if (hipError_t e = launch_backward(backward_part(a, b, a.B - b < kMostRoots ? a.B - b : kMostRoots), stream)) return e;
+        return hipSuccess;
+    }
     BwdParams p;
     p.grad_out = a.grad_out; p.grad_h1 = a.grad_h1; p.ids1 = a.ids1; p.ids2 = a.ids2;
     p.grad_x = a.grad_x; p.B = a.B; p.D = a.D; p.k1 = a.k1; p.k2 = a.k2; p.root_valid = a.root_valid; p.w1 = nullptr;

@@ -444,7 +444,7 @@ bool sorted_backward_shape_ok(int64_t B, int k1, int k2, int64_t D) {
     } else if (B * k1 * k2 * D * 4 < kSortedMinPayload) {
         return false;
     }
-    if (B * k1 * k2 > (int64_t)INT32_MAX) return false;
+    if (B * k1 * k2 > (int64_t)INT32_MAX || B * kSortedThreads > (int64_t)UINT32_MAX) return false;  // a workgroup per root
     return D <= (int64_t)kSortedMaxTiles * kWave * 4;                 // fits the register tiles with 16-byte chunks
                                                                       // (the launch checks the real chunk width)
 }

@@ -57,6 +57,23 @@ struct BwdArgs {
     const int32_t* root_valid = nullptr;   // 2-hop, chained calls: [B], a negative entry switches root b off
 };
 
+// A launch of 2^32 threads or more is cut off without an error: kernels that take a workgroup of up to
+// 512 threads per root are launched on this many roots at a time.
+constexpr int64_t kMostRoots = 1 << 22;
+
+// Roots [b, b + n) of a 2-hop call.
+inline BwdArgs backward_part(const BwdArgs& a, int64_t b, int64_t n) {
+    const int gb = a.grad_kind == 0 ? 4 : 2;
+    BwdArgs c = a;
+    c.B = n;
+    c.grad_out = static_cast<const char*>(a.grad_out) + b * a.D * gb;
+    if (a.grad_h1) c.grad_h1 = static_cast<const char*>(a.grad_h1) + b * a.k1 * a.D * gb;
+    c.ids1 = a.ids1 + b * a.k1;
+    c.ids2 = a.ids2 + b * a.k1 * a.k2;
+    if (a.root_valid) c.root_valid = a.root_valid + b;
+    return c;
+}
+
 // Weighted mean: the same launches with per-edge weights (edge_w aligned with indices) and
 // the sampled weights emitted / taken back next to the IDs.
 struct WeightArgs {

@@ -98,6 +98,14 @@ __global__ __launch_bounds__(512) void wbwd2_kernel(const WBwdParams p) {
 }
 
 hipError_t launch_backward_weighted(const BwdArgs& a, const WeightArgs& w, hipStream_t stream) {
+    if (a.ids2 && a.B > kMostRoots) {
+        for (int64_t b = 0; b < a.B; b += kMostRoots) {
+            WeightArgs v = w;
+            v.w1 += b * a.k1; v.w2 += b * a.k1 * a.k2;
+            if (hipError_t e = launch_backward_weighted(backward_part(a, b, a.B - b < kMostRoots ? a.B - b : kMostRoots), v, stream)) return e;
+        }
+        return hipSuccess;
+    }
     WBwdParams p;
     // the weighted backward is fp32 on both sides
     p.grad_out = static_cast<const float*>(a.grad_out); p.grad_h1 = static_cast<const float*>(a.grad_h1);

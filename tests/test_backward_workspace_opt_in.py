@@ -76,3 +76,8 @@ def test_room_for_slot_rows_only_where_a_call_writes_them(b, k1, k2, d, slot_row
     if slot_rows:
         need += up(b * k1 * d * 4)
     assert binding.fsa_mean_bwd_workspace_bytes(b, k1, k2, d) == need
+
+
+def test_calls_of_more_roots_than_a_launch_takes_have_no_sorted_route():
+    assert binding.fsa_mean_bwd_workspace_bytes((1 << 24) - 1, 1, 1, 64) > 0
+    assert binding.fsa_mean_bwd_workspace_bytes(1 << 24, 1, 1, 64) == 0
