@@ -5,9 +5,9 @@
 // Mapping: the same ownership as the forward (wave per seed; workgroup per root with waves
 // owning interleaved hop-1 slots).  For each owned slot the wave first aggregates inside
 // itself: equal IDs within the slot (parallel edges) are merged into one entry with a
-// multiplicity, so each distinct row receives one atomic per element.  Lanes then map to
-// consecutive floats of the row, so one wave instruction adds 256 contiguous bytes with
-// hardware fp32 atomics resolved at L2.
+// multiplicity, so each distinct row receives one atomic per element.  Lanes then lie over 256
+// consecutive bytes of a row (fsa_atomic_rows.hip.h).
+#include "fsa_atomic_rows.hip.h"
 #include "fsa_device.hip.h"
 #include "fsa_internal.h"
 
@@ -20,6 +20,7 @@ struct BwdParams {
     void* grad_x; int64_t B; int64_t D; int k1, k2;
     const float* w1;                     // 1-hop weighted mean: [B,k1] weights of the sampled edges, else unused
     const int32_t* root_valid;           // 2-hop, nullable: [B], a negative entry switches root b off
+    RowLanes lanes;                      // 2-hop: how the lanes of a wave lie over destination rows
 };
 
 // ---------------------------------------------------------------------------------------
@@ -29,20 +30,9 @@ struct BwdParams {
 // lane would leave every instruction striding over twice as many cache lines: measured 1.7x
 // slower).  With a 16-bit grad_x a lane owns two consecutive elements (EPL = 2; D is even)
 // and adds the pair in ONE packed atomic (global_atomic_pk_add_bf16 / _f16), which halves the
-// number of atomic operations per row -- the L2 atomic unit, not bandwidth, bounds this
-// kernel.  Products and sums before the atomic are fp32; the value is rounded to the 16-bit
+// 64-byte segments per row -- their rate, not bandwidth, bounds this kernel.  Products and sums before the atomic are fp32; the value is rounded to the 16-bit
 // type once (nearest-even) and every packed atomic rounds the running sum again.
 // ---------------------------------------------------------------------------------------
-struct g_f32 { using T = float; };
-struct g_bf16 { using T = uint16_t; };
-struct g_f16 { using T = uint16_t; };
-
-template <typename GT, typename XG> struct Epl { static constexpr int value = 2; };
-template <typename GT> struct Epl<GT, g_f32> { static constexpr int value = 1; };
-
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 
 // EPL consecutive gradient elements starting at element index `idx` (even when EPL == 2).
 template <typename GT, int EPL>
@@ -71,27 +61,6 @@ __device__ __forceinline__ void load_grad(const void* base, int64_t idx, float (
             const f32x2_t f = __builtin_convertvector(h, f32x2_t);
             g[0] = f[0];
             g[1] = f[1];
-        }
-    }
-}
-
-// grad_x[idx .. idx+EPL) += v, by hardware atomics without a return value.
-template <typename XG, int EPL>
-__device__ __forceinline__ void atomic_add_row(void* base, int64_t idx, const float (&v)[EPL]) {
-    if constexpr (std::is_same<XG, g_f32>::value) {
-        float* p = static_cast<float*>(base) + idx;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) unsafeAtomicAdd(p + e, v[e]);          // global_atomic_add_f32
-    } else {
-        static_assert(EPL == 2, "16-bit grad_x takes packed pairs");
-        const f32x2_t f = {v[0], v[1]};
-        uint16_t* p = static_cast<uint16_t*>(base) + idx;
-        if constexpr (std::is_same<XG, g_bf16>::value) {
-            const bf16x2_t b = __builtin_convertvector(f, bf16x2_t);
-            __builtin_amdgcn_global_atomic_fadd_v2bf16(reinterpret_cast<bf16x2_t*>(p), b);
-        } else {
-            const f16x2_t h = __builtin_convertvector(f, f16x2_t);
-            __builtin_amdgcn_global_atomic_fadd_v2f16(reinterpret_cast<f16x2_t*>(p), h);
         }
     }
 }
@@ -140,6 +109,7 @@ __device__ __forceinline__ int hot_hash(int id) {
 template <typename GT, typename XG, bool WEIGHTED>
 __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, int hot_rows) {
     constexpr int EPL = Epl<GT, XG>::value;
+    using XE = typename XG::T;
     extern __shared__ int smem[];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -261,7 +231,7 @@ __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, 
 #pragma unroll
                         for (int c = 0; c < EPL; ++c) atomicAdd(&hot[(int64_t)hr * p.D + d + c], v[c]);
                     } else {
-                        atomic_add_row<XG, EPL>(p.grad_x, (int64_t)rows[e] * p.D + d, v);
+                        atomic_add_row<XG, EPL>(static_cast<XE*>(p.grad_x) + (int64_t)rows[e] * p.D + d, v);
                     }
                 }
             }
@@ -277,7 +247,7 @@ __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, 
                 float v[EPL];
 #pragma unroll
                 for (int c = 0; c < EPL; ++c) v[c] = hot[(int64_t)r * p.D + d + c];
-                atomic_add_row<XG, EPL>(p.grad_x, (int64_t)row_node[r] * p.D + d, v);
+                atomic_add_row<XG, EPL>(static_cast<XE*>(p.grad_x) + (int64_t)row_node[r] * p.D + d, v);
             }
         }
     }
@@ -296,8 +266,8 @@ __global__ __launch_bounds__(512) void bwd2_kernel(const BwdParams p) {
     // per wave: leaf rows, multiplicities, per-slot total count and distinct count
     const int per_wave = 2 * nq_max * k2 + 2 * nq_max;
     int* leaf = smem + wave * per_wave;
-    int* mul = leaf + nq_max * k2;
-    int* cnt2 = mul + nq_max * k2;
+    float* mul = reinterpret_cast<float*>(leaf + nq_max * k2);
+    int* cnt2 = leaf + 2 * nq_max * k2;
     int* uniq = cnt2 + nq_max;
     int* live_slots = smem + nw * per_wave;
 
@@ -312,9 +282,9 @@ __global__ __launch_bounds__(512) void bwd2_kernel(const BwdParams p) {
         const bool valid = g < spw && q < nq;
         const int j = wave + q * nw;
         const int u = __shfl(u_mine, valid ? j : 0);
-        const bool active = valid && u >= 0;
         const int seg_base = valid ? g * k2 : 0;
-        const int id = active ? p.ids2[(b * k1 + j) * k2 + li] : -1;
+        int id = valid ? p.ids2[(b * k1 + j) * k2 + li] : -1;         // travels with ids1
+        if (u < 0) id = -1;
         const uint64_t seg = (k2 == 64 ? ~0ull : ((1ull << k2) - 1ull)) << seg_base;
         const int c2 = __popcll(__ballot(id >= 0) & seg);
         int mult; bool first;
@@ -324,7 +294,7 @@ __global__ __launch_bounds__(512) void bwd2_kernel(const BwdParams p) {
         if (keep) {
             const int slot = __popcll(kept & lanemask_lt(lane));
             leaf[q * k2 + slot] = id;
-            mul[q * k2 + slot] = mult;
+            mul[q * k2 + slot] = (float)mult;
         }
         if (valid && li == 0) { cnt2[q] = c2; uniq[q] = __popcll(kept); }
     }
@@ -343,33 +313,21 @@ __global__ __launch_bounds__(512) void bwd2_kernel(const BwdParams p) {
     for (int q = 0; q < nq; ++q) {
         const int c = cnt2[q];
         if (c == 0) continue;
-        const int n = uniq[q];
         const int64_t j = wave + q * nw;
         const float fc = (float)c;
-        for (int64_t d0 = 0; d0 < p.D; d0 += kWave * EPL) {
-            const int64_t d = d0 + lane * EPL;
-            if (d < p.D) {
-                float gsum[EPL];
-                load_grad<GT, EPL>(p.grad_out, b * p.D + d, gsum);
+        add_scaled_rows<XG, EPL>(p.grad_x, p.lanes, leaf + q * k2, mul + q * k2, uniq[q], blockIdx.y, gridDim.y, lane, [&](int64_t d, float (&gsum)[EPL]) {
+            load_grad<GT, EPL>(p.grad_out, b * p.D + d, gsum);
 #pragma unroll
-                for (int c = 0; c < EPL; ++c) gsum[c] = gsum[c] / fc1;
-                if (p.grad_h1) {
-                    float gh[EPL];
-                    load_grad<GT, EPL>(p.grad_h1, (b * k1 + j) * p.D + d, gh);
+            for (int c = 0; c < EPL; ++c) gsum[c] = gsum[c] / fc1;
+            if (p.grad_h1) {
+                float gh[EPL];
+                load_grad<GT, EPL>(p.grad_h1, (b * k1 + j) * p.D + d, gh);
 #pragma unroll
-                    for (int c = 0; c < EPL; ++c) gsum[c] += gh[c];
-                }
-#pragma unroll
-                for (int c = 0; c < EPL; ++c) gsum[c] = gsum[c] / fc;
-                for (int e = 0; e < n; ++e) {
-                    const float m = (float)mul[q * k2 + e];
-                    float v[EPL];
-#pragma unroll
-                    for (int c = 0; c < EPL; ++c) v[c] = gsum[c] * m;
-                    atomic_add_row<XG, EPL>(p.grad_x, (int64_t)leaf[q * k2 + e] * p.D + d, v);
-                }
+                for (int c = 0; c < EPL; ++c) gsum[c] += gh[c];
             }
-        }
+#pragma unroll
+            for (int c = 0; c < EPL; ++c) gsum[c] = gsum[c] / fc;
+        });
     }
 }
 
@@ -485,7 +443,9 @@ static hipError_t launch_backward_typed(const BwdArgs& a, const BwdParams& p, hi
         int nw = (forced >= 1 && forced <= 8) ? forced : (a.k1 < 8 ? a.k1 : 8);
         const int nq_max = (a.k1 + nw - 1) / nw;
         const size_t lds = sizeof(int) * ((size_t)nw * (2 * nq_max * a.k2 + 2 * nq_max) + nw);
-        hipLaunchKernelGGL((bwd2_kernel<GT, XG>), dim3((unsigned)a.B), dim3(nw * kWave), lds, stream, p);
+        BwdParams q = p;
+        q.lanes = row_lanes(a.grad_x, a.D / Epl<GT, XG>::value);
+        hipLaunchKernelGGL((bwd2_kernel<GT, XG>), dim3((unsigned)a.B, backward_parts(a.B, a.k2)), dim3(nw * kWave), lds, stream, q);
     }
     return hipGetLastError();
 }

@@ -61,6 +61,21 @@ struct BwdArgs {
 // 512 threads per root are launched on this many roots at a time.
 constexpr int64_t kMostRoots = 1 << 22;
 
+// Workgroups that share out the leaves of one root in the atomic 2-hop backwards.  A CU issues an atomic
+// instruction every 40 clocks or so, so a batch of fewer roots than CUs would leave most of the chip idle;
+// each workgroup goes through the root's IDs again, so every part keeps two leaves of a slot at least.
+// Backward alone, fanouts 15/10, 1 against 4 parts: 8 roots of 100 floats 10.3 -> 6.9 us, 64 roots 10.2 -> 7.9, 1 root
+// of 256 floats 11.4 -> 8.4, 64 roots of 602 floats 36 -> 24; 128 roots of 100 floats 11.9 -> 11.1 with 2; 256 and more
+// roots gain nothing (256 of 100 floats 17.6 / 17.7 / 17.5 with 1 / 2 / 4) and lose with many (300 k leaves of 64 floats
+// 67 -> 70 with 4).
+inline unsigned backward_parts(int64_t B, int k2) {
+    const int forced = tune_int("FSA_BWD2_PARTS", 0);
+    if (forced > 0) return (unsigned)forced;
+    unsigned parts = 1;
+    while (B * parts < 256 && (int)parts * 4 <= k2) parts *= 2;
+    return parts;
+}
+
 // Roots [b, b + n) of a 2-hop call.
 inline BwdArgs backward_part(const BwdArgs& a, int64_t b, int64_t n) {
     const int gb = a.grad_kind == 0 ? 4 : 2;

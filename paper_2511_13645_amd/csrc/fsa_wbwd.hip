@@ -3,6 +3,7 @@
 // the unweighted backward; the share of a sampled row is its weight over the slot's weight
 // sum instead of 1/count, and equal IDs inside a slot are merged by adding their weights.
 // The 1-hop case runs in the unweighted 1-hop kernel (fsa_bwd.hip) with weight shares.
+#include "fsa_atomic_rows.hip.h"
 #include "fsa_device.hip.h"
 #include "fsa_internal.h"
 
@@ -11,9 +12,8 @@ namespace fsa {
 struct WBwdParams {
     const float* grad_out; const float* grad_h1; const int32_t* ids1; const int32_t* ids2;
     const float* w1; const float* w2; float* grad_x; int64_t B; int64_t D; int k1, k2;
+    RowLanes lanes;                                     // how the lanes of a wave lie over destination rows
 };
-
-__device__ __forceinline__ void w_atomic_add(float* addr, float v) { unsafeAtomicAdd(addr, v); }
 
 __global__ __launch_bounds__(512) void wbwd2_kernel(const WBwdParams p) {
     extern __shared__ int smem[];
@@ -52,8 +52,10 @@ __global__ __launch_bounds__(512) void wbwd2_kernel(const WBwdParams p) {
         const float a = __shfl(a_own, valid ? q : 0);
         const bool active = valid && u >= 0;
         const int seg_base = valid ? g * k2 : 0;
-        const int id = active ? p.ids2[(b * k1 + j) * k2 + li] : -1;
-        const float w = id >= 0 ? p.w2[(b * k1 + j) * k2 + li] : 0.0f;
+        int id = valid ? p.ids2[(b * k1 + j) * k2 + li] : -1;         // both travel with ids1
+        float w = valid ? p.w2[(b * k1 + j) * k2 + li] : 0.0f;
+        if (!active) id = -1;
+        if (id < 0) w = 0.0f;
         // weight sum of the segment: butterfly over the wave restricted to the segment by masking
         float tot = 0.0f;
         for (int m = 0; m < k2; ++m) tot += __shfl(w, seg_base + m);
@@ -85,15 +87,10 @@ __global__ __launch_bounds__(512) void wbwd2_kernel(const WBwdParams p) {
         const int n = uniq[q];
         const int64_t j = wave + q * nw;
         const float outer_share = outer_total > 0.0f ? slot_a[q] / outer_total : 0.0f;
-        for (int64_t d0 = 0; d0 < p.D; d0 += kWave) {
-            const int64_t d = d0 + lane;
-            if (d < p.D) {
-                float gsum = p.grad_out[b * p.D + d] * outer_share;
-                if (p.grad_h1) gsum += p.grad_h1[(b * k1 + j) * p.D + d];
-                for (int e = 0; e < n; ++e)
-                    w_atomic_add(p.grad_x + (int64_t)leaf[q * k2 + e] * p.D + d, gsum * share[q * k2 + e]);
-            }
-        }
+        add_scaled_rows<g_f32, 1>(p.grad_x, p.lanes, leaf + q * k2, share + q * k2, n, blockIdx.y, gridDim.y, lane, [&](int64_t d, float (&gsum)[1]) {
+            gsum[0] = p.grad_out[b * p.D + d] * outer_share;
+            if (p.grad_h1) gsum[0] += p.grad_h1[(b * k1 + j) * p.D + d];
+        });
     }
 }
 
@@ -111,6 +108,7 @@ hipError_t launch_backward_weighted(const BwdArgs& a, const WeightArgs& w, hipSt
     p.grad_out = static_cast<const float*>(a.grad_out); p.grad_h1 = static_cast<const float*>(a.grad_h1);
     p.ids1 = a.ids1; p.ids2 = a.ids2;
     p.w1 = w.w1; p.w2 = w.w2; p.grad_x = static_cast<float*>(a.grad_x); p.B = a.B; p.D = a.D; p.k1 = a.k1; p.k2 = a.k2;
+    p.lanes = row_lanes(a.grad_x, a.D);
     if (!a.ids2) {
         // 1-hop: the unweighted kernel with weight shares instead of 1/count (it merges the rows
         // the seeds of a workgroup share in LDS, which the hub rows of a skewed graph need)
@@ -119,7 +117,7 @@ hipError_t launch_backward_weighted(const BwdArgs& a, const WeightArgs& w, hipSt
         const int nw = a.k1 < 8 ? a.k1 : 8;
         const int nq_max = (a.k1 + nw - 1) / nw;
         const size_t lds = sizeof(int) * ((size_t)nw * (2 * nq_max * a.k2 + 3 * nq_max) + nw);
-        hipLaunchKernelGGL(wbwd2_kernel, dim3((unsigned)a.B), dim3(nw * kWave), lds, stream, p);
+        hipLaunchKernelGGL(wbwd2_kernel, dim3((unsigned)a.B, backward_parts(a.B, a.k2)), dim3(nw * kWave), lds, stream, p);
     }
     return hipGetLastError();
 }
