@@ -58,6 +58,13 @@ inline RowLanes row_lanes(const void* grad_x, int64_t units) {
     return l;
 }
 
+// The values are here when this returns.  Without it the compiler puts the wait for a load that is first used
+// in a loop into the loop, where it waits for every atomic of the loop as well.
+template <int EPL> __device__ __forceinline__ void arrived(float (&g)[EPL]) {
+#pragma unroll
+    for (int c = 0; c < EPL; ++c) asm volatile("" : "+v"(g[c]));
+}
+
 // grad_x[rows[e], :] += factor[e] * g for e < n, where load(d, v) reads the EPL elements of g from element d
 // on; of `parts` callers with the same list each takes its share of it.  `rows` and `factor` lie in LDS.
 // Called by a whole wave.
@@ -79,6 +86,7 @@ __device__ __forceinline__ void add_scaled_rows(void* grad_x, const RowLanes& l,
         if (u >= l.units) return;
         float g[EPL];
         load((int64_t)u * EPL, g);
+        arrived(g);
         const int each = kWave >> l.width_shift;
         for (int e = part * each + (lane >> l.width_shift); e < n; e += parts * each) {
             float v[EPL];
@@ -92,6 +100,7 @@ __device__ __forceinline__ void add_scaled_rows(void* grad_x, const RowLanes& l,
         for (int u = lane; u < l.units; u += kWave) {
             float g[EPL];
             load((int64_t)u * EPL, g);
+            arrived(g);
             for (int e = part; e < n; e += parts) {
                 float v[EPL];
 #pragma unroll
@@ -110,6 +119,7 @@ __device__ __forceinline__ void add_scaled_rows(void* grad_x, const RowLanes& l,
 #pragma unroll
         for (int c = 0; c < EPL; ++c) cur[c] = 0.0f;
         if (u < l.units) load((int64_t)u * EPL, cur);
+        arrived(cur);
         for (int e = part; e < n; e += parts) {
             const int row = rows[e];
             // lanes from the cut on: the elements that the instruction before left

@@ -20,7 +20,7 @@ struct BwdParams {
     void* grad_x; int64_t B; int64_t D; int k1, k2;
     const float* w1;                     // 1-hop weighted mean: [B,k1] weights of the sampled edges, else unused
     const int32_t* root_valid;           // 2-hop, nullable: [B], a negative entry switches root b off
-    RowLanes lanes;                      // 2-hop: how the lanes of a wave lie over destination rows
+    RowLanes lanes;                      // how the lanes of a wave lie over destination rows
 };
 
 // ---------------------------------------------------------------------------------------
@@ -87,103 +87,153 @@ __device__ __forceinline__ void merge_equal_ids(int id, int k, int li, int seg_b
 // seeds w, w+nw, ...).  Rows that many seeds of the workgroup share -- the hub rows of a skewed
 // graph, which would otherwise serialise thousands of atomics on one L2 channel -- are first
 // summed in LDS and reach grad_x with ONE atomic row-add per workgroup:
-//   pass 1  every sampled ID bumps an LDS counter at hash(id);
-//   pass 2  the count threshold is doubled from kHotMin until no more buckets reach it than
-//           there are LDS rows; IDs in such buckets claim them (first claimant wins; a
-//           colliding ID simply stays on the direct path) and claimed buckets get an LDS row;
+//   pass 1  every sampled ID claims the bucket at hash(id) of an LDS table or the one beside it (first
+//           claimant wins; an ID that finds both taken stays on the direct path) and bumps its counter;
+//   pass 2  buckets that count kHotMin IDs take an LDS row each; when there are fewer rows than such
+//           buckets, they are handed out again to those that reach the lowest kHotMin * 2^i that no more do;
 //   pass 3  per seed: equal IDs of the seed are merged (multiplicity), then each distinct row
-//           receives grad_out[b,:] * mult/cnt -- into its LDS row if it owns a bucket, else
-//           straight into grad_x with hardware fp32 atomics, 256 contiguous bytes per wave
-//           instruction;
+//           receives grad_out[b,:] * mult/cnt -- into its LDS row if it has one, else
+//           straight into grad_x with hardware atomics;
 //   flush   LDS rows are added to grad_x.
-// When no counter reaches kHotMin (uniform graphs) passes 2 and flush are skipped.
+// When no counter reaches kHotMin (uniform graphs) pass 2 and flush are skipped.
+//
+// A small call is bound by its chain of dependent steps, a large one by each wave's trips to memory,
+// one seed after the other.  So a seed's IDs and the first tile of its gradient are requested
+// together, for the first seed before the LDS is cleared and for every further one before the adds of
+// the seed before it (a load behind atomics waits for them).  Backward alone, before and after: 1024 seeds x 10
+// of 64 floats 7.1 -> 6.4 us, KG shape B=1024 10.1 -> 8.3, B=16384 31 -> 29; 64 seeds x 15 of 128 floats 9.5 -> 6.8;
+// with the rows cut at their segments 4096 seeds x 15 of 300 floats 74 -> 63 us.  Asking for four seeds at a time
+// was slower everywhere (B=4096 13 -> 16 us).
 // ---------------------------------------------------------------------------------------
 constexpr int kHotBuckets = 2048;
 constexpr int kHotMin = 3;
 constexpr int kHotRowsMax = 64;
+constexpr int kHotLevels = 16;                                       // kHotMin * 2^15 exceeds any count (at most 2^15)
+constexpr int kBwd1MaxSeeds = 32;                                    // seeds per wave: at most a bit for each of a lane's entries
 
 __device__ __forceinline__ int hot_hash(int id) {
     return (int)(((uint32_t)id * 2654435761u) >> 21);              // 11 bits -> kHotBuckets
 }
 
+// The bucket that `id` owns, or -1.  An ID that finds its bucket taken has the one beside it.
+__device__ __forceinline__ int hot_bucket(const int* tag, int id) {
+    const int h = hot_hash(id);
+    return tag[h] == id ? h : tag[h ^ 1] == id ? h ^ 1 : -1;
+}
+
+// LDS ints of the 1-hop kernel without the hot rows: tags and counters, levels, flags, node of each hot row, and
+// per wave 64 rows with their factors.
+FSA_HD inline int bwd1_fixed_ints(int nw) { return 2 * kHotBuckets + kHotLevels + 4 + kHotRowsMax + nw * 2 * kWave; }
+
 template <typename GT, typename XG, bool WEIGHTED>
 __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, int hot_rows) {
     constexpr int EPL = Epl<GT, XG>::value;
-    using XE = typename XG::T;
-    extern __shared__ int smem[];
+    extern __shared__ __align__(16) int smem[];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nw = blockDim.x >> 6;
-    // LDS: counters, tags, row-of-bucket [kHotBuckets] each; [2] flags; node of each LDS row
-    // [kHotRowsMax]; per wave [64] rows + [64] weights + [64] hot-row index; then hot_rows * D
-    // floats.
-    int* count = smem;
-    int* tag = count + kHotBuckets;
-    int* row_of = tag + kHotBuckets;
-    int* flags = row_of + kHotBuckets;                               // [0] any hot, [1] rows handed out
-    int* row_node = flags + 2;
-    int* rows = row_node + kHotRowsMax + wave * 3 * kWave;
-    float* weight = reinterpret_cast<float*>(rows + kWave);
-    int* hot_of = rows + 2 * kWave;
-    float* hot = reinterpret_cast<float*>(row_node + kHotRowsMax + nw * 3 * kWave);
+    int* tag = smem;
+    uint32_t* count = reinterpret_cast<uint32_t*>(tag + kHotBuckets);  // IDs | 1 + LDS row << 16
+    int* level = tag + 2 * kHotBuckets;
+    int* flags = level + kHotLevels;                                 // [0] any hot, [1] hot buckets, [2] rows of the second round
+    int* row_node = flags + 4;
+    int* rows = row_node + kHotRowsMax + wave * 2 * kWave;
+    float* factor = reinterpret_cast<float*>(rows + kWave);
+    float* hot = reinterpret_cast<float*>(smem + bwd1_fixed_ints(nw));
     const int64_t b0 = (int64_t)blockIdx.x * nw * spw;
+    const RowLanes l = p.lanes;
+    const int u0 = lane & ((1 << l.width_shift) - 1);
 
-    for (int i = threadIdx.x; i < kHotBuckets; i += blockDim.x) { count[i] = 0; tag[i] = -1; row_of[i] = -1; }
-    if (threadIdx.x < 2) flags[threadIdx.x] = 0;
-    __syncthreads();
+    // seed s of this wave: its IDs (lane < k1), their weights, the first tile of its gradient
+    int next_id;
+    float next_w = 0.0f;
+    float next_g[EPL];
+    auto request = [&](int s) {
+        const int64_t b = b0 + wave + (int64_t)s * nw;
+        const bool there = b < p.B && lane < p.k1;
+        next_id = there ? p.ids1[b * p.k1 + lane] : -1;
+        if constexpr (WEIGHTED) next_w = there ? p.w1[b * p.k1 + lane] : 0.0f;
+        if (b < p.B) load_grad<GT, EPL>(p.grad_out, b * p.D + (int64_t)(u0 < l.units ? u0 : 0) * EPL, next_g);
+    };
+#pragma unroll
+    for (int c = 0; c < EPL; ++c) next_g[c] = 0.0f;
+    request(0);
 
-    // pass 1: count IDs per bucket (lanes cover consecutive entries of the workgroup's seeds)
-    const bool use_hot = hot_rows > 0;
-    if (use_hot) {
-        const int64_t first = b0 * p.k1;
-        const int64_t n_ent = ((b0 + (int64_t)nw * spw < p.B ? b0 + (int64_t)nw * spw : p.B) - b0) * p.k1;
+    bool any_hot = false;
+    int n_rows = 0;
+    if (hot_rows > 0) {
+        for (int i = threadIdx.x; i < kHotBuckets; i += blockDim.x) { tag[i] = -1; count[i] = 0; }
+        if (threadIdx.x < kHotLevels + 4) level[threadIdx.x] = 0;    // and the flags behind the levels
+        __syncthreads();
+        // the workgroup's IDs: with one seed per wave those that are here already, else all of them in order
+        const int64_t first_entry = b0 * p.k1;
+        const int n_ent = (int)(((b0 + (int64_t)nw * spw < p.B ? b0 + (int64_t)nw * spw : p.B) - b0) * p.k1);
+        const int turns = spw == 1 ? 1 : (n_ent + (int)blockDim.x - 1) / (int)blockDim.x;
+        auto entry = [&](int i) {
+            if (spw == 1) return next_id;
+            const int e = i * (int)blockDim.x + (int)threadIdx.x;
+            return e < n_ent ? p.ids1[first_entry + e] : -1;
+        };
+        uint32_t owner = 0u;                                         // bit i: this lane claimed a bucket for its entry i
         bool saw_hot = false;
-        for (int64_t e = threadIdx.x; e < n_ent; e += blockDim.x) {
-            const int id = p.ids1[first + e];
-            if (id >= 0) saw_hot = (atomicAdd(&count[hot_hash(id)], 1) + 1 >= kHotMin) || saw_hot;
+        for (int i = 0; i < turns; ++i) {
+            const int id = entry(i);
+            if (id >= 0) {
+                int h = hot_hash(id);
+                int was = atomicCAS(&tag[h], -1, id);
+                if (was != -1 && was != id) { h ^= 1; was = atomicCAS(&tag[h], -1, id); }
+                if (was == -1) owner |= 1u << i;
+                if (was == -1 || was == id) saw_hot = (atomicAdd(&count[h], 1u) + 1 >= kHotMin) || saw_hot;
+            }
         }
         if (saw_hot) flags[0] = 1;
         __syncthreads();
-        if (flags[0]) {                                              // workgroup-uniform
-            // pass 2: the busiest buckets, as many as there are LDS rows
-            int thresh = kHotMin;
-            for (;;) {                                               // workgroup-uniform trip count
-                int mine = 0;
-                for (int i = threadIdx.x; i < kHotBuckets; i += blockDim.x) mine += count[i] >= thresh;
-                if (mine) atomicAdd(&flags[1], mine);
-                __syncthreads();
-                const int n_over = flags[1];
-                __syncthreads();
-                if (threadIdx.x == 0) flags[1] = 0;
-                __syncthreads();
-                if (n_over <= hot_rows) break;
-                thresh *= 2;
+        any_hot = flags[0] != 0;                                     // workgroup-uniform
+        if (any_hot) {
+            for (int i = 0; i < turns; ++i) {
+                if (!((owner >> i) & 1u)) continue;
+                const int id = entry(i);
+                const int h = hot_bucket(tag, id);
+                const uint32_t c = count[h];
+                if (c < kHotMin) continue;
+                const int r = atomicAdd(&flags[1], 1);
+                if (r < hot_rows) { row_node[r] = id; count[h] = c | (uint32_t)(r + 1) << 16; }
             }
-            for (int64_t e = threadIdx.x; e < n_ent; e += blockDim.x) {
-                const int id = p.ids1[first + e];
-                if (id >= 0 && count[hot_hash(id)] >= thresh) atomicCAS(&tag[hot_hash(id)], -1, id);
-            }
+            for (int i = threadIdx.x; i < hot_rows * (int)p.D; i += blockDim.x) hot[i] = 0.0f;
             __syncthreads();
-            for (int i = threadIdx.x; i < kHotBuckets; i += blockDim.x) {
-                if (tag[i] >= 0) {                                   // at most hot_rows buckets qualify
-                    const int r = atomicAdd(&flags[1], 1);
-                    row_of[i] = r;
-                    row_node[r] = tag[i];
+            n_rows = flags[1];
+            if (n_rows > hot_rows) {                                 // workgroup-uniform
+                for (int i = 0; i < turns; ++i) {
+                    if (!((owner >> i) & 1u)) continue;
+                    const uint32_t c = count[hot_bucket(tag, entry(i))] & 0xffffu;
+                    if (c >= kHotMin) atomicAdd(&level[31 - __clz(c / kHotMin)], 1);
                 }
+                __syncthreads();
+                int at = kHotLevels, over = 0;                       // buckets of level `at` and above
+                while (at > 0 && over + level[at - 1] <= hot_rows) over += level[--at];
+                n_rows = over;
+                for (int i = 0; i < turns; ++i) {
+                    if (!((owner >> i) & 1u)) continue;
+                    const int id = entry(i);
+                    const int h = hot_bucket(tag, id);
+                    uint32_t c = count[h] & 0xffffu;
+                    if (c >= (uint32_t)kHotMin << at) {
+                        const int r = atomicAdd(&flags[2], 1);
+                        row_node[r] = id;
+                        c |= (uint32_t)(r + 1) << 16;
+                    }
+                    count[h] = c;
+                }
+                __syncthreads();
             }
-            __syncthreads();
-            const int n_rows = flags[1];
-            for (int64_t i = threadIdx.x; i < (int64_t)n_rows * p.D; i += blockDim.x) hot[i] = 0.0f;
-            __syncthreads();
         }
     }
-    const bool any_hot = use_hot && flags[0] != 0;
 
     // pass 3: one seed at a time per wave
     for (int s = 0; s < spw; ++s) {
         const int64_t b = b0 + wave + (int64_t)s * nw;
         if (b >= p.B) break;                                         // wave-uniform
-        const int id = lane < p.k1 ? p.ids1[b * p.k1 + lane] : -1;
+        const int id = next_id;
         // share of the seed's gradient that this lane's row receives: multiplicity / count, or,
         // for the weighted mean, the summed weight of its occurrences / the seed's weight sum
         // (a seed whose weights sum to zero contributes nothing)
@@ -191,7 +241,7 @@ __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, 
         bool first;
         bool live_seed = true;
         if constexpr (WEIGHTED) {
-            const float w = id >= 0 ? p.w1[b * p.k1 + lane] : 0.0f;
+            const float w = id >= 0 ? next_w : 0.0f;
             float total = w;
             for (int off = 1; off < kWave; off <<= 1) total += __shfl_xor(total, off);
             float wsum;
@@ -204,50 +254,55 @@ __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, 
             merge_equal_ids(id, p.k1, lane, 0, mult, first);
             share = (float)mult / (float)cnt;
         }
+        // the list: rows of grad_x from the front, LDS rows from the back
         const bool keep = id >= 0 && first && live_seed;
-        const uint64_t kept = __ballot(keep);
-        const int n = __popcll(kept);
+        int to = id;
+        if (any_hot && keep) {
+            const int h = hot_bucket(tag, id);
+            if (h >= 0 && count[h] >> 16) to = -(int)(count[h] >> 16);  // ~LDS row
+        }
+        const uint64_t direct = __ballot(keep && to >= 0), shared = __ballot(keep && to < 0);
+        const int n = __popcll(direct), n_shared = __popcll(shared);
         if (keep) {
-            const int slot = __popcll(kept & lanemask_lt(lane));
-            rows[slot] = id;
-            weight[slot] = share;
-            int hr = -1;
-            if (any_hot) { const int h = hot_hash(id); if (tag[h] == id) hr = row_of[h]; }
-            hot_of[slot] = hr;
+            const int slot = to >= 0 ? __popcll(direct & lanemask_lt(lane)) : kWave - 1 - __popcll(shared & lanemask_lt(lane));
+            rows[slot] = to;
+            factor[slot] = share;
         }
+        float held[EPL];
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) held[c] = next_g[c];
+        if (s + 1 < spw) request(s + 1);
         __builtin_amdgcn_wave_barrier();
-        for (int64_t d0 = 0; d0 < p.D; d0 += kWave * EPL) {
-            const int64_t d = d0 + lane * EPL;
-            if (d < p.D) {
-                float g[EPL];
+        add_scaled_rows<XG, EPL>(p.grad_x, l, rows, factor, n, 0, 1, lane, [&](int64_t d, float (&g)[EPL]) {
+            if (d < kWave * EPL) {
+#pragma unroll
+                for (int c = 0; c < EPL; ++c) g[c] = held[c];
+            } else {
                 load_grad<GT, EPL>(p.grad_out, b * p.D + d, g);
-                for (int e = 0; e < n; ++e) {
-                    const int hr = hot_of[e];
-                    const float wt = weight[e];
-                    float v[EPL];
-#pragma unroll
-                    for (int c = 0; c < EPL; ++c) v[c] = g[c] * wt;
-                    if (hr >= 0) {
-#pragma unroll
-                        for (int c = 0; c < EPL; ++c) atomicAdd(&hot[(int64_t)hr * p.D + d + c], v[c]);
-                    } else {
-                        atomic_add_row<XG, EPL>(static_cast<XE*>(p.grad_x) + (int64_t)rows[e] * p.D + d, v);
-                    }
-                }
             }
-        }
+            arrived(g);
+            for (int e = kWave - n_shared; e < kWave; ++e) {         // (narrow rows: for the first group of lanes)
+                if (lane >> l.width_shift) break;
+                float* at = hot + ~rows[e] * (int)p.D + d;
+#pragma unroll
+                for (int c = 0; c < EPL; ++c) atomicAdd(at + c, g[c] * factor[e]);
+            }
+        });
         __builtin_amdgcn_wave_barrier();
     }
 
     if (any_hot) {                                                   // workgroup-uniform
         __syncthreads();
-        const int n_rows = flags[1];
+        char* const base = static_cast<char*>(p.grad_x);
         for (int r = wave; r < n_rows; r += nw) {
-            for (int64_t d = (int64_t)lane * EPL; d < p.D; d += kWave * EPL) {
+            const int64_t row = row_node[r];
+            const int shift = l.base >= 0 ? (int)(((uint32_t)l.base + (uint32_t)row * (uint32_t)l.units) & (kSegment - 1)) : 0;
+            for (int d = lane - shift; d < l.units; d += kWave) {    // from the start of the row's first segment
+                if (d < 0) continue;
                 float v[EPL];
 #pragma unroll
-                for (int c = 0; c < EPL; ++c) v[c] = hot[(int64_t)r * p.D + d + c];
-                atomic_add_row<XG, EPL>(static_cast<XE*>(p.grad_x) + (int64_t)row_node[r] * p.D + d, v);
+                for (int c = 0; c < EPL; ++c) v[c] = hot[r * (int)p.D + d * EPL + c];
+                atomic_add_row<XG, EPL>(base + (row * l.units + d) * 4, v);
             }
         }
     }
@@ -412,25 +467,28 @@ hipError_t launch_deep_grad(const float* grad_out, const float* grad_h1, const i
 
 template <typename GT, typename XG, bool WEIGHTED>
 static hipError_t launch_bwd1(const BwdArgs& a, const BwdParams& p, hipStream_t stream) {
-    // Workgroups of 16 waves: the rows the seeds of a workgroup share are merged in LDS, so the
-    // more seeds a workgroup sees the fewer atomic row-adds reach a hub row, and 16 waves work
-    // through them side by side.  Seeds per wave grow with the batch so that the launch keeps
-    // a few hundred workgroups (measured on the KG shape, B = 1024 .. 262144: 14.7 us at
-    // B=4096 against 20.4 us with 4-wave workgroups, 84 against 136 us at B=65536).
+    // The more seeds a workgroup sees the fewer atomic row-adds reach a hub row, and 16 waves work through them
+    // side by side; a small batch is spread over the CUs in workgroups of 4 or 8 waves instead.  Seeds per wave
+    // grow with the batch so that the launch keeps a few hundred workgroups.  Measured, KG shape: B=4096
+    // 20.4 / 14.7 us with 4 / 16 waves, B=1024 8.3 / 8.0; product graph, 64 seeds of 300 floats 12.5 / 13.7.
     const int forced_spw = tune_int("FSA_BWD1_SEEDS_PER_WAVE", 0);
     const int forced_nw = tune_int("FSA_BWD1_WAVES", 0);
-    const int nw = (forced_nw >= 1 && forced_nw <= 16) ? forced_nw : 16;
+    int nw = 4;
+    while (nw < 16 && a.B > (int64_t)nw * 256) nw *= 2;
+    if (forced_nw >= 1 && forced_nw <= 16) nw = forced_nw;
     int spw = 1;
     while (spw < 16 && a.B / ((int64_t)nw * spw * 2) >= 256) spw *= 2;
-    if (forced_spw >= 1 && forced_spw <= 64) spw = forced_spw;
+    if (forced_spw >= 1 && forced_spw <= kBwd1MaxSeeds) spw = forced_spw;
     // LDS: the fixed part (hash tables, per-wave strips) plus as many fp32 rows as fit in 64 KB
-    const size_t lds_fixed = sizeof(int) * (3 * kHotBuckets + 2 + kHotRowsMax + nw * 3 * kWave);
+    const size_t lds_fixed = sizeof(int) * bwd1_fixed_ints(nw);
     int hot_rows = (int)((65536 - lds_fixed) / (sizeof(float) * (size_t)a.D));
     if (hot_rows > kHotRowsMax) hot_rows = kHotRowsMax;
     if (tune_int("FSA_BWD1_NO_HOT", 0)) hot_rows = 0;
     const unsigned grid = (unsigned)((a.B + nw * spw - 1) / (nw * spw));
     const size_t lds = lds_fixed + sizeof(float) * (size_t)hot_rows * a.D;
-    hipLaunchKernelGGL((bwd1_kernel<GT, XG, WEIGHTED>), dim3(grid), dim3(nw * kWave), lds, stream, p, spw, hot_rows);
+    BwdParams q = p;
+    q.lanes = row_lanes(a.grad_x, a.D / Epl<GT, XG>::value);
+    hipLaunchKernelGGL((bwd1_kernel<GT, XG, WEIGHTED>), dim3(grid), dim3(nw * kWave), lds, stream, q, spw, hot_rows);
     return hipGetLastError();
 }
 
