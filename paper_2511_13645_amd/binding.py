@@ -1,6 +1,10 @@
-"""Thin ctypes binding of the C-ABI HIP library (include/fsa.h), same names as the C entry
+"""Thin binding of the C-ABI HIP library (include/fsa.h), same names as the C entry
 points.  Argument marshalling only: every step of the path runs inside the library's
 kernels.  PyTorch is used for device memory and the current stream, nothing else.
+
+The functions below are the binding, through ctypes.  The most frequent of them first offer the call to
+their counterpart in ``_fsa_host`` (csrc_host/fsa_host.cpp), which does the same without the interpreter for
+plain arguments and returns None for anything else.
 
 The library must have been built (``python -m paper_2511_13645_amd.build`` or
 ``__graft_entry__.build()``); there is no CPU fallback -- a missing library raises.
@@ -16,6 +20,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfsa_hip.so")
+HOST_PATH = os.path.join(_HERE, "_fsa_host.so")
 
 FSA_F32, FSA_BF16, FSA_F16 = 0, 1, 2
 FSA_I32, FSA_I64 = 0, 1
@@ -30,6 +35,10 @@ EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_me
            "fsa_sample_wmean_fwd", "fsa_wmean_replay_fwd", "fsa_wmean_bwd")
 
 _lib: Optional[ctypes.CDLL] = None
+_host = None                                    # the module _fsa_host, once the library is loaded
+_HOST_ENTRIES = ("fsa_sample_mean_fwd", "fsa_sample_wmean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_ws",
+                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws")              # in the order that _fsa_host.bind takes them
+_PLAIN, _WORKSPACE, _LOW_PRECISION, _WEIGHTED = range(4)                # backward entry points, as _fsa_host.bwd counts them
 
 
 class FsaError(RuntimeError):
@@ -40,10 +49,12 @@ class FsaError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load the HIP library; fail loudly when it has not been built."""
-    global _lib
+    global _lib, _host
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("HIP library missing: %s (build it with __graft_entry__.build())" % LIB_PATH)
+        if not os.path.exists(HOST_PATH):
+            raise RuntimeError("host library missing: %s (build it with __graft_entry__.build())" % HOST_PATH)
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, u64, ci = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64, ctypes.c_int
         L.fsa_sample_mean_fwd.argtypes = [vp, ci, vp, i64, vp, ci, i64, vp, i64, vp, ci, u64,
@@ -88,7 +99,9 @@ def lib() -> ctypes.CDLL:
         L.fsa_mean3_bwd_ws.restype = ci
         L.fsa_status_string.argtypes = [ci]
         L.fsa_status_string.restype = ctypes.c_char_p
-        _lib = L
+        from . import _fsa_host
+        _fsa_host.bind(_raw_stream, *(ctypes.cast(getattr(L, name), vp).value for name in _HOST_ENTRIES))
+        _lib, _host = L, _fsa_host
     return _lib
 
 
@@ -154,6 +167,15 @@ def _host_ints(values: Tuple[int, ...]) -> ctypes.Array:
     return (ctypes.c_int32 * max(1, len(values)))(*values)
 
 
+def _taken(r, name: str) -> bool:
+    """Whether _fsa_host took a call (it returned something); raises if the library refused it (a status)."""
+    if r is None:
+        return False
+    if type(r) is int and r != FSA_OK:
+        raise FsaError(r, name)
+    return True
+
+
 def _room(workspace: Optional[torch.Tensor], like: torch.Tensor) -> Tuple[Optional[int], int]:
     """(address, bytes) of the workspace a caller hands to a backward call; (None, 0) without one."""
     if workspace is None:
@@ -172,6 +194,10 @@ def fsa_sample_mean_fwd(indptr: torch.Tensor, indices: torch.Tensor, x: torch.Te
                         ) -> Tuple[torch.Tensor, Optional[torch.Tensor], Optional[torch.Tensor], Optional[torch.Tensor]]:
     """Fused sample + mean forward.  Output tensors are allocated here (torch) unless given.
     Returns (out, out_h1, ids1, ids2); entries not asked for are None."""
+    if _host is not None and stream is None and out is None and out_h1 is None and out_ids1 is None and out_ids2 is None:
+        r = _host.sample_fwd(indptr, indices, None, x, seeds, fanouts, seed, emit_h1, emit_ids)
+        if _taken(r, "fsa_sample_mean_fwd"):
+            return r
     _need(indptr, "indptr"); _need(indices, "indices", torch.int32); _need(x, "x")
     _need(seeds, "seeds", torch.int32)
     fan = [int(k) for k in fanouts]
@@ -212,6 +238,10 @@ def fsa_mean_replay_fwd(x: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
                         emit_h1: bool = True, stream: Optional[torch.cuda.Stream] = None
                         ) -> Tuple[torch.Tensor, Optional[torch.Tensor]]:
     """Mean over saved IDs (no sampling).  Returns (out, out_h1)."""
+    if _host is not None and stream is None and out is None and out_h1 is None:
+        r = _host.replay_fwd(x, ids1, ids2, emit_h1)
+        if _taken(r, "fsa_mean_replay_fwd"):
+            return r
     _need(x, "x"); _need(ids1, "ids1", torch.int32)
     B, k1 = ids1.shape
     N, D = x.shape
@@ -241,6 +271,9 @@ def fsa_mean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torc
                  grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor,
                  stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """Scatter-add the mean's gradient into grad_x [N,D] fp32 (accumulated with atomics, not zeroed)."""
+    if _host is not None and stream is None:
+        if _taken(_host.bwd(_PLAIN, grad_out, ids1, None, ids2, None, grad_h1, grad_x, None), "fsa_mean_bwd"):
+            return grad_x
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -283,6 +316,9 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
     """fsa_mean_bwd with an optional caller workspace (any contiguous GPU tensor; torch allocations are
     256-byte aligned, sized by fsa_mean_bwd_workspace_bytes).  Given one, wide-row 2-hop calls update every
     destination row once, without atomics: no other work may write grad_x or the workspace while they run."""
+    if _host is not None and stream is None:
+        if _taken(_host.bwd(_WORKSPACE, grad_out, ids1, None, ids2, None, grad_h1, grad_x, workspace), "fsa_mean_bwd_ws"):
+            return grad_x
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape
@@ -316,6 +352,9 @@ def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
     fp32 master gradient or a 16-bit table added to with packed atomics (accumulated, not zeroed).
     `workspace`, sized by fsa_bwd_workspace_bytes: large 2-hop calls update every destination row once,
     without atomics; no other work may write grad_x or the workspace while the call runs."""
+    if _host is not None and stream is None:
+        if _taken(_host.bwd(_LOW_PRECISION, grad_out, ids1, None, ids2, None, grad_h1, grad_x, workspace), "fsa_mean_bwd_lp"):
+            return grad_x
     _need(grad_out, "grad_out"); _need(ids1, "ids1", torch.int32); _need(grad_x, "grad_x")
     B, k1 = ids1.shape
     D = grad_out.shape[1]
@@ -470,6 +509,10 @@ def fsa_sample_wmean_fwd(indptr: torch.Tensor, indices: torch.Tensor, edge_weigh
                          stream: Optional[torch.cuda.Stream] = None):
     """Weighted fused sample + mean.  Returns (out, out_h1, ids1, ids2, w1, w2); IDs and weights
     are emitted together (emit_ids), entries not asked for are None."""
+    if _host is not None and stream is None and edge_weight is not None:
+        r = _host.sample_fwd(indptr, indices, edge_weight, x, seeds, fanouts, seed, emit_h1, emit_ids)
+        if _taken(r, "fsa_sample_wmean_fwd"):
+            return r
     _need(indptr, "indptr"); _need(indices, "indices", torch.int32); _need(x, "x")
     _need(seeds, "seeds", torch.int32); _need(edge_weight, "edge_weight", torch.float32)
     if edge_weight.shape[0] != indices.shape[0]:
@@ -535,6 +578,9 @@ def fsa_wmean_bwd(grad_out: torch.Tensor, ids1: torch.Tensor, w1: torch.Tensor,
     """Weighted backward: scatter-add into grad_x [N,D] fp32 (accumulated, not zeroed).
     `workspace`, sized by fsa_bwd_workspace_bytes: large 2-hop calls update every destination row once,
     without atomics; no other work may write grad_x or the workspace while the call runs."""
+    if _host is not None and stream is None and w1 is not None:
+        if _taken(_host.bwd(_WEIGHTED, grad_out, ids1, w1, ids2, w2, grad_h1, grad_x, workspace), "fsa_wmean_bwd"):
+            return grad_x
     _need(grad_out, "grad_out", torch.float32); _need(ids1, "ids1", torch.int32); _need(w1, "w1", torch.float32)
     _need(grad_x, "grad_x", torch.float32)
     B, k1 = ids1.shape

@@ -1,4 +1,5 @@
-"""Builds the HIP library (gfx950) in-tree: ``paper_2511_13645_amd/libfsa_hip.so``."""
+"""Builds the HIP library (gfx950) in-tree, ``paper_2511_13645_amd/libfsa_hip.so``, and the binding's host
+path, ``paper_2511_13645_amd/_fsa_host.so``."""
 from __future__ import annotations
 
 import os
@@ -18,6 +19,10 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+
+
+HOST_SOURCE = os.path.join(HERE, "csrc_host", "fsa_host.cpp")
+HOST_LIB = os.path.join(HERE, "_fsa_host.so")
 
 
 def hipcc() -> str:
@@ -55,11 +60,29 @@ def build_hip(extra_flags=(), verbose: bool = False, out: str = LIB) -> str:
     return out
 
 
+def build_host(verbose: bool = False, out: str = HOST_LIB) -> str:
+    """Compile the binding's host path (plain C++ against torch's headers and the CPython C API)."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = out + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], HOST_SOURCE, "-o", tmp,
+           "-L" + os.path.join(base, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, out)
+    return out
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(HOST_LIB):
         return True
     newest = max(os.path.getmtime(os.path.join(CSRC, f)) for f in SOURCES + HEADERS)
-    return os.path.getmtime(LIB) < newest
+    return os.path.getmtime(LIB) < newest or os.path.getmtime(HOST_LIB) < os.path.getmtime(HOST_SOURCE)
 
 
 if __name__ == "__main__":
@@ -72,3 +95,5 @@ if __name__ == "__main__":
         target = os.path.join(HERE, os.path.basename(argv[i + 1]))
         del argv[i:i + 2]
     print(build_hip(argv, verbose=True, out=target))
+    if target == LIB:
+        print(build_host(verbose=True))
