@@ -30,9 +30,6 @@
 #ifndef FSA_PASS_GROUP
 #define FSA_PASS_GROUP 4
 #endif
-#ifndef FSA_MULTI_LOADS
-#define FSA_MULTI_LOADS 8
-#endif
 #ifndef FSA_ROOTS_PER_WG
 #define FSA_ROOTS_PER_WG 1
 #endif
@@ -62,6 +59,38 @@ struct FwdParams {
 #else
 #define FSA_STAMP(var) do { } while (0)
 #endif
+
+// A piece of VB bytes of one row for the multi-tile gathers.  `row` is the same in all lanes.  The row is
+// addressed as a buffer of its own: pieces that start at or behind its end (`bytes`) read as zero and cost no
+// memory access, so that the tiles of a row, and rows behind the end of a list (bytes = 0), are requested
+// without a branch -- the hardware counter that orders loads cannot be tracked across one.
+template <int VB>
+__device__ __forceinline__ typename RawOf<VB>::type row_piece(const char* row, int bytes, int at) {
+    if constexpr (VB == 2) {                    // (rows at odd multiples of 2 bytes: plain loads)
+        const int from = at < bytes ? at : 0;
+        uint16_t v = 0;
+        if (bytes > 0) v = *reinterpret_cast<const uint16_t*>(row + from);
+        return v;
+    } else {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), 0, bytes, 0x00020000);   // raw, 32-bit data
+        typename RawOf<VB>::type v;
+        if constexpr (VB == 16) { const auto q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        else if constexpr (VB == 8) { const auto q = __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        else { const auto q = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        return v;
+    }
+}
+
+// Rows in flight per lane in the multi-tile gathers: 40 registers' worth, four at most.  With one row at a
+// time a wave waited out a trip to memory per row, which bounds every launch that does not fill the chip (and
+// 16-byte pieces of 16-bit rows, whose sums leave room for two waves per SIMD, at any size).  Forward, with
+// IDs, before and after: 2408-byte rows, 25/10, 64 roots 33 -> 21 us, 200 39.5 -> 29, 600 97 -> 78, 1024 109 -> 107;
+// 1200-byte rows, 15/10, 2048 roots 86 -> 68; 1280-byte bf16 rows 154 -> 67; one hop, 8192 x 15 rows of 2560 bytes 67 -> 49.
+// 16 or 24 registers' worth: 25 and 22 us for the 64 roots, the same for the large ones.
+template <int VB, int MT> struct RowsInFlight {
+    static constexpr int fit = 40 / (MT * (VB < 4 ? 4 : VB) / 4);
+    static constexpr int value = fit < 1 ? 1 : fit > 4 ? 4 : fit;
+};
 
 // A value every lane of the wave holds, moved to scalar registers.
 __device__ __forceinline__ int64_t wave_uniform(int64_t v) {
@@ -139,10 +168,9 @@ __device__ __forceinline__ void wave_mean_of_rows(const FwdParams& p, int id, fl
 
     if constexpr (MT > 0) {
         // rows of 2 .. MT tiles of 64 lanes: all tiles of a row are loaded back to back, so a
-        // cache line shared by neighbouring tiles is fetched once
+        // cache line shared by neighbouring tiles is fetched once, R rows in flight (see the 2-hop kernel)
         using Raw = typename C::Raw;
-        constexpr int R = FSA_MULTI_LOADS / MT;                    // rows in flight
-        const int tiles = (p.chunks + kWave - 1) >> 6;
+        constexpr int R = RowsInFlight<VB, MT>::value;
         float acc[MT][VE];
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -150,41 +178,37 @@ __device__ __forceinline__ void wave_mean_of_rows(const FwdParams& p, int id, fl
             for (int e = 0; e < VE; ++e) acc[t][e] = 0.0f;
         }
         float wsum = 0.0f;
+        Raw r[R][MT];
+        float wr[R];
+        auto request = [&](int u, int i) {
+            const int at = i < cnt ? i : 0;
+            const int64_t row = __builtin_amdgcn_readfirstlane(ids[at]);
+            if constexpr (WEIGHTED) wr[u] = wts[at];
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+                r[u][t] = row_piece<VB>(p.x + (i < cnt ? row * p.row_bytes : 0), i < cnt ? (int)p.row_bytes : 0, (t * kWave + lane) * VB);
+        };
+#pragma unroll
+        for (int u = 0; u < R; ++u) request(u, u);
         for (int i0 = 0; i0 < cnt; i0 += R) {
-            Raw r[R][MT];
-            float wr[R];
-#pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int i = i0 + u < cnt ? i0 + u : cnt - 1;
-                const int64_t row_off = (int64_t)ids[i] * p.row_bytes;
-                if constexpr (WEIGHTED) wr[u] = wts[i];
-#pragma unroll
-                for (int t = 0; t < MT; ++t) {
-                    if (t < tiles) {                               // wave-uniform
-                        const int chunk = t * kWave + lane;        // lanes past the row width re-read chunk 0
-                        r[u][t] = *reinterpret_cast<const Raw*>(p.x + row_off + (chunk < p.chunks ? (int64_t)chunk * VB : 0));
-                    }
-                }
-            }
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 if (i0 + u < cnt) {
 #pragma unroll
                     for (int t = 0; t < MT; ++t) {
-                        if (t < tiles) {
-                            if constexpr (WEIGHTED) C::fma(acc[t], r[u][t], wr[u]);
-                            else C::add(acc[t], r[u][t]);
-                        }
+                        if constexpr (WEIGHTED) C::fma(acc[t], r[u][t], wr[u]);
+                        else C::add(acc[t], r[u][t]);
                     }
                     if constexpr (WEIGHTED) wsum += wr[u];
                 }
+                request(u, i0 + R + u);
             }
         }
         const float inv = WEIGHTED ? inv_weight(wsum) : inv_count(cnt > 0 ? cnt : 1);
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             const int chunk = t * kWave + lane;
-            if (t < tiles && chunk < p.chunks) {
+            if (chunk < p.chunks) {
 #pragma unroll
                 for (int e = 0; e < VE; ++e) acc[t][e] *= inv;
                 *reinterpret_cast<Raw*>(dst + (int64_t)chunk * VB) = C::pack(acc[t]);
@@ -280,8 +304,8 @@ constexpr int kRootsPerWorkgroup = FSA_ROOTS_PER_WG;             // with one wav
 #endif
 constexpr int kFwd1PackedPasses = FSA_FWD1_PACKED_PASSES;        // sampling passes of a packed 1-hop wave
 
-// MT > 0 selects the gather for rows wider than one tile of 64 lanes (2 .. MT tiles, MT at
-// most kMultiTiles): all tiles of a row are loaded back to back, so the cache line that two
+// MT > 0 selects the gather for rows wider than one tile of 64 lanes (2 .. MT tiles, MT 3, 5 or
+// kMultiTiles): all tiles of a row are loaded back to back, so the cache line that two
 // neighbouring tiles share is fetched once -- walking the whole list once per tile fetched it
 // twice, 20 % more HBM-side traffic than the rows themselves on 2408-byte rows.  MT = 0 is
 // the single-tile gather (and the fallback for rows wider than kMultiTiles tiles).
@@ -523,7 +547,9 @@ __global__ __launch_bounds__(512) void fwd2_kernel(const FwdParams p) {
     FSA_STAMP(t_gather);
     if constexpr (MT > 0) {
         // rows wider than one tile: sub == 64, one sub-group, the wave walks its whole list
-        constexpr int R = FSA_MULTI_LOADS / MT;                    // rows in flight: 2 x 4 tiles or 1 x 8
+        // R rows are in flight at any time: as soon as the oldest has been added, its registers take the
+        // row R entries further down the list.
+        constexpr int R = RowsInFlight<VB, MT>::value;
         const int tiles = (p.chunks + kWave - 1) >> 6;             // 2 .. MT, checked on the host
         float acc[MT][VE], root[MT][VE];
 #pragma unroll
@@ -539,36 +565,32 @@ __global__ __launch_bounds__(512) void fwd2_kernel(const FwdParams p) {
                     *reinterpret_cast<Raw*>(dst + (int64_t)chunk * VB) = C::pack(acc[0]);
             }
         }
+        Raw r[R][MT];
+        float wr[R];
+        bool ends[R];                                              // the row in flight in r[u] is the last of its slot
+        auto request = [&](int u, int i) {
+            const bool there = i < total;                          // wave-uniform
+            const int2 ent = flat[there ? i : 0];
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(ent.x), hi = __builtin_amdgcn_readfirstlane(ent.y);
+            ends[u] = (hi >> 31) != 0u;
+            if constexpr (WEIGHTED) wr[u] = flat_w[there ? i : 0];
+            const char* row = p.x + (there ? (uint64_t)(hi & 0x7fffffffu) << 32 | lo : 0ull);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) r[u][t] = row_piece<VB>(row, there ? (int)p.row_bytes : 0, (t * kWave + lane) * VB);
+        };
+#pragma unroll
+        for (int u = 0; u < R; ++u) request(u, u);
         for (int i0 = 0; i0 < total; i0 += R) {
-            int2 ent[R];
-            float wr[R];
-            Raw r[R][MT];
-#pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int i = i0 + u < total ? i0 + u : total - 1;
-                ent[u] = flat[i];
-                if constexpr (WEIGHTED) wr[u] = flat_w[i];
-                const uint64_t row_off = row_offset_of(ent[u]);
-#pragma unroll
-                for (int t = 0; t < MT; ++t) {
-                    if (t < tiles) {                               // wave-uniform
-                        const int chunk = t * kWave + lane;        // lanes past the row width re-read chunk 0
-                        r[u][t] = *reinterpret_cast<const Raw*>(p.x + row_off + (chunk < p.chunks ? (int64_t)chunk * VB : 0));
-                    }
-                }
-            }
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 if (i0 + u < total) {
 #pragma unroll
                     for (int t = 0; t < MT; ++t) {
-                        if (t < tiles) {
-                            if constexpr (WEIGHTED) C::fma(acc[t], r[u][t], wr[u]);
-                            else C::add(acc[t], r[u][t]);
-                        }
+                        if constexpr (WEIGHTED) C::fma(acc[t], r[u][t], wr[u]);
+                        else C::add(acc[t], r[u][t]);
                     }
                     if constexpr (WEIGHTED) wacc += wr[u];
-                    if (ent[u].y < 0) {                            // last row of its slot
+                    if (ends[u]) {
                         const int meta = flat_meta[i0 + u];
                         float inv, a = 1.0f;
                         if constexpr (WEIGHTED) {
@@ -582,22 +604,21 @@ __global__ __launch_bounds__(512) void fwd2_kernel(const FwdParams p) {
                         char* dst = p.out_h1 ? p.out_h1 + (b * k1 + (meta & 0xff)) * p.row_bytes : nullptr;
 #pragma unroll
                         for (int t = 0; t < MT; ++t) {
-                            if (t < tiles) {
-                                const int chunk = t * kWave + lane;
+                            const int chunk = t * kWave + lane;
 #pragma unroll
-                                for (int e = 0; e < VE; ++e) {
-                                    acc[t][e] *= inv;
-                                    if constexpr (WEIGHTED) root[t][e] = fmaf(a, acc[t][e], root[t][e]);
-                                    else root[t][e] += acc[t][e];
-                                }
-                                if (dst && chunk < p.chunks)
-                                    *reinterpret_cast<Raw*>(dst + (int64_t)chunk * VB) = C::pack(acc[t]);
-#pragma unroll
-                                for (int e = 0; e < VE; ++e) acc[t][e] = 0.0f;
+                            for (int e = 0; e < VE; ++e) {
+                                acc[t][e] *= inv;
+                                if constexpr (WEIGHTED) root[t][e] = fmaf(a, acc[t][e], root[t][e]);
+                                else root[t][e] += acc[t][e];
                             }
+                            if (dst && chunk < p.chunks)
+                                *reinterpret_cast<Raw*>(dst + (int64_t)chunk * VB) = C::pack(acc[t]);
+#pragma unroll
+                            for (int e = 0; e < VE; ++e) acc[t][e] = 0.0f;
                         }
                     }
                 }
+                request(u, i0 + R + u);
             }
         }
         if constexpr (WEIGHTED) { if (lane == 0) reinterpret_cast<float*>(live_slots)[strip] = rootw; }
@@ -850,16 +871,18 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
     constexpr int VE = Chunk<XT, VB>::VE;
     FwdParams p = p_in;
     const bool replay = a.indptr == nullptr;
-    // rows of 2 .. kMultiTiles tiles of 64 lanes take the row-major multi-tile gather
+    // rows of 2 .. kMultiTiles tiles of 64 lanes take the row-major multi-tile gather; tiles that a row does
+    // not have cost registers and instructions, so there are three sizes of it
     const int tiles = a.geom.tiles;
-    const int mt = (tiles <= 1 || tiles > kMultiTiles) ? 0 : (tiles <= 4 ? 4 : 8);
+    const int mt = (tiles <= 1 || tiles > kMultiTiles) ? 0 : tiles <= 3 ? 3 : tiles <= 5 ? 5 : 8;
     if constexpr (!WEIGHTED) {
         if (a.slot_cnt) {                       // mean over the per-slot rows of a [B,k1,D] table
             const int wpb = 4;
             const dim3 grid((unsigned)((a.B + wpb - 1) / wpb)), block(wpb * kWave);
             const size_t lds = sizeof(int) * kWave * wpb;
             if (mt == 0)      hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 0>), grid, block, lds, stream, p);
-            else if (mt == 4) hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 4>), grid, block, lds, stream, p);
+            else if (mt == 3) hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 3>), grid, block, lds, stream, p);
+            else if (mt == 5) hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 5>), grid, block, lds, stream, p);
             else              hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 8>), grid, block, lds, stream, p);
             return hipGetLastError();
         }
@@ -893,7 +916,8 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
             else        hipLaunchKernelGGL((fwd2_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
         } while (0)
         if (mt == 0) FSA_LAUNCH_FWD1P(0);
-        else if (mt == 4) FSA_LAUNCH_FWD1P(4);
+        else if (mt == 3) FSA_LAUNCH_FWD1P(3);
+        else if (mt == 5) FSA_LAUNCH_FWD1P(5);
         else FSA_LAUNCH_FWD1P(8);
 #undef FSA_LAUNCH_FWD1P
     } else if (a.hops == 1) {
@@ -907,7 +931,8 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
             else        hipLaunchKernelGGL((fwd1_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
         } while (0)
         if (mt == 0) FSA_LAUNCH_FWD1(0);
-        else if (mt == 4) FSA_LAUNCH_FWD1(4);
+        else if (mt == 3) FSA_LAUNCH_FWD1(3);
+        else if (mt == 5) FSA_LAUNCH_FWD1(5);
         else FSA_LAUNCH_FWD1(8);
 #undef FSA_LAUNCH_FWD1
     } else {
@@ -935,7 +960,8 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
             else        hipLaunchKernelGGL((fwd2_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
         } while (0)
         if (mt == 0) FSA_LAUNCH_FWD2(0);
-        else if (mt == 4) FSA_LAUNCH_FWD2(4);
+        else if (mt == 3) FSA_LAUNCH_FWD2(3);
+        else if (mt == 5) FSA_LAUNCH_FWD2(5);
         else FSA_LAUNCH_FWD2(8);
 #undef FSA_LAUNCH_FWD2
     }
