@@ -119,8 +119,8 @@ template <int VE, typename T> __device__ __forceinline__ T add_chunk(const T& v,
 
 // One workgroup per root: slot counts, coefficients, entries into buckets; and, with gradients into the
 // per-slot means, the one row that every leaf of a slot receives, so that the reduce kernel gathers one
-// row per leaf instead of two (it is bound by what it gathers; writing the rows here goes on beside the
-// appends' latency).
+// row per leaf instead of two (it is bound by what it gathers).  Bound by the places' atomics (one 64-byte
+// segment each: 251 k of them 14 us), then by the slot rows read and written.
 template <int VB>
 __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
     __shared__ int u[64];
@@ -171,20 +171,35 @@ __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
     if (p.slot_grad) {                                                // grid-uniform
         using T = typename FloatChunk<VB>::T;
         constexpr int VE = FloatChunk<VB>::VE;
+        constexpr int U = 8;                                          // loads in flight: 1024 roots of 25 slots of 2408 bytes
+                                                                      // 44.8 us with one, 39.4 with 8, 40.5 with 16
         __syncthreads();                                              // cf_shared
         const T* go = reinterpret_cast<const T*>(p.grad_out + b * p.D);
-        for (int j = tid >> 6; j < k1; j += (int)(blockDim.x >> 6)) { // a wave per slot
-            const float2 cf = cf_shared[j];
-            if (!(cf.y > 0.0f)) continue;                             // no leaf names an empty slot
-            const T* gh = reinterpret_cast<const T*>(p.grad_h1 + (b * k1 + j) * p.D);
-            T* dst = reinterpret_cast<T*>(p.slot_grad + (b * k1 + j) * p.D);
-            for (int chunk = tid & 63; chunk < p.chunks; chunk += kWave) {
-                float v[VE];
+        const T* gh = reinterpret_cast<const T*>(p.grad_h1 + b * k1 * p.D);
+        T* dst = reinterpret_cast<T*>(p.slot_grad + b * k1 * p.D);
+        const int n = k1 * p.chunks;                                  // the root's slot rows lie one after the other
+        for (int i0 = tid; i0 < n; i0 += U * (int)blockDim.x) {
+            T from_root[U], from_slot[U];
+            float2 cf[U];
 #pragma unroll
-                for (int c = 0; c < VE; ++c) v[c] = 0.0f;
-                fma_chunk<VE>(v, go[chunk], cf.x);
-                fma_chunk<VE>(v, gh[chunk], cf.y);
-                dst[chunk] = add_chunk<VE>(T{}, v);
+            for (int k = 0; k < U; ++k) {
+                const int i = i0 + k * (int)blockDim.x < n ? i0 + k * (int)blockDim.x : i0;  // past the end: the first one again
+                const int j = i / p.chunks;
+                cf[k] = cf_shared[j];
+                from_root[k] = go[i - j * p.chunks];
+                from_slot[k] = *(cf[k].y > 0.0f ? gh + i : go + (i - j * p.chunks));      // an empty slot's row is not read
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int i = i0 + k * (int)blockDim.x;
+                if (i < n && cf[k].y > 0.0f) {                        // no leaf names an empty slot
+                    float v[VE];
+#pragma unroll
+                    for (int c = 0; c < VE; ++c) v[c] = 0.0f;
+                    fma_chunk<VE>(v, from_root[k], cf[k].x);
+                    fma_chunk<VE>(v, from_slot[k], cf[k].y);
+                    dst[i] = add_chunk<VE>(T{}, v);
+                }
             }
         }
     }

@@ -137,6 +137,27 @@ template <> struct RawOf<8>  { using type = uint2; };
 template <> struct RawOf<4>  { using type = uint32_t; };
 template <> struct RawOf<2>  { using type = uint16_t; };
 
+// A piece of VB bytes of one row, for gathers of rows wider than one tile of lanes.  `row` is the same in all lanes.  The row is
+// addressed as a buffer of its own: pieces that start at or behind its end (`bytes`) read as zero and cost no
+// memory access, so that the tiles of a row, and rows behind the end of a list (bytes = 0), are requested
+// without a branch -- the hardware counter that orders loads cannot be tracked across one.
+template <int VB>
+__device__ __forceinline__ typename RawOf<VB>::type row_piece(const char* row, int bytes, int at) {
+    if constexpr (VB == 2) {                    // (rows at odd multiples of 2 bytes: plain loads)
+        const int from = at < bytes ? at : 0;
+        uint16_t v = 0;
+        if (bytes > 0) v = *reinterpret_cast<const uint16_t*>(row + from);
+        return v;
+    } else {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), 0, bytes, 0x00020000);   // raw, 32-bit data
+        typename RawOf<VB>::type v;
+        if constexpr (VB == 16) { const auto q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        else if constexpr (VB == 8) { const auto q = __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        else { const auto q = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0); __builtin_memcpy(&v, &q, sizeof v); }
+        return v;
+    }
+}
+
 __device__ __forceinline__ float bits_f32(uint32_t u) { return __uint_as_float(u); }
 
 // 1/n for a small positive count n: the hardware reciprocal is within 1 ulp, far inside the
