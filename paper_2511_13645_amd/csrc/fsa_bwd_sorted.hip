@@ -439,7 +439,9 @@ __global__ __launch_bounds__(kSortedThreads) void sorted_reduce_narrow_kernel(co
 // three launches and the binning do not) and the batch moves enough bytes to hide them.  Rows
 // under 1 KB gain less -- every leaf re-reads its slot's gradient rows, which the atomic backward
 // reads once per slot -- and only in large batches: D=128, 614 k leaves, 121 -> 102 us; D=100,
-// 614 k leaves, 237 -> 210 us; but 154 k leaves, 64 -> 75 us.
+// 614 k leaves, 237 -> 210 us; but 154 k leaves, 64 -> 75 us.  Since the atomics are cut at the rows' 64-byte
+// segments, forward and backward, atomics against this: D=100, 614 k leaves 278 / 227 us (D=128 305 / 231), 405 k
+// leaves 188 / 163; D=256, 77 k leaves 87 / 83.
 constexpr int64_t kSortedMinRowBytes = kSortedWideRowBytes;
 constexpr int64_t kSortedMinPayload = 32ll << 20;
 constexpr int64_t kSortedNarrowMinRowBytes = 256;
