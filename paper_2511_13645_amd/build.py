@@ -60,7 +60,7 @@ def build_hip(extra_flags=(), verbose: bool = False, out: str = LIB) -> str:
     return out
 
 
-def build_host(verbose: bool = False, out: str = HOST_LIB) -> str:
+def build_host(extra_flags=(), verbose: bool = False, out: str = HOST_LIB) -> str:
     """Compile the binding's host path (plain C++ against torch's headers and the CPython C API)."""
     import sysconfig
     import torch
@@ -69,7 +69,7 @@ def build_host(verbose: bool = False, out: str = HOST_LIB) -> str:
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
-           "-isystem", sysconfig.get_paths()["include"], HOST_SOURCE, "-o", tmp,
+           "-isystem", sysconfig.get_paths()["include"], *extra_flags, HOST_SOURCE, "-o", tmp,
            "-L" + os.path.join(base, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)

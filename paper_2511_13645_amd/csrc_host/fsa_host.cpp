@@ -103,7 +103,7 @@ template <size_t N> PyObject* tuple_of(const Tensor (&t)[N]) {
 template <typename T = void> T* data(const Tensor& t) { return t.defined() ? static_cast<T*>(t.data_ptr()) : nullptr; }
 template <typename T = void> T* data(const Tensor* t) { return t ? static_cast<T*>(t->data_ptr()) : nullptr; }
 
-// The C call, with other threads free to run meanwhile.
+// Allocations (which may wait for the driver) and the C call, with other threads free to run meanwhile.
 template <typename F> int without_gil(F f) {
     struct Released {
         PyThreadState* state = PyEval_SaveThread();
@@ -146,14 +146,15 @@ PyObject* sample_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const bool emit_ids = a[8] == Py_True, two = hops == 2;
         const auto rows = at::TensorOptions().dtype(x->dtype()).device(x->device());
         const auto ids = rows.dtype(at::kInt), weights = rows.dtype(at::kFloat);
+        const bool emit_h1 = two && a[7] == Py_True;
         Tensor o[6];
-        o[0] = at::empty({B, D}, rows);
-        if (two && a[7] == Py_True) o[1] = at::empty({B, fan[0], D}, rows);
-        if (emit_ids) o[2] = at::empty({B, fan[0]}, ids);
-        if (emit_ids && two) o[3] = at::empty({B, fan[0], fan[1]}, ids);
-        if (weighted && emit_ids) o[4] = at::empty({B, fan[0]}, weights);
-        if (weighted && emit_ids && two) o[5] = at::empty({B, fan[0], fan[1]}, weights);
         const int rc = without_gil([&] {
+            o[0] = at::empty({B, D}, rows);
+            if (emit_h1) o[1] = at::empty({B, fan[0], D}, rows);
+            if (emit_ids) o[2] = at::empty({B, fan[0]}, ids);
+            if (emit_ids && two) o[3] = at::empty({B, fan[0], fan[1]}, ids);
+            if (weighted && emit_ids) o[4] = at::empty({B, fan[0]}, weights);
+            if (weighted && emit_ids && two) o[5] = at::empty({B, fan[0], fan[1]}, weights);
             return weighted ? abi.sample_wmean_fwd(data(indptr), wide, data<int32_t>(indices), data<float>(edge_w), N, data(x), code, D,
                                                    data<int32_t>(seeds), B, fan, hops, seed, data(o[0]), data(o[1]),
                                                    data<int32_t>(o[2]), data<int32_t>(o[3]), data<float>(o[4]), data<float>(o[5]), stream)
@@ -185,10 +186,11 @@ PyObject* replay_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         void* stream;
         if (!stream_of(*x, &stream)) return nullptr;
         const auto rows = at::TensorOptions().dtype(x->dtype()).device(x->device());
+        const bool emit_h1 = two && a[3] == Py_True;
         Tensor o[2];
-        o[0] = at::empty({B, D}, rows);
-        if (two && a[3] == Py_True) o[1] = at::empty({B, k1, D}, rows);
         const int rc = without_gil([&] {
+            o[0] = at::empty({B, D}, rows);
+            if (emit_h1) o[1] = at::empty({B, k1, D}, rows);
             return abi.mean_replay_fwd(data(x), code, D, N, data<int32_t>(ids1), data<int32_t>(ids2), B, (int32_t)k1, (int32_t)k2,
                                        data(o[0]), data(o[1]), stream);
         });

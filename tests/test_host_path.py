@@ -1,0 +1,66 @@
+"""The binding's native host path (csrc_host/fsa_host.cpp) without a GPU: built with a header that lets CPU tensors
+through, its library calls answered by Python functions."""
+import ctypes
+import importlib.machinery
+import importlib.util
+import os
+
+import pytest
+import torch
+
+from paper_2511_13645_amd import binding, build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+B, N, E, D, K1, K2 = 5, 9, 20, 8, 3, 2
+
+
+class Host:
+    """The module, the calls that reached the library, and what they are to return."""
+    def __init__(self, path):
+        spec = importlib.util.spec_from_loader("_fsa_host", importlib.machinery.ExtensionFileLoader("_fsa_host", path))
+        self.module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.module)
+        self.shim = ctypes.CDLL(path)
+        self.calls, self.status, self.keep = [], 0, []
+        addresses = []
+        for name in binding._HOST_ENTRIES:
+            fn = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(binding.lib(), name).argtypes)(self._answer(name))
+            self.keep.append(fn)
+            addresses.append(ctypes.cast(fn, ctypes.c_void_p).value)
+        self.module.bind(lambda device: 4711, *addresses)
+
+    def _answer(self, name):
+        def call(*args):
+            self.calls.append((name, args))
+            return self.status
+        return call
+
+    def count(self, name):
+        return ctypes.c_int.in_dll(self.shim, name).value
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host") / "_fsa_host_on_cpu.so")
+    build.build_host(("-include", os.path.join(ROOT, "tests", "native", "host_path_shim.h")), out=out)
+    return Host(out)
+
+
+def _graph():
+    i32 = dict(dtype=torch.int32)
+    return dict(indptr=torch.zeros(N + 1, **i32), indices=torch.zeros(E, **i32), w=torch.zeros(E), x=torch.zeros(N, D),
+                seeds=torch.zeros(B, **i32), ids1=torch.zeros((B, K1), **i32), ids2=torch.zeros((B, K1, K2), **i32))
+
+
+@pytest.mark.parametrize("fan", [[K1], [K1, K2]])
+def test_outputs_are_allocated_without_the_interpreter_lock(host, fan):
+    """An allocation may wait for the driver; other threads run meanwhile, as they do in torch's own allocating calls."""
+    g, two = _graph(), len(fan) == 2
+    before, held = host.count("allocations"), host.count("allocations_with_gil")
+    for w in (None, g["w"]):
+        out = host.module.sample_fwd(g["indptr"], g["indices"], w, g["x"], g["seeds"], fan, 1, True, True)
+        assert out[0].shape == (B, D) and out[2].shape == (B, K1)
+    out = host.module.replay_fwd(g["x"], g["ids1"], g["ids2"] if two else None, True)
+    assert out[0].shape == (B, D)
+    assert host.count("allocations") - before == (4 + 6 + 2 if two else 2 + 3 + 1)
+    assert host.count("allocations_with_gil") == held
