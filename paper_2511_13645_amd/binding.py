@@ -4,7 +4,7 @@ kernels.  PyTorch is used for device memory and the current stream, nothing else
 
 The functions below are the binding, through ctypes.  The most frequent of them first offer the call to
 their counterpart in ``_fsa_host`` (csrc_host/fsa_host.cpp), which does the same without the interpreter for
-plain arguments and returns None for anything else.
+plain arguments and returns None for anything else.  Without that module they take every call.
 
 The library must have been built (``python -m paper_2511_13645_amd.build`` or
 ``__graft_entry__.build()``); there is no CPU fallback -- a missing library raises.
@@ -13,14 +13,19 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.machinery
+import importlib.util
 import os
+import warnings
 from typing import Optional, Sequence, Tuple
 
 import torch
 
+from . import build
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfsa_hip.so")
-HOST_PATH = os.path.join(_HERE, "_fsa_host.so")
+HOST_PATH = build.host_lib()
 
 FSA_F32, FSA_BF16, FSA_F16 = 0, 1, 2
 FSA_I32, FSA_I64 = 0, 1
@@ -35,7 +40,7 @@ EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_me
            "fsa_sample_wmean_fwd", "fsa_wmean_replay_fwd", "fsa_wmean_bwd")
 
 _lib: Optional[ctypes.CDLL] = None
-_host = None                                    # the module _fsa_host, once the library is loaded
+_host = None                                    # the module _fsa_host, once the library is loaded; None without it
 _HOST_ENTRIES = ("fsa_sample_mean_fwd", "fsa_sample_wmean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_ws",
                  "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws")              # in the order that _fsa_host.bind takes them
 _PLAIN, _WORKSPACE, _LOW_PRECISION, _WEIGHTED = range(4)                # backward entry points, as _fsa_host.bwd counts them
@@ -53,8 +58,6 @@ def lib() -> ctypes.CDLL:
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("HIP library missing: %s (build it with __graft_entry__.build())" % LIB_PATH)
-        if not os.path.exists(HOST_PATH):
-            raise RuntimeError("host library missing: %s (build it with __graft_entry__.build())" % HOST_PATH)
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, u64, ci = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64, ctypes.c_int
         L.fsa_sample_mean_fwd.argtypes = [vp, ci, vp, i64, vp, ci, i64, vp, i64, vp, ci, u64,
@@ -99,10 +102,22 @@ def lib() -> ctypes.CDLL:
         L.fsa_mean3_bwd_ws.restype = ci
         L.fsa_status_string.argtypes = [ci]
         L.fsa_status_string.restype = ctypes.c_char_p
-        from . import _fsa_host
-        _fsa_host.bind(_raw_stream, *(ctypes.cast(getattr(L, name), vp).value for name in _HOST_ENTRIES))
-        _lib, _host = L, _fsa_host
+        _lib, _host = L, _load_host(L)
     return _lib
+
+
+def _load_host(L: ctypes.CDLL):
+    """The module _fsa_host at HOST_PATH, or None and a warning: it saves host time and nothing else."""
+    try:
+        spec = importlib.util.spec_from_loader("_fsa_host", importlib.machinery.ExtensionFileLoader("_fsa_host", HOST_PATH))
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(_raw_stream, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _HOST_ENTRIES))
+        return module
+    except (ImportError, TypeError) as e:
+        warnings.warn("calls go through Python only, which takes a few microseconds more: no %s (%s; build it with "
+                      "__graft_entry__.build())" % (HOST_PATH, e), RuntimeWarning, stacklevel=3)
+        return None
 
 
 def status_string(status: int) -> str:

@@ -1,10 +1,12 @@
 """Builds the HIP library (gfx950) in-tree, ``paper_2511_13645_amd/libfsa_hip.so``, and the binding's host
-path, ``paper_2511_13645_amd/_fsa_host.so``."""
+path, ``paper_2511_13645_amd/_fsa_host.*.so``."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
+from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -22,7 +24,13 @@ HIPCC_FLAGS = [
 
 
 HOST_SOURCE = os.path.join(HERE, "csrc_host", "fsa_host.cpp")
-HOST_LIB = os.path.join(HERE, "_fsa_host.so")
+
+
+def host_lib() -> str:
+    """Where the host path for the running Python and torch lies.  It uses parts of both that other versions lay out
+    otherwise, so a build for another one has another name and is never loaded."""
+    import torch
+    return os.path.join(HERE, "_fsa_host.%s.torch-%s.so" % (sys.implementation.cache_tag, torch.__version__))
 
 
 def hipcc() -> str:
@@ -60,10 +68,10 @@ def build_hip(extra_flags=(), verbose: bool = False, out: str = LIB) -> str:
     return out
 
 
-def build_host(extra_flags=(), verbose: bool = False, out: str = HOST_LIB) -> str:
+def build_host(extra_flags=(), verbose: bool = False, out: Optional[str] = None) -> str:
     """Compile the binding's host path (plain C++ against torch's headers and the CPython C API)."""
-    import sysconfig
     import torch
+    out = out or host_lib()
     base = os.path.dirname(torch.__file__)
     tmp = out + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
@@ -79,10 +87,10 @@ def build_host(extra_flags=(), verbose: bool = False, out: str = HOST_LIB) -> st
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(HOST_LIB):
+    if not os.path.exists(LIB) or not os.path.exists(host_lib()):
         return True
     newest = max(os.path.getmtime(os.path.join(CSRC, f)) for f in SOURCES + HEADERS)
-    return os.path.getmtime(LIB) < newest or os.path.getmtime(HOST_LIB) < os.path.getmtime(HOST_SOURCE)
+    return os.path.getmtime(LIB) < newest or os.path.getmtime(host_lib()) < os.path.getmtime(HOST_SOURCE)
 
 
 if __name__ == "__main__":
@@ -96,4 +104,7 @@ if __name__ == "__main__":
         del argv[i:i + 2]
     print(build_hip(argv, verbose=True, out=target))
     if target == LIB:
-        print(build_host(verbose=True))
+        try:
+            print(build_host(verbose=True))
+        except (OSError, subprocess.CalledProcessError) as e:
+            print("the host path was not built, the binding goes without it: %s" % e, file=sys.stderr)

@@ -4,6 +4,8 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -64,3 +66,29 @@ def test_outputs_are_allocated_without_the_interpreter_lock(host, fan):
     assert out[0].shape == (B, D)
     assert host.count("allocations") - before == (4 + 6 + 2 if two else 2 + 3 + 1)
     assert host.count("allocations_with_gil") == held
+
+
+@pytest.mark.parametrize("found", ["nothing", "something else"])
+def test_the_library_loads_without_the_host_path(tmp_path, found):
+    """The host path only saves time: where it is missing, or what lies there is no module of this Python, the binding
+    says so and takes every call itself."""
+    path = tmp_path / "host.so"
+    if found == "something else":
+        path.write_bytes(b"not a shared object")
+    code = ("import warnings\n"
+            "from paper_2511_13645_amd import binding\n"
+            "binding.HOST_PATH = %r\n"
+            "with warnings.catch_warnings(record=True) as w:\n"
+            "    warnings.simplefilter('always')\n"
+            "    assert binding.lib() and binding._host is None\n"
+            "assert [x for x in w if issubclass(x.category, RuntimeWarning) and binding.HOST_PATH in str(x.message)]\n"
+            "assert binding.fsa_mean_bwd_workspace_bytes(1024, 25, 10, 602) > 0\n" % str(path))
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+
+
+def test_the_host_path_belongs_to_one_python_and_one_torch():
+    """It uses what neither keeps stable: a build for another one has another name and is not loaded."""
+    name = os.path.basename(binding.HOST_PATH)
+    assert sys.implementation.cache_tag in name and torch.__version__ in name
+    assert binding.lib() and binding._host.__file__ == binding.HOST_PATH
