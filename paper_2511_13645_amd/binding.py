@@ -42,7 +42,7 @@ EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_me
 _lib: Optional[ctypes.CDLL] = None
 _host = None                                    # the module _fsa_host, once the library is loaded; None without it
 _HOST_ENTRIES = ("fsa_sample_mean_fwd", "fsa_sample_wmean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_ws",
-                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws")              # in the order that _fsa_host.bind takes them
+                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws")              # entry points that _fsa_host calls
 _PLAIN, _WORKSPACE, _LOW_PRECISION, _WEIGHTED = range(4)                # backward entry points, as _fsa_host.bwd counts them
 
 
@@ -112,7 +112,7 @@ def _load_host(L: ctypes.CDLL):
         spec = importlib.util.spec_from_loader("_fsa_host", importlib.machinery.ExtensionFileLoader("_fsa_host", HOST_PATH))
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
-        module.bind(_raw_stream, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _HOST_ENTRIES))
+        module.bind(_raw_stream, {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _HOST_ENTRIES})
         return module
     except (ImportError, TypeError) as e:
         warnings.warn("calls go through Python only, which takes a few microseconds more: no %s (%s; build it with "

@@ -11,8 +11,9 @@ from typing import Optional
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfsa_hip.so")
+ABI_HEADER = os.path.normpath(os.path.join(HERE, "..", "include", "fsa.h"))
 SOURCES = ["fsa_api.hip", "fsa_fwd.hip", "fsa_bwd.hip", "fsa_bwd_sorted.hip", "fsa_bwd_owned.hip", "fsa_wbwd.hip"]
-HEADERS = ["fsa_device.hip.h", "fsa_atomic_rows.hip.h", "fsa_internal.h", "fsa_layout.h", os.path.join("..", "..", "include", "fsa.h")]
+HEADERS = ["fsa_device.hip.h", "fsa_atomic_rows.hip.h", "fsa_internal.h", "fsa_layout.h", ABI_HEADER]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -90,7 +91,8 @@ def is_stale() -> bool:
     if not os.path.exists(LIB) or not os.path.exists(host_lib()):
         return True
     newest = max(os.path.getmtime(os.path.join(CSRC, f)) for f in SOURCES + HEADERS)
-    return os.path.getmtime(LIB) < newest or os.path.getmtime(host_lib()) < os.path.getmtime(HOST_SOURCE)
+    newest_host = max(os.path.getmtime(f) for f in (HOST_SOURCE, ABI_HEADER))
+    return os.path.getmtime(LIB) < newest or os.path.getmtime(host_lib()) < newest_host
 
 
 if __name__ == "__main__":

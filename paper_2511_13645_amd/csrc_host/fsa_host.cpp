@@ -6,6 +6,8 @@
 // expected types and shapes on one GPU, no mode that wants to see the allocations -- and returns None for
 // anything else: the Python code of the binding, which is complete by itself, then takes the call and
 // raises what there is to raise.  A failed library call returns its status, an int.
+#include "../../include/fsa.h"
+
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -20,22 +22,13 @@ using at::Tensor;
 
 PyObject* raw_stream = nullptr;                        // device index -> current stream's handle
 
-// Addresses of the C ABI's entry points (include/fsa.h), set by bind().
+// Addresses of the C ABI's entry points, set by bind(), with the types that fsa.h declares them with.
+#define FSA_HOST_ENTRIES(X) X(fsa_sample_mean_fwd) X(fsa_sample_wmean_fwd) X(fsa_mean_replay_fwd) X(fsa_mean_bwd) \
+                            X(fsa_mean_bwd_ws) X(fsa_mean_bwd_lp_ws) X(fsa_wmean_bwd_ws)
 struct {
-    int (*sample_mean_fwd)(const void*, int, const int32_t*, int64_t, const void*, int, int64_t, const int32_t*, int64_t,
-                           const int32_t*, int, uint64_t, void*, void*, int32_t*, int32_t*, void*);
-    int (*sample_wmean_fwd)(const void*, int, const int32_t*, const float*, int64_t, const void*, int, int64_t, const int32_t*,
-                            int64_t, const int32_t*, int, uint64_t, void*, void*, int32_t*, int32_t*, float*, float*, void*);
-    int (*mean_replay_fwd)(const void*, int, int64_t, int64_t, const int32_t*, const int32_t*, int64_t, int32_t, int32_t, void*,
-                           void*, void*);
-    int (*mean_bwd)(const float*, const float*, const int32_t*, const int32_t*, int64_t, int32_t, int32_t, int64_t, float*,
-                    int64_t, void*);
-    int (*mean_bwd_ws)(const float*, const float*, const int32_t*, const int32_t*, int64_t, int32_t, int32_t, int64_t, float*,
-                       int64_t, void*, int64_t, void*);
-    int (*mean_bwd_lp_ws)(const void*, const void*, int, const int32_t*, const int32_t*, int64_t, int32_t, int32_t, int64_t,
-                          void*, int, int64_t, void*, int64_t, void*);
-    int (*wmean_bwd_ws)(const float*, const float*, const int32_t*, const int32_t*, const float*, const float*, int64_t, int32_t,
-                        int32_t, int64_t, float*, int64_t, void*, int64_t, void*);
+#define FSA_HOST_MEMBER(name) decltype(&::name) name;
+    FSA_HOST_ENTRIES(FSA_HOST_MEMBER)
+#undef FSA_HOST_MEMBER
 } abi;
 
 // The tensor behind an argument, or nullptr for anything but a plain tensor or parameter.
@@ -47,9 +40,9 @@ bool together(const Tensor& a, const Tensor& b) { return a.get_device() == b.get
 
 int float_code(const Tensor& t) {                      // fsa.h's dtype code, -1 for none
     switch (t.scalar_type()) {
-        case at::kFloat: return 0;
-        case at::kBFloat16: return 1;
-        case at::kHalf: return 2;
+        case at::kFloat: return FSA_F32;
+        case at::kBFloat16: return FSA_BF16;
+        case at::kHalf: return FSA_F16;
         default: return -1;
     }
 }
@@ -66,7 +59,7 @@ int fanouts_of(PyObject* seq, int32_t (&fan)[2]) {
         if (!PyLong_CheckExact(k)) return 0;
         int over = 0;
         const long v = PyLong_AsLongAndOverflow(k, &over);
-        if (over || v < 1 || v > 64) return 0;         // the library refuses it: not here
+        if (over || v < 1 || v > FSA_KMAX) return 0;         // the library refuses it: not here
         fan[i] = (int32_t)v;
     }
     return (int)n;
@@ -134,10 +127,10 @@ PyObject* sample_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int hops = fanouts_of(a[5], fan);
         if (!hops || !PyLong_CheckExact(a[6]) || !PyBool_Check(a[7]) || !PyBool_Check(a[8]) || observed()) Py_RETURN_NONE;
         if (!plain(indptr, 1) || !plain(indices, 1, at::kInt) || !plain(x, 2) || !plain(seeds, 1, at::kInt)) Py_RETURN_NONE;
-        const bool wide = indptr->scalar_type() == at::kLong;
+        const int itype = indptr->scalar_type() == at::kLong ? FSA_I64 : FSA_I32;
         const int code = float_code(*x);
         const int64_t B = seeds->size(0), N = x->size(0), D = x->size(1);
-        if ((!wide && indptr->scalar_type() != at::kInt) || code < 0 || indptr->size(0) != N + 1) Py_RETURN_NONE;
+        if ((itype == FSA_I32 && indptr->scalar_type() != at::kInt) || code < 0 || indptr->size(0) != N + 1) Py_RETURN_NONE;
         if (!together(*x, *indptr) || !together(*x, *indices) || !together(*x, *seeds)) Py_RETURN_NONE;
         if (weighted && (!plain(edge_w, 1, at::kFloat) || edge_w->size(0) != indices->size(0) || !together(*x, *edge_w))) Py_RETURN_NONE;
         void* stream;
@@ -155,14 +148,14 @@ PyObject* sample_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (emit_ids && two) o[3] = at::empty({B, fan[0], fan[1]}, ids);
             if (weighted && emit_ids) o[4] = at::empty({B, fan[0]}, weights);
             if (weighted && emit_ids && two) o[5] = at::empty({B, fan[0], fan[1]}, weights);
-            return weighted ? abi.sample_wmean_fwd(data(indptr), wide, data<int32_t>(indices), data<float>(edge_w), N, data(x), code, D,
+            return weighted ? abi.fsa_sample_wmean_fwd(data(indptr), itype, data<int32_t>(indices), data<float>(edge_w), N, data(x), code, D,
                                                    data<int32_t>(seeds), B, fan, hops, seed, data(o[0]), data(o[1]),
                                                    data<int32_t>(o[2]), data<int32_t>(o[3]), data<float>(o[4]), data<float>(o[5]), stream)
-                            : abi.sample_mean_fwd(data(indptr), wide, data<int32_t>(indices), N, data(x), code, D, data<int32_t>(seeds), B,
+                            : abi.fsa_sample_mean_fwd(data(indptr), itype, data<int32_t>(indices), N, data(x), code, D, data<int32_t>(seeds), B,
                                                   fan, hops, seed, data(o[0]), data(o[1]), data<int32_t>(o[2]), data<int32_t>(o[3]),
                                                   stream);
         });
-        if (rc != 0) return PyLong_FromLong(rc);
+        if (rc != FSA_OK) return PyLong_FromLong(rc);
         if (weighted) return tuple_of(o);
         const Tensor four[4] = {o[0], o[1], o[2], o[3]};
         return tuple_of(four);
@@ -182,7 +175,7 @@ PyObject* replay_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (code < 0 || !together(*x, *ids1)) Py_RETURN_NONE;
         if (two && (!plain(ids2, 3, at::kInt) || ids2->size(0) != B || ids2->size(1) != k1 || !together(*x, *ids2))) Py_RETURN_NONE;
         const int64_t k2 = two ? ids2->size(2) : 0;
-        if (k1 < 1 || k1 > 64 || k2 > 64 || (two && k2 < 1)) Py_RETURN_NONE;
+        if (k1 < 1 || k1 > FSA_KMAX || k2 > FSA_KMAX || (two && k2 < 1)) Py_RETURN_NONE;
         void* stream;
         if (!stream_of(*x, &stream)) return nullptr;
         const auto rows = at::TensorOptions().dtype(x->dtype()).device(x->device());
@@ -191,10 +184,10 @@ PyObject* replay_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int rc = without_gil([&] {
             o[0] = at::empty({B, D}, rows);
             if (emit_h1) o[1] = at::empty({B, k1, D}, rows);
-            return abi.mean_replay_fwd(data(x), code, D, N, data<int32_t>(ids1), data<int32_t>(ids2), B, (int32_t)k1, (int32_t)k2,
+            return abi.fsa_mean_replay_fwd(data(x), code, D, N, data<int32_t>(ids1), data<int32_t>(ids2), B, (int32_t)k1, (int32_t)k2,
                                        data(o[0]), data(o[1]), stream);
         });
-        return rc != 0 ? PyLong_FromLong(rc) : tuple_of(o);
+        return rc != FSA_OK ? PyLong_FromLong(rc) : tuple_of(o);
     });
 }
 
@@ -216,10 +209,10 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (kind < kPlain || kind > kWeighted || observed() || !plain(g, 2) || !plain(ids1, 2, at::kInt) || !plain(gx, 2)) Py_RETURN_NONE;
         const int64_t B = ids1->size(0), k1 = ids1->size(1), D = g->size(1), N = gx->size(0);
         const int g_code = float_code(*g), x_code = float_code(*gx);
-        if (g_code < 0 || x_code < 0 || (kind != kLowPrecision && (g_code != 0 || x_code != 0))) Py_RETURN_NONE;
+        if (g_code < 0 || x_code < 0 || (kind != kLowPrecision && (g_code != FSA_F32 || x_code != FSA_F32))) Py_RETURN_NONE;
         if (g->size(0) != B || gx->size(1) != D || (ids2 && (ids2->dim() != 3 || ids2->scalar_type() != at::kInt || ids2->size(0) != B || ids2->size(1) != k1))) Py_RETURN_NONE;
         const int64_t k2 = ids2 ? ids2->size(2) : 0;
-        if (k1 < 1 || k1 > 64 || k2 > 64 || (ids2 && k2 < 1)) Py_RETURN_NONE;
+        if (k1 < 1 || k1 > FSA_KMAX || k2 > FSA_KMAX || (ids2 && k2 < 1)) Py_RETURN_NONE;
         if (gh && (gh->dim() != 3 || gh->scalar_type() != g->scalar_type() || gh->size(0) != B || gh->size(1) != k1 || gh->size(2) != D)) Py_RETURN_NONE;
         if ((kind == kWeighted) != (w1 != nullptr) || (w1 && (!plain(w1, 2, at::kFloat) || w1->size(0) != B || w1->size(1) != k1))) Py_RETURN_NONE;
         if ((w1 && ids2) != (w2 != nullptr) || (w2 && (!plain(w2, 3, at::kFloat) || w2->size(0) != B || w2->size(1) != k1 || w2->size(2) != k2))) Py_RETURN_NONE;
@@ -233,24 +226,28 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int32_t *i1 = data<int32_t>(ids1), *i2 = data<int32_t>(ids2);
         const int rc = without_gil([&]() -> int {
             switch (kind) {
-                case kPlain: return abi.mean_bwd(data<float>(g), data<float>(gh), i1, i2, B, f1, f2, D, data<float>(gx), N, stream);
-                case kWorkspace: return abi.mean_bwd_ws(data<float>(g), data<float>(gh), i1, i2, B, f1, f2, D, data<float>(gx), N, data(ws), ws_bytes, stream);
-                case kLowPrecision: return abi.mean_bwd_lp_ws(data(g), data(gh), g_code, i1, i2, B, f1, f2, D, data(gx), x_code, N, data(ws), ws_bytes, stream);
-                default: return abi.wmean_bwd_ws(data<float>(g), data<float>(gh), i1, i2, data<float>(w1), data<float>(w2), B, f1, f2, D, data<float>(gx), N, data(ws), ws_bytes, stream);
+                case kPlain: return abi.fsa_mean_bwd(data<float>(g), data<float>(gh), i1, i2, B, f1, f2, D, data<float>(gx), N, stream);
+                case kWorkspace: return abi.fsa_mean_bwd_ws(data<float>(g), data<float>(gh), i1, i2, B, f1, f2, D, data<float>(gx), N, data(ws), ws_bytes, stream);
+                case kLowPrecision: return abi.fsa_mean_bwd_lp_ws(data(g), data(gh), g_code, i1, i2, B, f1, f2, D, data(gx), x_code, N, data(ws), ws_bytes, stream);
+                default: return abi.fsa_wmean_bwd_ws(data<float>(g), data<float>(gh), i1, i2, data<float>(w1), data<float>(w2), B, f1, f2, D, data<float>(gx), N, data(ws), ws_bytes, stream);
             }
         });
         return PyLong_FromLong(rc);
     });
 }
 
-// (raw_stream, addresses in the order of `abi`)
+// (raw_stream, {entry point: address})
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    constexpr Py_ssize_t kEntries = sizeof(abi) / sizeof(void*);
-    if (n != 1 + kEntries) { PyErr_SetString(PyExc_TypeError, "a stream function and one address per entry point"); return nullptr; }
-    for (Py_ssize_t i = 0; i < kEntries; ++i) {
-        reinterpret_cast<void**>(&abi)[i] = PyLong_AsVoidPtr(a[1 + i]);
-        if (PyErr_Occurred()) return nullptr;
+    if (n != 2 || !PyDict_Check(a[1])) { PyErr_SetString(PyExc_TypeError, "a stream function and the entry points' addresses"); return nullptr; }
+#define FSA_HOST_BIND(name)                                                                                             \
+    {                                                                                                                   \
+        PyObject* at = PyDict_GetItemString(a[1], #name);                                                               \
+        if (!at) { PyErr_SetString(PyExc_TypeError, "no address for " #name); return nullptr; }                         \
+        abi.name = reinterpret_cast<decltype(abi.name)>(PyLong_AsVoidPtr(at));                                          \
+        if (PyErr_Occurred()) return nullptr;                                                                           \
     }
+    FSA_HOST_ENTRIES(FSA_HOST_BIND)
+#undef FSA_HOST_BIND
     Py_INCREF(a[0]);
     Py_XDECREF(raw_stream);
     raw_stream = a[0];

@@ -24,12 +24,12 @@ class Host:
         spec.loader.exec_module(self.module)
         self.shim = ctypes.CDLL(path)
         self.calls, self.status, self.keep = [], 0, []
-        addresses = []
+        addresses = {}
         for name in binding._HOST_ENTRIES:
             fn = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(binding.lib(), name).argtypes)(self._answer(name))
             self.keep.append(fn)
-            addresses.append(ctypes.cast(fn, ctypes.c_void_p).value)
-        self.module.bind(lambda device: 4711, *addresses)
+            addresses[name] = ctypes.cast(fn, ctypes.c_void_p).value
+        self.module.bind(lambda device: 4711, addresses)
 
     def _answer(self, name):
         def call(*args):
@@ -92,3 +92,40 @@ def test_the_host_path_belongs_to_one_python_and_one_torch():
     name = os.path.basename(binding.HOST_PATH)
     assert sys.implementation.cache_tag in name and torch.__version__ in name
     assert binding.lib() and binding._host.__file__ == binding.HOST_PATH
+
+
+def _sources(tmp_path, change=lambda text: text):
+    """A copy of fsa_host.cpp with include/fsa.h where it looks for it, the header changed."""
+    src = tmp_path / "package" / "csrc_host" / "fsa_host.cpp"
+    for path, text in ((src, open(build.HOST_SOURCE).read()),
+                       (tmp_path / "include" / "fsa.h", change(open(os.path.join(ROOT, "include", "fsa.h")).read()))):
+        path.parent.mkdir(parents=True, exist_ok=True)
+        path.write_text(text)
+    return str(src)
+
+
+def test_a_changed_declaration_of_the_library_does_not_compile(tmp_path, monkeypatch, capfd):
+    declared = "int fsa_mean_bwd(const float* grad_out, "
+    def change(text):
+        assert declared in text
+        return text.replace(declared, declared + "int64_t first_root, ")
+    monkeypatch.setattr(build, "HOST_SOURCE", _sources(tmp_path, change))
+    with pytest.raises(subprocess.CalledProcessError):
+        build.build_host(("-fsyntax-only",), out=str(tmp_path / "host.so"))
+    assert "abi.fsa_mean_bwd(" in capfd.readouterr().err
+
+
+def test_the_host_path_is_stale_after_a_change_of_the_header(tmp_path, monkeypatch):
+    header = os.path.join(ROOT, "include", "fsa.h")
+    at = os.path.getmtime(header)
+    files = {}
+    for name, mtime in (("LIB", at + 1e6), ("HOST_SOURCE", at - 20), ("host", at - 10)):
+        files[name] = str(tmp_path / name)
+        open(files[name], "w").close()
+        os.utime(files[name], (mtime, mtime))
+    monkeypatch.setattr(build, "LIB", files["LIB"])
+    monkeypatch.setattr(build, "HOST_SOURCE", files["HOST_SOURCE"])
+    monkeypatch.setattr(build, "host_lib", lambda: files["host"])
+    assert build.is_stale()
+    os.utime(files["host"], (at + 10, at + 10))
+    assert not build.is_stale()
