@@ -509,9 +509,9 @@ static hipError_t launch_backward_typed(const BwdArgs& a, const BwdParams& p, hi
 }
 
 hipError_t launch_backward(const BwdArgs& a, hipStream_t stream) {
-    if (a.ids2 && a.B > kMostRoots) {
-        for (int64_t b = 0; b < a.B; b += kMostRoots)
-            if (hipError_t e = launch_backward(backward_part(a, b, a.B - b < kMostRoots ? a.B - b : kMostRoots), stream)) return e;
+    if (const int64_t most = most_at_a_time(a.ids2 ? 2 : 1); a.B > most) {
+        for (int64_t b = 0; b < a.B; b += most)
+            if (hipError_t e = launch_backward(backward_part(a, b, a.B - b < most ? a.B - b : most), stream)) return e;
         return hipSuccess;
     }
     BwdParams p;

@@ -949,6 +949,14 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
 
 template <bool WEIGHTED>
 static hipError_t launch_forward_any(const FwdArgs& a, const WeightArgs* w, hipStream_t stream) {
+    if (const int64_t most = most_at_a_time(a.hops); a.B > most) {
+        for (int64_t b = 0; b < a.B; b += most) {
+            WeightArgs v = w ? *w : WeightArgs{};
+            const FwdArgs part = forward_part(a, b, a.B - b < most ? a.B - b : most, v);
+            if (hipError_t e = launch_forward_any<WEIGHTED>(part, w ? &v : nullptr, stream)) return e;
+        }
+        return hipSuccess;
+    }
     FwdParams p{};
     p.indptr = a.indptr; p.indices = a.indices; p.x = static_cast<const char*>(a.x);
     p.seeds = a.seeds; p.ids1 = a.ids1; p.ids2 = a.ids2;

@@ -57,9 +57,12 @@ struct BwdArgs {
     const int32_t* root_valid = nullptr;   // 2-hop, chained calls: [B], a negative entry switches root b off
 };
 
-// A launch of 2^32 threads or more is cut off without an error: kernels that take a workgroup of up to
-// 512 threads per root are launched on this many roots at a time.
+// A launch of 2^32 threads or more is cut off without an error.  So the 2-hop kernels, which take a workgroup of up
+// to 512 threads per root, are launched on this many roots at a time, the others, at most a wave per seed, on
+// this many seeds.
 constexpr int64_t kMostRoots = 1 << 22;
+constexpr int64_t kMostSeeds = 1 << 25;
+inline int64_t most_at_a_time(int hops) { return hops == 2 ? kMostRoots : kMostSeeds; }
 
 // Workgroups that share out the leaves of one root in the atomic 2-hop backwards.  A CU issues an atomic
 // instruction every 40 clocks or so, so a batch of fewer roots than CUs would leave most of the chip idle;
@@ -76,7 +79,7 @@ inline unsigned backward_parts(int64_t B, int k2) {
     return parts;
 }
 
-// Roots [b, b + n) of a 2-hop call.
+// Roots [b, b + n) of a call.
 inline BwdArgs backward_part(const BwdArgs& a, int64_t b, int64_t n) {
     const int gb = a.grad_kind == 0 ? 4 : 2;
     BwdArgs c = a;
@@ -84,7 +87,7 @@ inline BwdArgs backward_part(const BwdArgs& a, int64_t b, int64_t n) {
     c.grad_out = static_cast<const char*>(a.grad_out) + b * a.D * gb;
     if (a.grad_h1) c.grad_h1 = static_cast<const char*>(a.grad_h1) + b * a.k1 * a.D * gb;
     c.ids1 = a.ids1 + b * a.k1;
-    c.ids2 = a.ids2 + b * a.k1 * a.k2;
+    if (a.ids2) c.ids2 = a.ids2 + b * a.k1 * a.k2;
     if (a.root_valid) c.root_valid = a.root_valid + b;
     return c;
 }
@@ -96,6 +99,20 @@ struct WeightArgs {
     const float* w1; const float* w2;           // replay / backward inputs
     float* out_w1; float* out_w2;               // sampling forward outputs (nullable)
 };
+
+// Roots [b, b + n) of a call; `w` is cut along with it.
+inline FwdArgs forward_part(const FwdArgs& a, int64_t b, int64_t n, WeightArgs& w) {
+    const int64_t row = a.D * (a.x_kind == 0 ? 4 : 2), slots = b * a.k1, leaves = slots * a.k2;
+    auto at = [](auto*& q, int64_t by) { if (q) q += by; };
+    auto at_row = [row](void*& q, int64_t by) { if (q) q = static_cast<char*>(q) + by * row; };
+    FwdArgs c = a;
+    c.B = n;
+    at(c.seeds, b); at(c.ids1, slots); at(c.ids2, leaves); at(c.out_ids1, slots); at(c.out_ids2, leaves); at(c.out_live, b);
+    at_row(c.out, b); at_row(c.out_h1, slots);
+    if (a.slot_cnt) { c.slot_cnt += slots; c.x = static_cast<const char*>(a.x) + slots * row; }   // x is the slots' own table
+    at(w.w1, slots); at(w.w2, leaves); at(w.out_w1, slots); at(w.out_w2, leaves);
+    return c;
+}
 
 hipError_t launch_forward(const FwdArgs& a, hipStream_t stream);
 hipError_t launch_forward_weighted(const FwdArgs& a, const WeightArgs& w, hipStream_t stream);

@@ -95,11 +95,12 @@ __global__ __launch_bounds__(512) void wbwd2_kernel(const WBwdParams p) {
 }
 
 hipError_t launch_backward_weighted(const BwdArgs& a, const WeightArgs& w, hipStream_t stream) {
-    if (a.ids2 && a.B > kMostRoots) {
-        for (int64_t b = 0; b < a.B; b += kMostRoots) {
+    if (const int64_t most = most_at_a_time(a.ids2 ? 2 : 1); a.B > most) {
+        for (int64_t b = 0; b < a.B; b += most) {
             WeightArgs v = w;
-            v.w1 += b * a.k1; v.w2 += b * a.k1 * a.k2;
-            if (hipError_t e = launch_backward_weighted(backward_part(a, b, a.B - b < kMostRoots ? a.B - b : kMostRoots), v, stream)) return e;
+            v.w1 += b * a.k1;
+            if (a.ids2) v.w2 += b * a.k1 * a.k2;
+            if (hipError_t e = launch_backward_weighted(backward_part(a, b, a.B - b < most ? a.B - b : most), v, stream)) return e;
         }
         return hipSuccess;
     }
