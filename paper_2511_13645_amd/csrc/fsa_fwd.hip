@@ -24,6 +24,8 @@
 #include "fsa_device.hip.h"
 #include "fsa_internal.h"
 
+#include <type_traits>
+
 #ifndef FSA_UNROLL
 #define FSA_UNROLL 4
 #endif
@@ -60,14 +62,24 @@ struct FwdParams {
 #define FSA_STAMP(var) do { } while (0)
 #endif
 
-// Rows in flight per lane in the multi-tile gathers: 40 registers' worth, four at most.  With one row at a
-// time a wave waited out a trip to memory per row, which bounds every launch that does not fill the chip (and
-// 16-byte pieces of 16-bit rows, whose sums leave room for two waves per SIMD, at any size).  Forward, with
+// Rows in flight per lane in the multi-tile gathers.  With one row at a time a wave waited out a trip to memory
+// per row, which bounds every launch that does not fill the chip (and 16-byte pieces of 16-bit rows, whose
+// sums leave room for two waves per SIMD, at any size).  40 registers' worth, four rows at most.  Forward, with
 // IDs, before and after: 2408-byte rows, 25/10, 64 roots 33 -> 21 us, 200 39.5 -> 29, 600 97 -> 78, 1024 109 -> 107;
 // 1200-byte rows, 15/10, 2048 roots 86 -> 68; 1280-byte bf16 rows 154 -> 67; one hop, 8192 x 15 rows of 2560 bytes 67 -> 49.
 // 16 or 24 registers' worth: 25 and 22 us for the 64 roots, the same for the large ones.
-template <int VB, int MT> struct RowsInFlight {
-    static constexpr int fit = 40 / (MT * (VB < 4 ? 4 : VB) / 4);
+//
+// Small pieces of fp32 rows, and short rows of 4-byte pieces of 16-bit ones, gained nothing or lost where the launch fills
+// the chip by itself (1032-byte rows, 25/10, 4096 roots 172 -> 179 us; 1004-byte rows 161 -> 170).  They have 32 registers'
+// worth, which leaves six waves a SIMD and so three 8-wave roots a CU (2408-byte rows, 15/10, 600 roots 56 -> 50 us), and of
+// rows of up to 8 registers a FULL launch has 10 registers' worth or two rows (those 179 -> 175, those 170 -> 164; bf16 rows
+// of 772 bytes, replay, 4096 roots 91 -> 86).  What stays above one row at a time: 257 .. 511 roots of 2400 bytes and more
+// (300: 2408-byte rows 32.9 -> 34.7 us, 3080 41.9 -> 43.3).  A few CUs have a second root there, and the more the others
+// request the longer those CUs go on alone; one row at a time would cost 4 to 12 us at 256 roots and below.
+template <typename XT, int VB, int MT, bool FULL> struct RowsInFlight {
+    static constexpr int regs = MT * (VB < 4 ? 4 : VB) / 4;          // of one row
+    static constexpr bool careful = VB < 16 && (std::is_same<XT, f32_t>::value || (VB == 4 && MT <= 5));
+    static constexpr int fit = careful && FULL && regs <= 8 ? (10 / regs < 2 ? 2 : 10 / regs) : (careful ? 32 : 40) / regs;
     static constexpr int value = fit < 1 ? 1 : fit > 4 ? 4 : fit;
 };
 
@@ -149,7 +161,7 @@ __device__ __forceinline__ void wave_mean_of_rows(const FwdParams& p, int id, fl
         // rows of 2 .. MT tiles of 64 lanes: all tiles of a row are loaded back to back, so a
         // cache line shared by neighbouring tiles is fetched once, R rows in flight (see the 2-hop kernel)
         using Raw = typename C::Raw;
-        constexpr int R = RowsInFlight<VB, MT>::value;
+        constexpr int R = RowsInFlight<XT, VB, MT, false>::value;
         float acc[MT][VE];
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
@@ -283,18 +295,22 @@ constexpr int kRootsPerWorkgroup = FSA_ROOTS_PER_WG;             // with one wav
 #endif
 constexpr int kFwd1PackedPasses = FSA_FWD1_PACKED_PASSES;        // sampling passes of a packed 1-hop wave
 
-// MT > 0 selects the gather for rows wider than one tile of 64 lanes (2 .. MT tiles, MT 3, 5 or
-// kMultiTiles): all tiles of a row are loaded back to back, so the cache line that two
+// MT > 0 selects the gather for rows wider than one tile of 64 lanes (2 .. MT tiles, kMultiTiles at
+// most; see with_tiles): all tiles of a row are loaded back to back, so the cache line that two
 // neighbouring tiles share is fetched once -- walking the whole list once per tile fetched it
 // twice, 20 % more HBM-side traffic than the rows themselves on 2408-byte rows.  MT = 0 is
 // the single-tile gather (and the fallback for rows wider than kMultiTiles tiles).
 constexpr int kMultiTiles = 8;
+// Waves of a launch from which more of them, not more loads each, hide the trips to memory.  15/10, four rows in flight and
+// two: 1032-byte rows (8-byte pieces), 270 roots of 8 waves 20.0 / 18.6 us, 256 roots 15.4 / 16.1; 1004-byte rows (4-byte
+// pieces), 300 roots 17.5 / 17.5, 600 25.1 / 25.1, 4096 112 / 111; 516-byte ones 300 roots 13.7 / 15.2.
+template <int VB> constexpr int64_t kFullWaves = VB == 8 ? 2049 : 4096;
 
 __device__ __forceinline__ uint64_t row_offset_of(const int2& ent) {
     return ((uint64_t)((uint32_t)ent.y & 0x7fffffffu) << 32) | (uint32_t)ent.x;
 }
 
-template <typename XT, int VB, bool REPLAY, int MT, bool WEIGHTED>
+template <typename XT, int VB, bool REPLAY, int MT, bool WEIGHTED, bool FULL>
 __global__ __launch_bounds__(512) void fwd2_kernel(const FwdParams p) {
     using C = Chunk<XT, VB>;
     using Raw = typename C::Raw;
@@ -528,7 +544,7 @@ __global__ __launch_bounds__(512) void fwd2_kernel(const FwdParams p) {
         // rows wider than one tile: sub == 64, one sub-group, the wave walks its whole list
         // R rows are in flight at any time: as soon as the oldest has been added, its registers take the
         // row R entries further down the list.
-        constexpr int R = RowsInFlight<VB, MT>::value;
+        constexpr int R = RowsInFlight<XT, VB, MT, FULL>::value;
         const int tiles = (p.chunks + kWave - 1) >> 6;             // 2 .. MT, checked on the host
         float acc[MT][VE], root[MT][VE];
 #pragma unroll
@@ -845,24 +861,60 @@ static size_t lds_limit() {
     return (size_t)v;
 }
 
+// Calls f with the tile count, a constant, of the multi-tile gather that rows of `tiles` tiles take: 0 for one
+// tile, and for more than kMultiTiles.  Tiles that a row does not have cost registers and instructions, so there
+// are three sizes, and one for every count for 8-byte pieces of fp32 rows, where a spare tile was measured to cost time
+// (25/10, 4096 roots with a spare tile and without: 520-byte rows 114 -> 99 us, 1544 270 -> 246, 2568 297 -> 275; one hop,
+// 8192 x 15 rows of 2568 bytes 63 -> 56; other rows are ahead of a gather of one row at a time with it).
+template <typename XT, int VB, typename F> static void with_tiles(int tiles, F f) {
+    if (tiles <= 1 || tiles > kMultiTiles) return f(std::integral_constant<int, 0>{});
+    if constexpr (VB == 8 && std::is_same<XT, f32_t>::value) {
+        switch (tiles) {
+            case 2: return f(std::integral_constant<int, 2>{});
+            case 4: return f(std::integral_constant<int, 4>{});
+            case 6: return f(std::integral_constant<int, 6>{});
+            case 7: return f(std::integral_constant<int, 7>{});
+            default: break;
+        }
+    }
+    if (tiles <= 3) return f(std::integral_constant<int, 3>{});
+    if (tiles <= 5) return f(std::integral_constant<int, 5>{});
+    return f(std::integral_constant<int, 8>{});
+}
+
+// The 2-hop kernel over `waves` waves in all.
+template <typename XT, int VB, bool WEIGHTED>
+static void launch_fwd2(const FwdParams& p, int tiles, int64_t waves, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    with_tiles<XT, VB>(tiles, [&](auto n) {
+        constexpr int MT = decltype(n)::value;
+        auto go = [&](auto full) {
+            constexpr bool FULL = decltype(full)::value;
+            if (p.indptr) hipLaunchKernelGGL((fwd2_kernel<XT, VB, false, MT, WEIGHTED, FULL>), grid, block, lds, stream, p);
+            else          hipLaunchKernelGGL((fwd2_kernel<XT, VB, true, MT, WEIGHTED, FULL>), grid, block, lds, stream, p);
+        };
+        if constexpr (MT > 0) {
+            if constexpr (RowsInFlight<XT, VB, MT, true>::value != RowsInFlight<XT, VB, MT, false>::value) {
+                if (waves >= kFullWaves<VB>) return go(std::true_type{});
+            }
+        }
+        go(std::false_type{});
+    });
+}
+
 template <typename XT, int VB, bool WEIGHTED>
 static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStream_t stream) {
     constexpr int VE = Chunk<XT, VB>::VE;
     FwdParams p = p_in;
     const bool replay = a.indptr == nullptr;
-    // rows of 2 .. kMultiTiles tiles of 64 lanes take the row-major multi-tile gather; tiles that a row does
-    // not have cost registers and instructions, so there are three sizes of it
     const int tiles = a.geom.tiles;
-    const int mt = (tiles <= 1 || tiles > kMultiTiles) ? 0 : tiles <= 3 ? 3 : tiles <= 5 ? 5 : 8;
     if constexpr (!WEIGHTED) {
         if (a.slot_cnt) {                       // mean over the per-slot rows of a [B,k1,D] table
             const int wpb = 4;
             const dim3 grid((unsigned)((a.B + wpb - 1) / wpb)), block(wpb * kWave);
             const size_t lds = sizeof(int) * kWave * wpb;
-            if (mt == 0)      hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 0>), grid, block, lds, stream, p);
-            else if (mt == 3) hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 3>), grid, block, lds, stream, p);
-            else if (mt == 5) hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 5>), grid, block, lds, stream, p);
-            else              hipLaunchKernelGGL((slot_mean_kernel<XT, VB, 8>), grid, block, lds, stream, p);
+            with_tiles<XT, VB>(tiles, [&](auto n) {
+                hipLaunchKernelGGL((slot_mean_kernel<XT, VB, decltype(n)::value>), grid, block, lds, stream, p);
+            });
             return hipGetLastError();
         }
     }
@@ -889,31 +941,17 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
         p.out_live = nullptr;
         p.waves_per_root = 1;
         const dim3 grid((unsigned)p.B), block(kWave);
-#define FSA_LAUNCH_FWD1P(MT_)                                                                                            \
-        do {                                                                                                             \
-            if (replay) hipLaunchKernelGGL((fwd2_kernel<XT, VB, true, MT_, WEIGHTED>), grid, block, lds, stream, p);     \
-            else        hipLaunchKernelGGL((fwd2_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
-        } while (0)
-        if (mt == 0) FSA_LAUNCH_FWD1P(0);
-        else if (mt == 3) FSA_LAUNCH_FWD1P(3);
-        else if (mt == 5) FSA_LAUNCH_FWD1P(5);
-        else FSA_LAUNCH_FWD1P(8);
-#undef FSA_LAUNCH_FWD1P
+        launch_fwd2<XT, VB, WEIGHTED>(p, tiles, p.B, grid, block, lds, stream);
     } else if (a.hops == 1) {
         const int wpb_t = tune_int("FSA_FWD1_WAVES", 4);
         const int wpb = wpb_t >= 1 && wpb_t <= 4 ? wpb_t : 4;
         const dim3 grid((unsigned)((a.B + wpb - 1) / wpb)), block(wpb * kWave);
         const size_t lds = sizeof(int) * kFwd1StripInts * wpb;
-#define FSA_LAUNCH_FWD1(MT_)                                                                                             \
-        do {                                                                                                             \
-            if (replay) hipLaunchKernelGGL((fwd1_kernel<XT, VB, true, MT_, WEIGHTED>), grid, block, lds, stream, p);     \
-            else        hipLaunchKernelGGL((fwd1_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
-        } while (0)
-        if (mt == 0) FSA_LAUNCH_FWD1(0);
-        else if (mt == 3) FSA_LAUNCH_FWD1(3);
-        else if (mt == 5) FSA_LAUNCH_FWD1(5);
-        else FSA_LAUNCH_FWD1(8);
-#undef FSA_LAUNCH_FWD1
+        with_tiles<XT, VB>(tiles, [&](auto n) {
+            constexpr int MT = decltype(n)::value;
+            if (replay) hipLaunchKernelGGL((fwd1_kernel<XT, VB, true, MT, WEIGHTED>), grid, block, lds, stream, p);
+            else        hipLaunchKernelGGL((fwd1_kernel<XT, VB, false, MT, WEIGHTED>), grid, block, lds, stream, p);
+        });
     } else {
         // waves per root: as few as the batch allows, but enough for the strips to fit in LDS
         int nw = fwd2_waves(a.B, a.k1, a.geom);
@@ -933,16 +971,7 @@ static hipError_t launch_typed(const FwdArgs& a, const FwdParams& p_in, hipStrea
         if (lds > limit) return hipErrorInvalidValue;              // fanouts too large for this device's LDS
         const dim3 grid((unsigned)((a.B + rpw - 1) / rpw)), block(nw * rpw * kWave);
         p.waves_per_root = nw;
-#define FSA_LAUNCH_FWD2(MT_)                                                                                             \
-        do {                                                                                                             \
-            if (replay) hipLaunchKernelGGL((fwd2_kernel<XT, VB, true, MT_, WEIGHTED>), grid, block, lds, stream, p);     \
-            else        hipLaunchKernelGGL((fwd2_kernel<XT, VB, false, MT_, WEIGHTED>), grid, block, lds, stream, p);    \
-        } while (0)
-        if (mt == 0) FSA_LAUNCH_FWD2(0);
-        else if (mt == 3) FSA_LAUNCH_FWD2(3);
-        else if (mt == 5) FSA_LAUNCH_FWD2(5);
-        else FSA_LAUNCH_FWD2(8);
-#undef FSA_LAUNCH_FWD2
+        launch_fwd2<XT, VB, WEIGHTED>(p, tiles, a.B * nw, grid, block, lds, stream);
     }
     return hipGetLastError();
 }

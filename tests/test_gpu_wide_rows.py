@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D, bf16", [(640, False), (768, False), (772, False), (1280, False), (1284, False),     # 16-byte pieces
-                                     (386, False), (642, False), (770, False),                                   # 8
+                                     (130, False), (386, False), (514, False), (642, False), (770, False), (962, False),  # 8
                                      (129, False), (193, False), (321, False), (511, False),                     # 4
                                      (1544, True), (772, True), (386, True), (129, True), (385, True)])          # 16, 8, 4, 2, 2
 def test_tiles_and_pieces(fsa, orc, D, bf16):  # noqa: F811
@@ -27,10 +27,11 @@ def test_tiles_and_pieces(fsa, orc, D, bf16):  # noqa: F811
     w = rng.random(indices.shape[0]).astype(np.float32) + 0.25
     up = lambda a: torch.from_numpy(a).to("cuda:0")
     hx, is_bf16 = host_x(x)
-    ref = orc.sample_wmean_fwd(indptr, indices, w, hx, seeds, [5, 3], 3, bf16=is_bf16)
-    got = fsa.fsa_sample_wmean_fwd(up(indptr), up(indices), up(w), x.to("cuda:0"), up(seeds), [5, 3], 3)
-    torch.cuda.synchronize()
-    a_out, a_h1 = forward_scales(x.to("cuda:0"), got[2], got[3])
-    # weights from 0.25 to 1.25: a weighted mean of magnitudes is within five plain ones
-    assert_close(to_f64(got[0]), ref[0], 5 * a_out, TOL[x.dtype], "weighted out")
-    assert_close(to_f64(got[1]), ref[1], 5 * a_h1, TOL[x.dtype], "weighted out_h1")
+    for many, fan in ((seeds, [5, 3]), (np.resize(seeds, 4200), [3, 2])):
+        ref = orc.sample_wmean_fwd(indptr, indices, w, hx, many, fan, 3, bf16=is_bf16)
+        got = fsa.fsa_sample_wmean_fwd(up(indptr), up(indices), up(w), x.to("cuda:0"), up(many), fan, 3)
+        torch.cuda.synchronize()
+        a_out, a_h1 = forward_scales(x.to("cuda:0"), got[2], got[3])
+        # weights from 0.25 to 1.25: a weighted mean of magnitudes is within five plain ones
+        assert_close(to_f64(got[0]), ref[0], 5 * a_out, TOL[x.dtype], "weighted out")
+        assert_close(to_f64(got[1]), ref[1], 5 * a_h1, TOL[x.dtype], "weighted out_h1")
