@@ -47,6 +47,7 @@ struct RowLanes {
     int base;                  // unit of its 64-byte segment at which grad_x starts, or -1: lanes start where rows start
 };
 constexpr int kSegment = 16;   // units of a 64-byte segment
+inline int rows_an_instruction(const RowLanes& l) { return kWave >> l.width_shift; }
 
 inline RowLanes row_lanes(const void* grad_x, int64_t units) {
     const int at = (int)((reinterpret_cast<uintptr_t>(grad_x) >> 2) & (kSegment - 1));

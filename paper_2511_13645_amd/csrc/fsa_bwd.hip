@@ -503,7 +503,7 @@ static hipError_t launch_backward_typed(const BwdArgs& a, const BwdParams& p, hi
         const size_t lds = sizeof(int) * ((size_t)nw * (2 * nq_max * a.k2 + 2 * nq_max) + nw);
         BwdParams q = p;
         q.lanes = row_lanes(a.grad_x, a.D / Epl<GT, XG>::value);
-        hipLaunchKernelGGL((bwd2_kernel<GT, XG>), dim3((unsigned)a.B, backward_parts(a.B, a.k2)), dim3(nw * kWave), lds, stream, q);
+        hipLaunchKernelGGL((bwd2_kernel<GT, XG>), dim3((unsigned)a.B, backward_parts(a.B, a.k2, rows_an_instruction(q.lanes))), dim3(nw * kWave), lds, stream, q);
     }
     return hipGetLastError();
 }

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fsa_layout.h"
+
 #ifdef FSA_TUNING
 #include <cstdlib>
 #endif
@@ -64,19 +66,10 @@ constexpr int64_t kMostRoots = 1 << 22;
 constexpr int64_t kMostSeeds = 1 << 25;
 inline int64_t most_at_a_time(int hops) { return hops == 2 ? kMostRoots : kMostSeeds; }
 
-// Workgroups that share out the leaves of one root in the atomic 2-hop backwards.  A CU issues an atomic
-// instruction every 40 clocks or so, so a batch of fewer roots than CUs would leave most of the chip idle;
-// each workgroup goes through the root's IDs again, so every part keeps two leaves of a slot at least.
-// Backward alone, fanouts 15/10, 1 against 4 parts: 8 roots of 100 floats 10.3 -> 6.9 us, 64 roots 10.2 -> 7.9, 1 root
-// of 256 floats 11.4 -> 8.4, 64 roots of 602 floats 36 -> 24; 128 roots of 100 floats 11.9 -> 11.1 with 2; 256 and more
-// roots gain nothing (256 of 100 floats 17.6 / 17.7 / 17.5 with 1 / 2 / 4) and lose with many (300 k leaves of 64 floats
-// 67 -> 70 with 4).
-inline unsigned backward_parts(int64_t B, int k2) {
+// Workgroups per root of the atomic 2-hop backwards (fsa_layout.h), whose atomic instructions take `each` rows.
+inline unsigned backward_parts(int64_t B, int k2, int each) {
     const int forced = tune_int("FSA_BWD2_PARTS", 0);
-    if (forced > 0) return (unsigned)forced;
-    unsigned parts = 1;
-    while (B * parts < 256 && (int)parts * 4 <= k2) parts *= 2;
-    return parts;
+    return (unsigned)(forced > 0 ? forced : parts_of_root(B, k2, each));
 }
 
 // Roots [b, b + n) of a call.

@@ -1,5 +1,5 @@
-// Index arithmetic of the forward kernels' LDS strips, shared by the kernels and the host
-// launch code, and written without HIP types so that a plain C++ compiler can build it: the
+// Index arithmetic of the forward kernels' LDS strips and of the 2-hop backward's parts, shared by the kernels and
+// the host launch code, and written without HIP types so that a plain C++ compiler can build it: the
 // CPU tests sweep every fanout / waves-per-root combination through these functions and
 // check that every offset a kernel can form stays inside the strip the host sizes.
 #pragma once
@@ -60,6 +60,22 @@ FSA_HD inline long long fwd2_lds_bytes(int k1, int k2, int nw, int roots_per_wg,
     const Fwd2Layout L = fwd2_layout((k1 + nw - 1) / nw, k2, weighted);
     const long long strips = (long long)nw * roots_per_wg;
     return 4 * (strips * L.per_wave + round_up4((int)strips)) + 4LL * nw * sub * ve;
+}
+
+// Workgroups that share out the leaves of one root in the atomic 2-hop backwards; an atomic instruction of theirs takes
+// `each` rows, so of P parts part p starts at leaf p * each of a slot.  A CU issues an atomic instruction every 40
+// clocks or so, so a batch of fewer roots than CUs would leave most of the chip idle; each workgroup goes through the
+// root's IDs again, so every part has an instruction of its own, and two leaves of a full slot at least.  That makes up to
+// 4 parts for k2 = 10, 8 for 25, 32 for 64.  Backward alone, 1 / 2 / 4 / 8 / 16 / 32 parts: fanouts 15/10, 8 roots of 100 floats
+// 10.5 / 8.2 / 7.2 / 6.8 / 6.4 / 6.5 us, 64 roots 10.5 / 8.9 / 8.3 / 8.4 / 10.0 / 16, 128 roots of 602 floats 49 / 44 / 44 / 46 / 58 / 78;
+// 15/25, 8 roots of 100 floats 18.2 / 12.6 / 9.8 / 8.4 / 7.7 / 7.4; 10/64, one root of 602 floats 163 / 90 / 55 / 37 / 28 / 23, 64 roots
+// 169 / 118 / 101 / 96 / 94 / 102.  Rows of 16 floats take four an instruction and gain nothing from more parts at 15/10 (all
+// 5.8 .. 6.0 at 8 roots).  256 and more roots gain nothing (256 of 100 floats 17.6 / 17.7 / 17.5 with 1 / 2 / 4) and lose with
+// many (300 k leaves of 64 floats 67 -> 70 with 4).
+FSA_HD inline int parts_of_root(long long B, int k2, int each) {
+    int parts = 1;
+    while (B * parts < 256 && parts * 2 * (each > 2 ? each : 2) <= k2) parts *= 2;
+    return parts;
 }
 
 // 1-hop forward: per wave 64 staged IDs (the draws of the duplicate test use the same ints

@@ -118,7 +118,7 @@ hipError_t launch_backward_weighted(const BwdArgs& a, const WeightArgs& w, hipSt
         const int nw = a.k1 < 8 ? a.k1 : 8;
         const int nq_max = (a.k1 + nw - 1) / nw;
         const size_t lds = sizeof(int) * ((size_t)nw * (2 * nq_max * a.k2 + 3 * nq_max) + nw);
-        hipLaunchKernelGGL(wbwd2_kernel, dim3((unsigned)a.B, backward_parts(a.B, a.k2)), dim3(nw * kWave), lds, stream, p);
+        hipLaunchKernelGGL(wbwd2_kernel, dim3((unsigned)a.B, backward_parts(a.B, a.k2, rows_an_instruction(p.lanes))), dim3(nw * kWave), lds, stream, p);
     }
     return hipGetLastError();
 }

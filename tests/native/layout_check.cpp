@@ -122,6 +122,18 @@ int main() {
         const int last_m0 = ((k1 - 1) / 4) * 4;
         if (last_m0 + 3 >= fsa::kDrawStripInts || last_m0 + 3 >= 72) { std::printf("FAILED hop-0 draw strip k1=%d\n", k1); return 1; }
     }
+    // parts of a root in the 2-hop backward: each starts inside a full slot and has two leaves of it at least
+    for (int each = 1; each <= 4; each *= 2)
+    for (int k2 = 1; k2 <= 64; ++k2)
+    for (long long B = 1; B <= 300; ++B) {
+        const int parts = fsa::parts_of_root(B, k2, each);
+        for (int part = 0; part < parts && parts > 1; ++part) {
+            int leaves = 0;
+            for (int e = 0; e < k2; ++e) leaves += e / each % parts == part;
+            if (leaves < 2) { std::printf("FAILED part %d of %d with %d leaves of %d, %d rows an instruction\n", part, parts, leaves, k2, each); return 1; }
+        }
+        if (parts < 1 || (B >= 256 && parts != 1)) { std::printf("FAILED %d parts of a root, B=%lld\n", parts, B); return 1; }
+    }
     std::printf("ok %lld cases\n", cases);
     return 0;
 }
