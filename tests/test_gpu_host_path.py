@@ -109,3 +109,37 @@ def test_what_is_not_plain_is_left_to_the_python_path(fsa, data, monkeypatch):
     with pytest.raises(fsa.FsaError):              # refused by the library: the native path's status, the same exception
         fsa.fsa_mean_bwd_lp(torch.zeros((77, 35), device="cuda:0"), want[2], want[3], grad_x=odd)
     assert count.took.pop() is True
+
+
+def test_replay_and_backward_refuse_what_the_python_path_refuses(fsa, data, monkeypatch):
+    """One argument wrong at a time: the native path leaves the call alone, and the caller sees the error that the
+    binding raises without it."""
+    x = torch.randn((data["n"], 36), device="cuda:0")
+    _, _, i1, i2, w1, w2 = fsa.fsa_sample_wmean_fwd(data["indptr"], data["indices"], data["w"], x, data["seeds"], [6, 3], 5)
+    B = len(data["seeds"])
+    count = _Counting(fsa._host)
+
+    def refused(call, **good):
+        wrong = {"dtype": lambda t: t.double(), "host": lambda t: t.cpu(), "strides": lambda t: t.transpose(0, -1),
+                 "batch": lambda t: t[1:].contiguous(), "width": lambda t: t[..., 1:].contiguous(), "dims": lambda t: t[None]}
+        for name, t in good.items():
+            for how, bad in wrong.items():
+                if how == "width" and name in ("x", "ids2") and call == fsa.fsa_mean_replay_fwd or (name, how) == ("ids2", "width") and "w2" not in good:
+                    continue                       # another width, other fanouts: a call of its own
+                if name in ("x", "grad_x") and how == "batch":
+                    continue                       # a smaller table is a table
+                args = dict(good, **{name: bad(t)})
+                seen = []
+                for host in (count, None):
+                    monkeypatch.setattr(fsa, "_host", host)
+                    with pytest.raises(Exception) as e:
+                        call(**args)
+                    seen.append((e.type, str(e.value)))
+                assert count.took.pop() is False and seen[0] == seen[1], (call.__name__, name, how)
+
+    refused(fsa.fsa_mean_replay_fwd, x=x, ids1=i1, ids2=i2)
+    g, gh, gx = torch.zeros((B, 36), device="cuda:0"), torch.zeros((B, 6, 36), device="cuda:0"), torch.zeros_like(x)
+    for call in (fsa.fsa_mean_bwd, fsa.fsa_mean_bwd_ws, fsa.fsa_mean_bwd_lp):
+        refused(call, grad_out=g, ids1=i1, ids2=i2, grad_h1=gh, grad_x=gx)
+    refused(fsa.fsa_wmean_bwd, grad_out=g, ids1=i1, w1=w1, ids2=i2, w2=w2, grad_h1=gh, grad_x=gx)
+    assert not count.took
