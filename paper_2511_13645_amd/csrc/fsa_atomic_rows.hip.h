@@ -71,9 +71,11 @@ template <int EPL> __device__ __forceinline__ void arrived(float (&g)[EPL]) {
 // Called by a whole wave.
 //
 // What bounds it: the memory side takes an atomic instruction apart into 64-byte segments and serves
-// 18.5 G of them a second, whether 1 or 16 lanes fall into one, in whatever order, and wherever the rows
-// lie (150,000 rows of 128 floats: 61 us with all lanes, with every second and with every fourth; the same
-// from 128 CUs on as on 256).  So a row that starts inside a segment is not cut every 64 elements, where
+// 20.8 G of them a second, 19 to 20 G in tables of a gigabyte and more, whether 1 or 16 lanes fall into one and in
+// whatever order (150,000 rows of 128 floats: 61 us with all lanes, with every second and with every fourth; the same
+// from 128 CUs on as on 256).  A launch and its IDs add 6 us: 150,000 / 1,200,000 distinct rows of 64 floats 34 / 235 us, of
+// 100 57 / 411, of 128 64 / 468, of 256 123 / 934, of 128 bf16 elements 34 / 236.  So a row that starts inside a segment is
+// not cut every 64 elements, where
 // both pieces touch the segment of the cut, but at the last segment's start before that: the lanes behind
 // the cut go along with the next instruction (150,000 rows of 100 floats 59.5 -> 53.8 us, of 150 91 -> 78;
 // 37,500 of 602 87 -> 75).  Rows of two segments or one share an instruction, because an instruction costs

@@ -280,7 +280,7 @@ __global__ __launch_bounds__(1024) void bwd1_kernel(const BwdParams p, int spw, 
             } else {
                 load_grad<GT, EPL>(p.grad_out, b * p.D + d, g);
             }
-            arrived(g);
+            arrived(g);                                              // (and after these, for the atomics on rows)
             for (int e = kWave - n_shared; e < kWave; ++e) {         // (narrow rows: for the first group of lanes)
                 if (lane >> l.width_shift) break;
                 float* at = hot + ~rows[e] * (int)p.D + d;

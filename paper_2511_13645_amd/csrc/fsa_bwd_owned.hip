@@ -440,8 +440,9 @@ static OwnedLayout owned_layout(int64_t slots, int64_t leaves) {
 // 82 -> 68 us at 77 k; three hops, 400 bytes at 768 k, 409 -> 320 us; bf16 rows of 512 bytes 309 -> 239 us
 // and of 1024 bytes 594 -> 382 us at 614 k; 1024-byte fp32 rows at 38 k (39 MB) 38 -> 30 us alone.
 // Since the atomics are cut at the rows' 64-byte segments, products 78.3 / 80.2 us a pass with atomics / with this
-// route, weighted 81.4 / 82.9, three hops 366 / 302: the lines stay, because the calls above them have
-// reproducible results.
+// route, weighted 81.4 / 82.9, three hops 366 / 302, so calls just above the lines pay up to 2 %.  The lines stay because
+// callers size their workspace by them and rely on what it buys: sums in a fixed order in every row that is named
+// up to 16 times (include/fsa.h; rows named more often, as hubs are, go in by atomics here as well).
 // The line counts leaf slots, because the call knows no more; on graphs whose slots are mostly empty or whose
 // rows are mostly shared the two are equal (512-byte rows, backward alone: 169 k nodes, 256 k slots of which 73 k
 // hold 31 k distinct rows, 44 -> 43 us; hubs, 307 k slots of which 36 k hold 5.7 k distinct rows, 79 -> 83 us).
