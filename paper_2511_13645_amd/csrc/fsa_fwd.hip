@@ -71,15 +71,17 @@ struct FwdParams {
 //
 // Small pieces of fp32 rows, and short rows of 4-byte pieces of 16-bit ones, gained nothing or lost where the launch fills
 // the chip by itself (1032-byte rows, 25/10, 4096 roots 172 -> 179 us; 1004-byte rows 161 -> 170).  They have 32 registers'
-// worth, which leaves six waves a SIMD and so three 8-wave roots a CU (2408-byte rows, 15/10, 600 roots 56 -> 50 us), and of
-// rows of up to 8 registers a FULL launch has 10 registers' worth or two rows (those 179 -> 175, those 170 -> 164; bf16 rows
-// of 772 bytes, replay, 4096 roots 91 -> 86).  What stays above one row at a time: 257 .. 511 roots of 2400 bytes and more
+// worth, which leaves six waves a SIMD and so three 8-wave roots a CU (2408-byte rows, 15/10, 600 roots 56 -> 50 us); where
+// roots have fewer waves that makes no difference, and rows of more than 8 registers keep 40 (1024 roots 69.7 / 69.4 us with
+// 32 / 40, 25/10 4096 roots 392.6 / 390.7).  Of rows of up to 8 registers a FULL launch has 10 registers' worth or two rows
+// (those 179 -> 175, those 170 -> 164; bf16 rows of 772 bytes, replay, 4096 roots 91 -> 86).  What stays above one row at a time: 257 .. 511 roots of 2400 bytes and more
 // (300: 2408-byte rows 32.9 -> 34.7 us, 3080 41.9 -> 43.3).  A few CUs have a second root there, and the more the others
 // request the longer those CUs go on alone; one row at a time would cost 4 to 12 us at 256 roots and below.
 template <typename XT, int VB, int MT, bool FULL> struct RowsInFlight {
     static constexpr int regs = MT * (VB < 4 ? 4 : VB) / 4;          // of one row
     static constexpr bool careful = VB < 16 && (std::is_same<XT, f32_t>::value || (VB == 4 && MT <= 5));
-    static constexpr int fit = careful && FULL && regs <= 8 ? (10 / regs < 2 ? 2 : 10 / regs) : (careful ? 32 : 40) / regs;
+    static constexpr bool brief = careful && regs <= 8;
+    static constexpr int fit = brief && FULL ? (10 / regs < 2 ? 2 : 10 / regs) : (careful && !FULL ? 32 : 40) / regs;
     static constexpr int value = fit < 1 ? 1 : fit > 4 ? 4 : fit;
 };
 
@@ -894,7 +896,7 @@ static void launch_fwd2(const FwdParams& p, int tiles, int64_t waves, dim3 grid,
         };
         if constexpr (MT > 0) {
             if constexpr (RowsInFlight<XT, VB, MT, true>::value != RowsInFlight<XT, VB, MT, false>::value) {
-                if (waves >= kFullWaves<VB>) return go(std::true_type{});
+                if (RowsInFlight<XT, VB, MT, true>::brief ? waves >= kFullWaves<VB> : p.waves_per_root < 8) return go(std::true_type{});
             }
         }
         go(std::false_type{});
