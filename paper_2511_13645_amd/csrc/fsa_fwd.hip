@@ -74,8 +74,9 @@ struct FwdParams {
 // worth, which leaves six waves a SIMD and so three 8-wave roots a CU (2408-byte rows, 15/10, 600 roots 56 -> 50 us); where
 // roots have fewer waves that makes no difference, and rows of more than 8 registers keep 40 (1024 roots 69.7 / 69.4 us with
 // 32 / 40, 25/10 4096 roots 392.6 / 390.7).  Of rows of up to 8 registers a FULL launch has 10 registers' worth or two rows
-// (those 179 -> 175, those 170 -> 164; bf16 rows of 772 bytes, replay, 4096 roots 91 -> 86).  What stays above one row at a time: 257 .. 511 roots of 2400 bytes and more
-// (300: 2408-byte rows 32.9 -> 34.7 us, 3080 41.9 -> 43.3).  A few CUs have a second root there, and the more the others
+// (those 179 -> 175, those 170 -> 164; bf16 rows of 772 bytes, replay, 4096 roots 91 -> 86).
+// What stays above one row at a time: 257 .. 511 roots of 1500 bytes and more at 15/10 (300: 1544-byte rows 25.3 -> 26.0 us,
+// 2408 33.0 -> 34.6, 2568 36.1 -> 37.8, 3080 41.9 -> 43.3).  A few CUs have a second root there, and the more the others
 // request the longer those CUs go on alone; one row at a time would cost 4 to 12 us at 256 roots and below.
 template <typename XT, int VB, int MT, bool FULL> struct RowsInFlight {
     static constexpr int regs = MT * (VB < 4 ? 4 : VB) / 4;          // of one row
