@@ -17,3 +17,11 @@ def orc():
     import oracle
     oracle.lib()
     return oracle
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _no_garbage_of_earlier_modules():
+    """Tensors that a failed expectation or an autograd graph left in a reference cycle go before the next module
+    starts: a test that watches the allocator's counters must not see the collector free them in between."""
+    import gc
+    gc.collect()
