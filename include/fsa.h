@@ -204,6 +204,25 @@ int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype
                        void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
+ * The backward as a gradient of its own: every row of grad_x [num_nodes,D] is written once, whatever it
+ * held -- the gradient the leaves give it, or zeros -- so nothing needs clearing first.  No other work may
+ * write grad_x or the workspace while the call runs.  dtype: of grad_out, grad_h1 and grad_x alike; sums are
+ * formed in fp32, in an order that varies; a 16-bit row is rounded once, or, where it and the rows beside it are
+ * named by more than 256 leaves, once per 256 of these.
+ * Requires a workspace (contents irrelevant on entry, overwritten) of fsa_mean_bwd_dense_workspace_bytes
+ * (k2 = 0 for one hop), 256-byte aligned, and grad_x 16-byte aligned.  That size is 0 where the call is not
+ * available (more than 1024 elements to a row, for one) and answers FSA_ERR_ARG; ..._pays is 1 where it is expected to
+ * be faster than clearing grad_x and fsa_mean_bwd or fsa_mean_bwd_lp: large batches on tables not much larger.
+ */
+int64_t fsa_mean_bwd_dense_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int64_t num_nodes);
+int fsa_mean_bwd_dense_pays(int64_t B, int32_t k1, int32_t k2, int64_t D, int dtype, int64_t num_nodes);
+int fsa_mean_bwd_dense(const void* grad_out, const void* grad_h1, int dtype,
+                       const int32_t* ids1, const int32_t* ids2,
+                       int64_t B, int32_t k1, int32_t k2, int64_t D,
+                       void* grad_x, int64_t num_nodes,
+                       void* workspace, int64_t workspace_bytes, void* stream);
+
+/*
  * Layer-wise two-hop forward: fsa_sample_mean_fwd for fanouts (k1,k2) that ALSO emits the plain
  * hop-1 mean  out_m1[b] = mean of X over the sampled hop-1 nodes U1(seed)  -- what a layer-wise
  * GraphSAGE needs next to the nested mean, and the other way to read "the seed's mean" in a

@@ -2,12 +2,12 @@
 ``save_indices`` records the sampled IDs in forward and replays them in backward, so that
 gradients reach the same sampled neighborhoods).
 
-Only glue: forward calls ``fsa_sample_mean_fwd``, backward calls ``fsa_mean_bwd`` (fp32) or
-``fsa_mean_bwd_lp`` (16-bit tables or gradients) on the IDs saved by that forward.  IDs are
+Only glue: forward calls ``fsa_sample_mean_fwd``, backward calls ``fsa_mean_bwd_dense`` where that pays, else
+``fsa_mean_bwd`` (fp32) or ``fsa_mean_bwd_lp`` (16-bit tables or gradients), on the IDs saved by that forward.  IDs are
 emitted only when the feature table needs a gradient (or the caller asks for them), as in the
 paper's optional flag.
 
-A bf16 / fp16 table gets its gradient in its own type, added with packed 16-bit atomics, or --
+A bf16 / fp16 table gets its gradient in its own type, or --
 when the caller passes ``master_grad``, an fp32 [N,D] tensor -- the backward accumulates into
 that master gradient instead and leaves ``x.grad`` unset.  A master gradient is added to with
 atomics, so backward passes on several streams may share one.  ``workspace`` (any contiguous GPU
@@ -60,7 +60,17 @@ class _FusedSampleMean(torch.autograd.Function):
         if ctx.master_grad is not None:
             binding.fsa_mean_bwd_lp(g_out, ids1, ids2, gh, grad_x=ctx.master_grad)
             return (None,) * 10
-        if ctx.x_dtype == torch.float32:
+        B, k1 = ids1.shape
+        k2 = ids2.shape[2] if ids2 is not None else 0
+        n, d = ctx.shape
+        # x.grad is a tensor of its own: written row by row where that is faster than clearing it and adding, unless
+        # a caller's workspace buys sums whose order does not vary; 16-bit rows of odd length are summed in fp32 to the end
+        owned = (ctx.workspace is not None and ctx.x_dtype == torch.float32 and k2 > 0 and
+                 binding.fsa_mean_bwd_workspace_bytes(B, k1, k2, d) > 0)
+        odd = d % 2 != 0 and ctx.x_dtype != torch.float32
+        if not owned and not odd and binding.fsa_mean_bwd_dense_pays(B, k1, k2, d, ctx.x_dtype, n):
+            grad_x = binding.grad_dense(g_out.to(ctx.x_dtype), ids1, ids2, None if gh is None else gh.to(ctx.x_dtype), n)
+        elif ctx.x_dtype == torch.float32:
             grad_x = torch.zeros(ctx.shape, dtype=torch.float32, device=g_out.device)
             binding.fsa_mean_bwd_ws(g_out.float(), ids1, ids2, None if gh is None else gh.float(), grad_x=grad_x,
                                     workspace=ctx.workspace)

@@ -37,12 +37,13 @@ EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_me
            "fsa_sample_mean_layerwise_fwd", "fsa_sample_mean3_fwd", "fsa_mean3_replay_fwd", "fsa_mean3_bwd",
            "fsa_mean3_bwd_noalloc", "fsa_mean_bwd_ws", "fsa_mean_bwd_workspace_bytes",
            "fsa_bwd_workspace_bytes", "fsa_mean_bwd_lp_ws", "fsa_mean3_bwd_ws", "fsa_wmean_bwd_ws",
+           "fsa_mean_bwd_dense", "fsa_mean_bwd_dense_workspace_bytes", "fsa_mean_bwd_dense_pays",
            "fsa_sample_wmean_fwd", "fsa_wmean_replay_fwd", "fsa_wmean_bwd")
 
 _lib: Optional[ctypes.CDLL] = None
 _host = None                                    # the module _fsa_host, once the library is loaded; None without it
 _HOST_ENTRIES = ("fsa_sample_mean_fwd", "fsa_sample_wmean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_ws",
-                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws")              # entry points that _fsa_host calls
+                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws", "fsa_mean_bwd_dense", "fsa_mean_bwd_dense_workspace_bytes")              # entry points that _fsa_host calls
 _PLAIN, _WORKSPACE, _LOW_PRECISION, _WEIGHTED = range(4)                # backward entry points, as _fsa_host.bwd counts them
 
 
@@ -100,6 +101,12 @@ def lib() -> ctypes.CDLL:
         L.fsa_wmean_bwd_ws.restype = ci
         L.fsa_mean3_bwd_ws.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, i64, vp, i64, vp, vp, i64, vp]
         L.fsa_mean3_bwd_ws.restype = ci
+        L.fsa_mean_bwd_dense_workspace_bytes.argtypes = [i64, i32, i32, i64, i64]
+        L.fsa_mean_bwd_dense_workspace_bytes.restype = i64
+        L.fsa_mean_bwd_dense_pays.argtypes = [i64, i32, i32, i64, ci, i64]
+        L.fsa_mean_bwd_dense_pays.restype = ci
+        L.fsa_mean_bwd_dense.argtypes = [vp, vp, ci, vp, vp, i64, i32, i32, i64, vp, i64, vp, i64, vp]
+        L.fsa_mean_bwd_dense.restype = ci
         L.fsa_status_string.argtypes = [ci]
         L.fsa_status_string.restype = ctypes.c_char_p
         _lib, _host = L, _load_host(L)
@@ -357,6 +364,56 @@ def fsa_mean_bwd_ws(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[t
     if rc != FSA_OK:
         raise FsaError(rc, "fsa_mean_bwd_ws")
     return grad_x
+
+
+def fsa_mean_bwd_dense_workspace_bytes(B: int, k1: int, k2: int, D: int, num_nodes: int) -> int:
+    """Workspace bytes of fsa_mean_bwd_dense (k2 = 0: one hop); 0 where it is not available."""
+    return int(lib().fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, num_nodes))
+
+
+def fsa_mean_bwd_dense_pays(B: int, k1: int, k2: int, D: int, dtype: torch.dtype, num_nodes: int) -> bool:
+    """Whether fsa_mean_bwd_dense is expected to be faster than clearing a gradient and adding to it."""
+    return bool(lib().fsa_mean_bwd_dense_pays(B, k1, k2, D, _FLOAT_TYPE[dtype], num_nodes))
+
+
+def fsa_mean_bwd_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,
+                       grad_h1: Optional[torch.Tensor] = None, *, grad_x: torch.Tensor, workspace: torch.Tensor,
+                       stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+    """The backward as a gradient of its own: writes every row of grad_x [N,D] once, whatever it held (nothing to
+    clear).  One type for grad_out, grad_h1 and grad_x.  `workspace`, sized by fsa_mean_bwd_dense_workspace_bytes:
+    no other work may write grad_x or the workspace while the call runs."""
+    _need(grad_out, "grad_out"); _need(ids1, "ids1", torch.int32); _need(grad_x, "grad_x", grad_out.dtype)
+    B, k1 = ids1.shape
+    N, D = grad_x.shape
+    _shape(grad_out, "grad_out", (B, D))
+    k2 = 0
+    if ids2 is not None:
+        _need(ids2, "ids2", torch.int32)
+        if ids2.dim() != 3 or tuple(ids2.shape[:2]) != (B, k1):
+            raise ValueError("ids2 must be [B,k1,k2]")
+        k2 = ids2.shape[2]
+    if grad_h1 is not None:
+        _need(grad_h1, "grad_h1", grad_out.dtype)
+        _shape(grad_h1, "grad_h1", (B, k1, D))
+    _same_device(grad_x, (grad_out, "grad_out"), (grad_h1, "grad_h1"), (ids1, "ids1"), (ids2, "ids2"))
+    ws, ws_bytes = _room(workspace, grad_x)
+    rc = lib().fsa_mean_bwd_dense(_ptr(grad_out), _ptr(grad_h1), _x_dtype(grad_out), _ptr(ids1), _ptr(ids2), B, k1, k2, D,
+                                  _ptr(grad_x), N, ws, ws_bytes, _stream(stream, grad_x))
+    if rc != FSA_OK:
+        raise FsaError(rc, "fsa_mean_bwd_dense")
+    return grad_x
+
+
+def grad_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor], grad_h1: Optional[torch.Tensor],
+               num_nodes: int) -> torch.Tensor:
+    """fsa_mean_bwd_dense into a gradient [num_nodes,D] allocated here, with a workspace that lasts for the call."""
+    if _host is not None:
+        grad_x = _host.grad_dense(grad_out, ids1, ids2, grad_h1, num_nodes)
+        if _taken(grad_x, "fsa_mean_bwd_dense"):
+            return grad_x
+    need = fsa_mean_bwd_dense_workspace_bytes(ids1.shape[0], ids1.shape[1], 0 if ids2 is None else ids2.shape[2], grad_out.shape[1], num_nodes)
+    return fsa_mean_bwd_dense(grad_out, ids1, ids2, grad_h1, grad_x=grad_out.new_empty((num_nodes, grad_out.shape[1])),
+                              workspace=grad_out.new_empty(need, dtype=torch.uint8))
 
 
 def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,

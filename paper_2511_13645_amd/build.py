@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfsa_hip.so")
 ABI_HEADER = os.path.normpath(os.path.join(HERE, "..", "include", "fsa.h"))
-SOURCES = ["fsa_api.hip", "fsa_fwd.hip", "fsa_bwd.hip", "fsa_bwd_sorted.hip", "fsa_bwd_owned.hip", "fsa_wbwd.hip"]
+SOURCES = ["fsa_api.hip", "fsa_fwd.hip", "fsa_bwd.hip", "fsa_bwd_sorted.hip", "fsa_bwd_owned.hip", "fsa_bwd_dense.hip", "fsa_wbwd.hip"]
 HEADERS = ["fsa_device.hip.h", "fsa_atomic_rows.hip.h", "fsa_internal.h", "fsa_layout.h", ABI_HEADER]
 
 HIPCC_FLAGS = [

@@ -258,6 +258,41 @@ int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype
     return status_of(backward_any(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream)));
 }
 
+int64_t fsa_mean_bwd_dense_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int64_t num_nodes) {
+    if (B <= 0 || D <= 0 || num_nodes <= 0 || !fanout_ok(k1) || k2 < 0 || (k2 > 0 && !fanout_ok(k2))) return 0;
+    return (int64_t)fsa::dense_workspace_bytes(B, k1, k2, D, num_nodes);
+}
+
+int fsa_mean_bwd_dense_pays(int64_t B, int32_t k1, int32_t k2, int64_t D, int dtype, int64_t num_nodes) {
+    if (fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, num_nodes) == 0) return 0;
+    if (dtype != FSA_F32 && dtype != FSA_BF16 && dtype != FSA_F16) return 0;
+    return fsa::dense_pays(B, k1, k2, D, elem_bytes(dtype), num_nodes) ? 1 : 0;
+}
+
+int fsa_mean_bwd_dense(const void* grad_out, const void* grad_h1, int dtype,
+                       const int32_t* ids1, const int32_t* ids2,
+                       int64_t B, int32_t k1, int32_t k2, int64_t D,
+                       void* grad_x, int64_t num_nodes,
+                       void* workspace, int64_t workspace_bytes, void* stream) {
+    if (!grad_out || !ids1 || !grad_x || !workspace) return FSA_ERR_NULL;
+    if (int rc = check_common(dtype, D, num_nodes, B)) return rc;
+    if (!fanout_ok(k1) || (ids2 && !fanout_ok(k2))) return FSA_ERR_ARG;
+    if (!ids2 && grad_h1) return FSA_ERR_ARG;
+    const int64_t need = fsa_mean_bwd_dense_workspace_bytes(B, k1, ids2 ? k2 : 0, D, num_nodes);
+    if (need == 0 || workspace_bytes < need) return FSA_ERR_ARG;
+    const uintptr_t g_align = (uintptr_t)elem_bytes(dtype);
+    if (!aligned(grad_out, g_align) || !aligned(grad_h1, g_align) || !aligned(ids1, 4) || !aligned(ids2, 4) ||
+        !aligned(grad_x, 16) || !aligned(workspace, 256))
+        return FSA_ERR_ALIGN;
+    drop_stale_hip_error();
+
+    fsa::BwdArgs a{};
+    a.grad_out = grad_out; a.grad_h1 = grad_h1; a.ids1 = ids1; a.ids2 = ids2;
+    a.B = B; a.k1 = k1; a.k2 = ids2 ? k2 : 0; a.D = D; a.grad_x = grad_x;
+    a.grad_kind = dtype; a.grad_x_kind = dtype;
+    return status_of(fsa::launch_backward_dense(a, num_nodes, workspace, (size_t)workspace_bytes, static_cast<hipStream_t>(stream)));
+}
+
 int fsa_sample_wmean_fwd(const void* indptr, int indptr_type, const int32_t* indices,
                          const float* edge_weight, int64_t num_nodes,
                          const void* x, int x_dtype, int64_t D,

@@ -121,6 +121,12 @@ hipError_t launch_backward_sorted(const BwdArgs& a, void* workspace, size_t work
 size_t owned_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int x_bytes);
 hipError_t launch_backward_owned(const BwdArgs& a, const WeightArgs* w, void* workspace, size_t workspace_bytes,
                                  hipStream_t stream, bool* used);
+// Backward that writes every row of grad_x once, whatever it held (N rows; ids2 or one hop; grad_x of the
+// gradients' type).  dense_workspace_bytes is 0 where it does not run, dense_pays says
+// where it is faster than clearing and atomics.
+bool dense_pays(int64_t B, int k1, int k2, int64_t D, int elem_bytes, int64_t N);
+size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N);
+hipError_t launch_backward_dense(const BwdArgs& a, int64_t N, void* workspace, size_t workspace_bytes, hipStream_t stream);
 hipError_t launch_backward1_weighted(const BwdArgs& a, const float* w1, hipStream_t stream);   // 1-hop, fp32
 // work[b,j,:] = (slot j took part ? grad_out[b,:] / #such slots : 0) + grad_h1[b,j,:]  (grad_h1 nullable)
 hipError_t launch_deep_grad(const float* grad_out, const float* grad_h1, const int32_t* ids1, const int32_t* ids2,

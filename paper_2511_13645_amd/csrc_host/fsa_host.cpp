@@ -24,7 +24,8 @@ PyObject* raw_stream = nullptr;                        // device index -> curren
 
 // Addresses of the C ABI's entry points, set by bind(), with the types that fsa.h declares them with.
 #define FSA_HOST_ENTRIES(X) X(fsa_sample_mean_fwd) X(fsa_sample_wmean_fwd) X(fsa_mean_replay_fwd) X(fsa_mean_bwd) \
-                            X(fsa_mean_bwd_ws) X(fsa_mean_bwd_lp_ws) X(fsa_wmean_bwd_ws)
+                            X(fsa_mean_bwd_ws) X(fsa_mean_bwd_lp_ws) X(fsa_wmean_bwd_ws) \
+                            X(fsa_mean_bwd_dense) X(fsa_mean_bwd_dense_workspace_bytes)
 struct {
 #define FSA_HOST_MEMBER(name) decltype(&::name) name;
     FSA_HOST_ENTRIES(FSA_HOST_MEMBER)
@@ -236,6 +237,36 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// (grad_out, ids1, ids2 | None, grad_h1 | None, num_nodes) -> grad_x of fsa_mean_bwd_dense
+PyObject* grad_dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 5) Py_RETURN_NONE;
+    return or_none([&]() -> PyObject* {
+        const Tensor *g = tensor_of(a[0]), *ids1 = tensor_of(a[1]);
+        const bool two = a[2] != Py_None, slots = a[3] != Py_None;
+        const Tensor *ids2 = two ? tensor_of(a[2]) : nullptr, *gh = slots ? tensor_of(a[3]) : nullptr;
+        if (!PyLong_CheckExact(a[4]) || observed() || !plain(g, 2) || !plain(ids1, 2, at::kInt) || float_code(*g) < 0) Py_RETURN_NONE;
+        const int64_t B = ids1->size(0), k1 = ids1->size(1), D = g->size(1), N = PyLong_AsLongLong(a[4]);
+        if (N < 1 || g->size(0) != B || !together(*g, *ids1)) { PyErr_Clear(); Py_RETURN_NONE; }
+        if (two && (!plain(ids2, 3, at::kInt) || ids2->size(0) != B || ids2->size(1) != k1 || !together(*g, *ids2))) Py_RETURN_NONE;
+        const int64_t k2 = two ? ids2->size(2) : 0;
+        if (k1 < 1 || k1 > FSA_KMAX || k2 > FSA_KMAX || (two && k2 < 1)) Py_RETURN_NONE;
+        if (slots && (!two || !plain(gh, 3, g->scalar_type()) || gh->size(0) != B || gh->size(1) != k1 || gh->size(2) != D || !together(*g, *gh))) Py_RETURN_NONE;
+        const int64_t need = abi.fsa_mean_bwd_dense_workspace_bytes(B, (int32_t)k1, (int32_t)k2, D, N);
+        if (need <= 0) Py_RETURN_NONE;
+        void* stream;
+        if (!stream_of(*g, &stream)) return nullptr;
+        const auto rows = at::TensorOptions().dtype(g->dtype()).device(g->device());
+        Tensor grad_x, ws;                                   // (the workspace may go once the call is queued: same stream)
+        const int rc = without_gil([&] {
+            grad_x = at::empty({N, D}, rows);
+            ws = at::empty({need}, rows.dtype(at::kByte));
+            return abi.fsa_mean_bwd_dense(data(g), data(gh), float_code(*g), data<int32_t>(ids1), data<int32_t>(ids2), B, (int32_t)k1, (int32_t)k2, D,
+                                          data(grad_x), N, data(ws), need, stream);
+        });
+        return rc != FSA_OK ? PyLong_FromLong(rc) : wrap(grad_x);
+    });
+}
+
 // (raw_stream, {entry point: address})
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 2 || !PyDict_Check(a[1])) { PyErr_SetString(PyExc_TypeError, "a stream function and the entry points' addresses"); return nullptr; }
@@ -259,6 +290,7 @@ PyMethodDef methods[] = {
     {"sample_fwd", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(sample_fwd)), METH_FASTCALL, nullptr},
     {"replay_fwd", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(replay_fwd)), METH_FASTCALL, nullptr},
     {"bwd", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(bwd)), METH_FASTCALL, nullptr},
+    {"grad_dense", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(grad_dense)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fsa_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
