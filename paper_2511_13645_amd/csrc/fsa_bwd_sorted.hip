@@ -154,20 +154,24 @@ __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
         p.ws.coef[b * k1 + tid] = cf;
         cf_shared[tid] = cf;
     }
-    for (int e = tid; e < n_ent; e += blockDim.x) {
-        const int j = e / k2;
-        const int id = u[j] >= 0 ? p.ids2[b * n_ent + e] : -1;
-        if (id < 0) continue;
-        const unsigned long long key = ((unsigned long long)(uint32_t)id << 32) | (uint32_t)(b * k1 + j);
-        const int bucket = bucket_of(id, p.ws.log_p);
-        const int pos = atomicAdd(&p.ws.cursor[(size_t)bucket * kCursorStride], 1);
-        if (pos < kBucketCap) {
-            p.ws.pairs[(size_t)bucket * kBucketCap + pos] = key;
-        } else {
-            const int o = atomicAdd(p.ws.overflow_count, 1);          // < B*k1*k2: every entry lands at most once
-            p.ws.overflow[o] = key;
+    auto place_entries = [&] {
+        for (int e = tid; e < n_ent; e += blockDim.x) {
+            const int j = e / k2;
+            const int id = u[j] >= 0 ? p.ids2[b * n_ent + e] : -1;
+            if (id < 0) continue;
+            const unsigned long long key = ((unsigned long long)(uint32_t)id << 32) | (uint32_t)(b * k1 + j);
+            const int bucket = bucket_of(id, p.ws.log_p);
+            const int pos = atomicAdd(&p.ws.cursor[(size_t)bucket * kCursorStride], 1);
+            if (pos < kBucketCap) {
+                p.ws.pairs[(size_t)bucket * kBucketCap + pos] = key;
+            } else {
+                const int o = atomicAdd(p.ws.overflow_count, 1);      // < B*k1*k2: every entry lands at most once
+                p.ws.overflow[o] = key;
+            }
         }
-    }
+    };
+    const bool rows_first = p.slot_grad && ((b >> 8) & 1) != 0;
+    if (!rows_first) place_entries();
     if (p.slot_grad) {                                                // grid-uniform
         using T = typename FloatChunk<VB>::T;
         constexpr int VE = FloatChunk<VB>::VE;
@@ -203,6 +207,7 @@ __global__ __launch_bounds__(256) void sorted_bin_kernel(const SortedParams p) {
             }
         }
     }
+    if (rows_first) place_entries();
 }
 
 // Loads bucket `bucket`'s entries into `keys`, sorts them ascending -- (row, slot) order fixes the
