@@ -60,17 +60,23 @@ class _FusedSampleMean(torch.autograd.Function):
         if ctx.master_grad is not None:
             binding.fsa_mean_bwd_lp(g_out, ids1, ids2, gh, grad_x=ctx.master_grad)
             return (None,) * 10
-        B, k1 = ids1.shape
-        k2 = ids2.shape[2] if ids2 is not None else 0
         n, d = ctx.shape
         # x.grad is a tensor of its own: written row by row where that is faster than clearing it and adding, unless
         # a caller's workspace buys sums whose order does not vary; 16-bit rows of odd length are summed in fp32 to the end
-        owned = (ctx.workspace is not None and ctx.x_dtype == torch.float32 and k2 > 0 and
-                 binding.fsa_mean_bwd_workspace_bytes(B, k1, k2, d) > 0)
-        odd = d % 2 != 0 and ctx.x_dtype != torch.float32
-        if not owned and not odd and binding.fsa_mean_bwd_dense_pays(B, k1, k2, d, ctx.x_dtype, n):
-            grad_x = binding.grad_dense(g_out.to(ctx.x_dtype), ids1, ids2, None if gh is None else gh.to(ctx.x_dtype), n)
-        elif ctx.x_dtype == torch.float32:
+        if ctx.x_dtype == torch.float32:
+            owned = (ctx.workspace is not None and ids2 is not None and
+                     binding.fsa_mean_bwd_workspace_bytes(ids1.shape[0], ids1.shape[1], ids2.shape[2], d) > 0)
+        else:
+            owned = d % 2 != 0
+        if not owned:
+            if g_out.dtype is not ctx.x_dtype:
+                g_out = g_out.to(ctx.x_dtype)
+            if gh is not None and gh.dtype is not ctx.x_dtype:
+                gh = gh.to(ctx.x_dtype)
+            grad_x = binding.grad_dense(g_out, ids1, ids2, gh, n)
+            if grad_x is not None:
+                return (grad_x,) + (None,) * 9
+        if ctx.x_dtype == torch.float32:
             grad_x = torch.zeros(ctx.shape, dtype=torch.float32, device=g_out.device)
             binding.fsa_mean_bwd_ws(g_out.float(), ids1, ids2, None if gh is None else gh.float(), grad_x=grad_x,
                                     workspace=ctx.workspace)

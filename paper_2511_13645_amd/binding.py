@@ -43,7 +43,8 @@ EXPORTS = ("fsa_sample_mean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_me
 _lib: Optional[ctypes.CDLL] = None
 _host = None                                    # the module _fsa_host, once the library is loaded; None without it
 _HOST_ENTRIES = ("fsa_sample_mean_fwd", "fsa_sample_wmean_fwd", "fsa_mean_replay_fwd", "fsa_mean_bwd", "fsa_mean_bwd_ws",
-                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws", "fsa_mean_bwd_dense", "fsa_mean_bwd_dense_workspace_bytes")              # entry points that _fsa_host calls
+                 "fsa_mean_bwd_lp_ws", "fsa_wmean_bwd_ws", "fsa_mean_bwd_dense", "fsa_mean_bwd_dense_workspace_bytes",
+                 "fsa_mean_bwd_dense_pays")              # entry points that _fsa_host calls
 _PLAIN, _WORKSPACE, _LOW_PRECISION, _WEIGHTED = range(4)                # backward entry points, as _fsa_host.bwd counts them
 
 
@@ -405,15 +406,21 @@ def fsa_mean_bwd_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optiona
 
 
 def grad_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor], grad_h1: Optional[torch.Tensor],
-               num_nodes: int) -> torch.Tensor:
-    """fsa_mean_bwd_dense into a gradient [num_nodes,D] allocated here, with a workspace that lasts for the call."""
+               num_nodes: int) -> Optional[torch.Tensor]:
+    """fsa_mean_bwd_dense into a gradient [num_nodes,D] allocated here, with a workspace that lasts for the call; None
+    where clearing a gradient and adding to it is expected to be faster."""
     if _host is not None:
         grad_x = _host.grad_dense(grad_out, ids1, ids2, grad_h1, num_nodes)
+        if grad_x is False:
+            return None
         if _taken(grad_x, "fsa_mean_bwd_dense"):
             return grad_x
-    need = fsa_mean_bwd_dense_workspace_bytes(ids1.shape[0], ids1.shape[1], 0 if ids2 is None else ids2.shape[2], grad_out.shape[1], num_nodes)
-    return fsa_mean_bwd_dense(grad_out, ids1, ids2, grad_h1, grad_x=grad_out.new_empty((num_nodes, grad_out.shape[1])),
-                              workspace=grad_out.new_empty(need, dtype=torch.uint8))
+    B, k1 = ids1.shape
+    D, k2 = grad_out.shape[1], 0 if ids2 is None else ids2.shape[2]
+    if not fsa_mean_bwd_dense_pays(B, k1, k2, D, grad_out.dtype, num_nodes):
+        return None
+    ws = grad_out.new_empty(fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, num_nodes), dtype=torch.uint8)
+    return fsa_mean_bwd_dense(grad_out, ids1, ids2, grad_h1, grad_x=grad_out.new_empty((num_nodes, D)), workspace=ws)
 
 
 def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,

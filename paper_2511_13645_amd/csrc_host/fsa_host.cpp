@@ -25,7 +25,7 @@ PyObject* raw_stream = nullptr;                        // device index -> curren
 // Addresses of the C ABI's entry points, set by bind(), with the types that fsa.h declares them with.
 #define FSA_HOST_ENTRIES(X) X(fsa_sample_mean_fwd) X(fsa_sample_wmean_fwd) X(fsa_mean_replay_fwd) X(fsa_mean_bwd) \
                             X(fsa_mean_bwd_ws) X(fsa_mean_bwd_lp_ws) X(fsa_wmean_bwd_ws) \
-                            X(fsa_mean_bwd_dense) X(fsa_mean_bwd_dense_workspace_bytes)
+                            X(fsa_mean_bwd_dense) X(fsa_mean_bwd_dense_workspace_bytes) X(fsa_mean_bwd_dense_pays)
 struct {
 #define FSA_HOST_MEMBER(name) decltype(&::name) name;
     FSA_HOST_ENTRIES(FSA_HOST_MEMBER)
@@ -237,7 +237,7 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// (grad_out, ids1, ids2 | None, grad_h1 | None, num_nodes) -> grad_x of fsa_mean_bwd_dense
+// (grad_out, ids1, ids2 | None, grad_h1 | None, num_nodes) -> grad_x of fsa_mean_bwd_dense, or False where it does not pay
 PyObject* grad_dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 5) Py_RETURN_NONE;
     return or_none([&]() -> PyObject* {
@@ -251,8 +251,8 @@ PyObject* grad_dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t k2 = two ? ids2->size(2) : 0;
         if (k1 < 1 || k1 > FSA_KMAX || k2 > FSA_KMAX || (two && k2 < 1)) Py_RETURN_NONE;
         if (slots && (!two || !plain(gh, 3, g->scalar_type()) || gh->size(0) != B || gh->size(1) != k1 || gh->size(2) != D || !together(*g, *gh))) Py_RETURN_NONE;
+        if (!abi.fsa_mean_bwd_dense_pays(B, (int32_t)k1, (int32_t)k2, D, float_code(*g), N)) Py_RETURN_FALSE;
         const int64_t need = abi.fsa_mean_bwd_dense_workspace_bytes(B, (int32_t)k1, (int32_t)k2, D, N);
-        if (need <= 0) Py_RETURN_NONE;
         void* stream;
         if (!stream_of(*g, &stream)) return nullptr;
         const auto rows = at::TensorOptions().dtype(g->dtype()).device(g->device());
