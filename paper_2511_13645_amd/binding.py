@@ -408,7 +408,7 @@ def fsa_mean_bwd_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optiona
 def grad_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor], grad_h1: Optional[torch.Tensor],
                num_nodes: int) -> Optional[torch.Tensor]:
     """fsa_mean_bwd_dense into a gradient [num_nodes,D] allocated here, with a workspace that lasts for the call; None
-    where clearing a gradient and adding to it is expected to be faster."""
+    where clearing a gradient and adding to it is expected to be faster, or where the workspace finds no memory."""
     if _host is not None:
         grad_x = _host.grad_dense(grad_out, ids1, ids2, grad_h1, num_nodes)
         if grad_x is False:
@@ -419,8 +419,12 @@ def grad_dense(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.
     D, k2 = grad_out.shape[1], 0 if ids2 is None else ids2.shape[2]
     if not fsa_mean_bwd_dense_pays(B, k1, k2, D, grad_out.dtype, num_nodes):
         return None
-    ws = grad_out.new_empty(fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, num_nodes), dtype=torch.uint8)
-    return fsa_mean_bwd_dense(grad_out, ids1, ids2, grad_h1, grad_x=grad_out.new_empty((num_nodes, D)), workspace=ws)
+    grad_x = grad_out.new_empty((num_nodes, D))
+    try:
+        ws = grad_out.new_empty(fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, num_nodes), dtype=torch.uint8)
+    except torch.cuda.OutOfMemoryError:                        # no room beside the gradient: the other way needs none
+        return None
+    return fsa_mean_bwd_dense(grad_out, ids1, ids2, grad_h1, grad_x=grad_x, workspace=ws)
 
 
 def fsa_mean_bwd_lp(grad_out: torch.Tensor, ids1: torch.Tensor, ids2: Optional[torch.Tensor] = None,

@@ -123,3 +123,24 @@ def test_autograd_takes_the_dense_route_and_replays_in_a_graph(orc):
         graph.replay()
         torch.cuda.synchronize()
         assert_close(to_f64(captured), ref, scale, 1e-5, "autograd, dense route, replayed")
+
+
+@pytest.mark.parametrize("short_of_memory", [False, True])
+def test_dense_gradient_through_python_and_without_room_for_its_workspace(monkeypatch, short_of_memory):
+    from paper_2511_13645_amd import binding
+    n, D, B, k1, k2 = 20000, 64, 1024, 25, 10
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    ids1 = torch.randint(0, n, (B, k1), generator=gen, device=DEV, dtype=torch.int32)
+    ids2 = torch.randint(0, n, (B, k1, k2), generator=gen, device=DEV, dtype=torch.int32)
+    g = torch.randn((B, D), generator=gen, device=DEV)
+    native = binding.grad_dense(g, ids1, ids2, None, n)
+    monkeypatch.setattr(binding, "_host", None)
+    if short_of_memory:
+        def none_left(*a, **kw):
+            raise torch.cuda.OutOfMemoryError("no memory")
+        monkeypatch.setattr(binding, "fsa_mean_bwd_dense_workspace_bytes", none_left)
+        assert binding.grad_dense(g, ids1, ids2, None, n) is None
+    else:
+        # two orders of up to a few dozen fp32 additions a row
+        assert torch.allclose(binding.grad_dense(g, ids1, ids2, None, n), native, rtol=1e-5, atol=1e-6)
+    assert binding.grad_dense(g[:1], ids1[:1], ids2[:1], None, n) is None      # too small to pay
