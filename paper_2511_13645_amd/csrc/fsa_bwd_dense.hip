@@ -6,13 +6,14 @@
 // What bounds it: the rows written (N*D elements, once).  Clearing first and adding with atomics wrote them all, read
 // the named ones back and paid a 64-byte segment's atomic (20.8 G/s) for every 64 bytes of every leaf.
 //
-// Three launches on the caller's stream, all state in the caller's workspace:
+// Four launches on the caller's stream, all state in the caller's workspace:
 //   clear   zero the bins' counters (a fill kernel: a memset node must not end up in a captured graph);
-//   bin     grad_x is cut into bins of consecutive rows; every live leaf slot appends an entry to its row's bin;
-//           a full bin sends its entries to the overflow list;
-//   write   a workgroup per bin sums the gradients of its rows' entries in registers, in fp32, and writes every row.
-//           A bin that overflowed picks its entries out of the overflow list as well, so hub rows take no atomics in
-//           memory either.
+//   bin     grad_x is cut into bins of consecutive rows; every live leaf slot appends an entry to its row's bin.
+//           A full bin gets a tile, its rows in fp32, and further entries go to lists;
+//   rest    workgroups take up to 256 entries of a list each, sum them by rows and add one row per distinct row to its
+//           bin's tile: however a batch's leaves are skewed, these are no more row atomics than adding leaf by leaf;
+//   write   a workgroup per bin sums the gradients of its rows' entries in registers, in fp32, adds the tile if there
+//           is one, and writes every row.
 // The order of additions follows the places that the entries got, which varies from run to run, as with atomics.
 #include "fsa_atomic_rows.hip.h"
 #include "fsa_device.hip.h"
@@ -30,6 +31,12 @@ constexpr int kDenseThreads = 256;
 constexpr int kDenseBinElements = 8192;
 constexpr int kDenseRowsMin = 32;                                    // (bins start at multiples of 16 bytes of grad_x, whatever D)
 constexpr int kDenseRowsMax = 256;
+// Room of a bin at most: longer is a longer chain for one workgroup, shorter leaves more of an evenly loaded batch to the
+// lists (16 M leaf slots, 28 % live, on 169,343 rows of 128 floats: 512 1260 us, 1024 974, 2048 788, the longest bin 82 us).
+constexpr int kDenseMostRoom = 2048;
+constexpr int kRestLists = 32;                                       // of entries that found their bins full: a wave's append is an
+                                                                     // atomic on its list's length, one per 11 ns on one address
+constexpr int kCountStride = 2 * kSegment;                           // ints between their lengths: a 128-byte line each
 constexpr int64_t kDenseMinSegments = 768 * 1024;                   // see dense_pays
 constexpr int64_t kDenseMaxRowsPerSlot = 16;
 constexpr int64_t kDenseMaxD = 1024;                                 // 16 KB of LDS at four groups
@@ -43,7 +50,11 @@ struct DenseParams {
     int D, k1, k2;                        // a root has k1 slots, a slot k2 leaves (one hop: k1 = 1, a seed is a slot)
     int slots_per_wg;                     // binning: whole roots
     int row_shift, bins, room, stride;    // rows of a bin (log2), bins, entries a bin holds, ints between two counters
-    int* counter; int* overflow_count; unsigned long long* entries; unsigned long long* overflow; int* overflow_bin;
+    int* counter; int* rest_count; int* tile_count;
+    unsigned long long* entries;          // [bins][room]
+    unsigned long long* rest; int* rest_bin;                         // [kRestLists][rest_room]: entries and their bins
+    int64_t rest_room;
+    int* tile_of; float* tiles;           // [bins], full bins only; [tiles][rows of a bin][D]
 };
 
 // A leaf slot in a bin: its row of the bin, its root and slot, and how many slots of the root and leaf slots of the slot
@@ -61,33 +72,39 @@ struct Entry {
     __device__ int64_t root() const { return (int64_t)(v & 0x3fffffffffull); }
 };
 
-struct DensePlan { int row_shift, room, stride; int64_t bins; size_t off[5], total; };
+struct DensePlan { int row_shift, room, stride; int64_t bins, rest_room; size_t off[7], total; };
 
-static DensePlan dense_plan(int64_t slots, int k2, int64_t D, int64_t N) {
+static DensePlan dense_plan(int64_t slots, int k2, int slots_per_wg, int64_t D, int64_t N) {
     DensePlan q{};
     while ((2ll << q.row_shift) <= kDenseRowsMax && (2ll << q.row_shift) * D <= kDenseBinElements) ++q.row_shift;
     while ((1 << q.row_shift) < kDenseRowsMin) ++q.row_shift;
     q.bins = (N + (1ll << q.row_shift) - 1) >> q.row_shift;
-    // room for four times the mean with every slot full; a skewed batch's hubs go to the overflow list
-    const int64_t mean = slots * k2 / q.bins;
+    // room for four times the mean with every slot full, while that is no long chain for the bin's workgroup
+    const int64_t leaves = slots * k2, mean = leaves / q.bins;
     q.room = 32;
-    while (q.room < 4096 && q.room < 4 * mean) q.room *= 2;
+    while (q.room < kDenseMostRoom && q.room < 4 * mean) q.room *= 2;
     q.stride = q.bins <= 16384 ? kSegment * 2 : 4;                   // few counters: a 128-byte line each, over all L2 channels
-    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    const int64_t full = (leaves - 1) / q.room < q.bins ? (leaves - 1) / q.room : q.bins;   // bins that can get a tile
+    const int64_t wgs = (slots + slots_per_wg - 1) / slots_per_wg;                          // of the binning
+    q.rest_room = full > 0 ? (wgs + kRestLists - 1) / kRestLists * slots_per_wg * k2 : 0;
     size_t o = 0;
-    q.off[0] = o; o += up((size_t)q.bins * q.stride * sizeof(int));
-    q.off[1] = o; o += up(sizeof(int));
-    q.off[2] = o; o += up((size_t)q.bins * q.room * sizeof(unsigned long long));
-    q.off[3] = o; o += up((size_t)slots * k2 * sizeof(unsigned long long));
-    q.off[4] = o; o += up((size_t)slots * k2 * sizeof(int));
+    auto take = [&](int i, size_t bytes) { q.off[i] = o; o += (bytes + 255) & ~(size_t)255; };
+    take(0, (size_t)q.bins * q.stride * sizeof(int));
+    take(1, kRestLists * kCountStride * sizeof(int) + sizeof(int));
+    take(2, (size_t)q.bins * q.room * sizeof(unsigned long long));
+    take(3, kRestLists * (size_t)q.rest_room * sizeof(unsigned long long));
+    take(4, kRestLists * (size_t)q.rest_room * sizeof(int));
+    take(5, full > 0 ? (size_t)q.bins * sizeof(int) : 0);
+    take(6, ((size_t)full << q.row_shift) * D * sizeof(float));
     q.total = o;
     return q;
 }
 
-__global__ __launch_bounds__(256) void dense_clear_kernel(int* counter, int bins, int stride, int* overflow_count) {
+__global__ __launch_bounds__(256) void dense_clear_kernel(int* counter, int bins, int stride, int* rest_count, int* tile_count) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < bins) counter[(size_t)i * stride] = 0;
-    if (i == 0) *overflow_count = 0;
+    if (i < kRestLists) rest_count[i * kCountStride] = 0;
+    if (i == 0) *tile_count = 0;
 }
 
 // A workgroup takes whole roots (one with two hops, as many seeds as have 256 leaf slots with one hop).  Bound by the
@@ -133,16 +150,30 @@ __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DensePar
     for (int e0 = tid;;) {
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            if (id[k] < 0) continue;
             const int bin = id[k] >> p.row_shift;
             const int64_t root = p.ids1 ? (int64_t)blockIdx.x : slot0 + slot[k];
             const Entry e = Entry::of(id[k] & ((1 << p.row_shift) - 1), root, p.ids1 ? slot[k] : 0, c1, cnt[slot[k]]);
-            if (at[k] < p.room) {
-                p.entries[(size_t)bin * p.room + at[k]] = e.v;
-            } else {
-                const int o = atomicAdd(p.overflow_count, 1);        // an entry lands once: below slots * k2
-                p.overflow[o] = e.v;
-                p.overflow_bin[o] = bin;
+            if (id[k] >= 0 && at[k] < p.room) p.entries[(size_t)bin * p.room + at[k]] = e.v;
+            const bool over = id[k] >= 0 && at[k] >= p.room;
+            const uint64_t all = __ballot(over);
+            if (all == 0) continue;                                  // wave-uniform
+            const int list = blockIdx.x % kRestLists;                // has room for all entries of its workgroups
+            int n_before = 0;
+            if (lane == 0) n_before = atomicAdd(&p.rest_count[list * kCountStride], __popcll(all));
+            const int64_t o = list * p.rest_room + __shfl(n_before, 0) + __popcll(all & lanemask_lt(lane));
+            if (over) { p.rest[o] = e.v; p.rest_bin[o] = bin; }
+            // the bin's first entry too many gets it a tile, which this wave clears
+            for (uint64_t first = __ballot(over && at[k] == p.room); first; first &= first - 1) {
+                const int from = __ffsll((unsigned long long)first) - 1;
+                int t = 0;
+                if (lane == from) {
+                    t = atomicAdd(p.tile_count, 1);
+                    p.tile_of[bin] = t;
+                }
+                t = __shfl(t, from);
+                const size_t n = (size_t)p.D << p.row_shift;         // a multiple of 32
+                float4* const tile = reinterpret_cast<float4*>(p.tiles + (size_t)t * n);
+                for (size_t i = lane; i < n / 4; i += kWave) tile[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
         }
         e0 += U * kDenseThreads;
@@ -157,113 +188,184 @@ template <> struct TableOf<g_f32> { using T = f32_t; };
 template <> struct TableOf<g_bf16> { using T = bf16_t; };
 template <> struct TableOf<g_f16> { using T = f16_t; };
 
-// A workgroup per bin.  Its entries are sorted by row in LDS, 256 at a time, by
-// counting; groups of `1 << group_shift` lanes, VE elements each, take a row each, sum its entries in registers and write
-// it.  Rows of more than kHubEntries entries are summed by all groups together.  Entries beyond the first 256 of a bin
-// are added to the rows that are written already, by the lanes that wrote them.
-// (Bound by instructions before it was by the rows written: with the sums in LDS, cleared, added to and copied out, 46 us for
-// 75,000 entries in 169,343 rows of 128 floats, and 110 us where LDS took them with atomics, at 3 to 7 clocks a lane.)
+// Rows of more than kHubEntries of a workgroup's 256 entries are summed by all of its groups together.
 constexpr int kHubEntries = 32;
-template <typename GT, int VE, bool SLOT_GRADS>
-__global__ __launch_bounds__(kDenseThreads) void dense_write_kernel(const DenseParams p, int group_shift) {
+
+// What a workgroup of the two kernels below knows of 256 entries sorted by rows, which groups of `1 << group_shift`
+// lanes, VE elements each, sum in registers: a row each, or a hub row all together.
+template <typename GT, int VE, bool SLOT_GRADS> struct RowSums {
     using Row = Chunk<typename TableOf<GT>::T, VE * (std::is_same<GT, g_f32>::value ? 4 : 2)>;
     using Raw = typename Row::Raw;
-    extern __shared__ __align__(16) float partial[];                 // [groups][D], rows of many entries
-    __shared__ int count[kDenseRowsMax], start[kDenseRowsMax];
-    __shared__ int4 sorted[kDenseThreads];                           // root, slot, their coefficients
-    __shared__ int wave_total[kDenseThreads / kWave];
-    __shared__ int hubs[kDenseThreads / kHubEntries];
-    __shared__ int n_hubs, picked;
-    unsigned long long* const chosen = reinterpret_cast<unsigned long long*>(sorted);   // entries from the overflow list
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int D = p.D;
-    const uint32_t row_bytes = (uint32_t)D * (uint32_t)(sizeof(Raw) / VE);
-    const int grp = tid >> group_shift, sl = tid & ((1 << group_shift) - 1), lanes = 1 << group_shift;
-    const int n_grp = kDenseThreads >> group_shift;
-    const char* const go = static_cast<const char*>(p.grad_out);
-    const char* const gh = static_cast<const char*>(p.grad_h1);
+    const DenseParams& p;
+    const int group_shift;
+    const int4* const sorted;                                        // LDS: root, slot, their coefficients
+    const int *const count, *const start;                            // LDS, by row: entries, the first one's place
+    const int* const hubs;                                           // LDS: rows of more than kHubEntries
+    float* const partial;                                            // LDS: [groups][D]
+
+    __device__ static int4 sorted_entry(const Entry e, int k1) {
+        const float c1 = (float)e.c1(), c2 = (float)e.c2();
+        return make_int4((int)e.root(), (int)(e.root() * k1 + e.slot()), __float_as_int(1.0f / (c1 * c2)), __float_as_int(1.0f / c2));
+    }
 
     // acc += the gradients of the U sorted entries e, e + step, ... at byte `at` of their rows
-    auto gather = [&](auto u_, float (&acc)[VE], int e, int step, uint32_t at) {
-        constexpr int U = decltype(u_)::value;
+    template <int U> __device__ __forceinline__ void gather(float (&acc)[VE], int e, int step, uint32_t at) const {
+        const uint32_t row_bytes = (uint32_t)p.D * (uint32_t)(sizeof(Raw) / VE);
         Raw a[U], b[U];
         int4 s[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             s[u] = sorted[e + u * step];
-            a[u] = *reinterpret_cast<const Raw*>(go + ((uint64_t)(uint32_t)s[u].x * row_bytes + at));
-            if constexpr (SLOT_GRADS) b[u] = *reinterpret_cast<const Raw*>(gh + ((uint64_t)(uint32_t)s[u].y * row_bytes + at));
+            a[u] = *reinterpret_cast<const Raw*>(static_cast<const char*>(p.grad_out) + ((uint64_t)(uint32_t)s[u].x * row_bytes + at));
+            if constexpr (SLOT_GRADS)
+                b[u] = *reinterpret_cast<const Raw*>(static_cast<const char*>(p.grad_h1) + ((uint64_t)(uint32_t)s[u].y * row_bytes + at));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             Row::fma(acc, a[u], __int_as_float(s[u].z));
             if constexpr (SLOT_GRADS) Row::fma(acc, b[u], __int_as_float(s[u].w));
         }
-    };
-    auto sum = [&](float (&acc)[VE], int e, int end, int step, uint32_t at) {
-        for (; e + 3 * step < end; e += 4 * step) gather(std::integral_constant<int, 4>{}, acc, e, step, at);
-        for (; e < end; e += step) gather(std::integral_constant<int, 1>{}, acc, e, step, at);
-    };
-    // The rows of a bin at `out`: n entries of theirs, thread tid has the tid-th; `more`: the rows are written already.
-    auto add = [&](int n, Entry mine, char* out, int rows, bool more) {
-        if (tid < rows) count[tid] = 0;
-        if (tid == 0) n_hubs = 0;
-        __syncthreads();
-        const int place = tid < n ? atomicAdd(&count[mine.row()], 1) : 0;
-        __syncthreads();
-        const int c = tid < rows ? count[tid] : 0;
-        int at = wave_inclusive_scan(c, lane);
-        if (lane == kWave - 1) wave_total[wave] = at;
-        if (c > kHubEntries) hubs[atomicAdd(&n_hubs, 1)] = tid;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) at += wave_total[w];
-        if (tid < rows) start[tid] = at - c;
-        __syncthreads();
-        if (tid < n) {
-            const float c1 = (float)mine.c1(), c2 = (float)mine.c2();
-            sorted[start[mine.row()] + place] = make_int4((int)mine.root(), (int)(mine.root() * p.k1 + mine.slot()),
-                                                          __float_as_int(1.0f / (c1 * c2)), __float_as_int(1.0f / c2));
-        }
-        __syncthreads();
+    }
+    __device__ __forceinline__ void sum(float (&acc)[VE], int e, int end, int step, uint32_t at) const {
+        for (; e + 3 * step < end; e += 4 * step) gather<4>(acc, e, step, at);
+        for (; e < end; e += step) gather<1>(acc, e, step, at);
+    }
+
+    // out(r, d, acc) for every row r < rows and its elements d, always by the same lanes for one r; rows without entries
+    // only if `empty`.  All threads of the workgroup, between two barriers.
+    template <typename F> __device__ __forceinline__ void operator()(int rows, bool empty, int n_hubs, F out) const {
+        const int tid = threadIdx.x, grp = tid >> group_shift, n_grp = kDenseThreads >> group_shift;
+        const int lanes = 1 << group_shift, D = p.D, d0 = (tid & (lanes - 1)) * VE;
+        constexpr uint32_t EB = sizeof(Raw) / VE;
         for (int r = grp; r < rows; r += n_grp) {
             const int m = count[r], e = start[r];
-            if (m > kHubEntries || (more && m == 0)) continue;
-            char* const row = out + (uint32_t)r * row_bytes;
-            for (int d = sl * VE; d < D; d += lanes * VE) {
-                const uint32_t by = (uint32_t)d * (uint32_t)(sizeof(Raw) / VE);
+            if (m > kHubEntries || (!empty && m == 0)) continue;
+            for (int d = d0; d < D; d += lanes * VE) {
                 float acc[VE] = {};
-                if (more) Row::add(acc, *reinterpret_cast<const Raw*>(row + by));
-                sum(acc, e, e + m, 1, by);
-                *reinterpret_cast<Raw*>(row + by) = Row::pack(acc);
+                sum(acc, e, e + m, 1, (uint32_t)d * EB);
+                out(r, d, acc);
             }
         }
-        const int nh = n_hubs;
-        for (int h = 0; h < nh; ++h) {                               // workgroup-uniform
+        for (int h = 0; h < n_hubs; ++h) {                           // workgroup-uniform
             const int r = hubs[h], e = start[r], end = e + count[r];
-            for (int d = sl * VE; d < D; d += lanes * VE) {
+            for (int d = d0; d < D; d += lanes * VE) {
                 float acc[VE] = {};
-                sum(acc, e + grp, end, n_grp, (uint32_t)d * (uint32_t)(sizeof(Raw) / VE));
+                sum(acc, e + grp, end, n_grp, (uint32_t)d * EB);
 #pragma unroll
                 for (int k = 0; k < VE; ++k) partial[grp * D + d + k] = acc[k];
             }
             __syncthreads();
-            if (grp == r % n_grp) {                                  // the lanes that write row r whenever it is written
-                char* const row = out + (uint32_t)r * row_bytes;
-                for (int d = sl * VE; d < D; d += lanes * VE) {
-                    const uint32_t by = (uint32_t)d * (uint32_t)(sizeof(Raw) / VE);
+            if (grp == r % n_grp) {
+                for (int d = d0; d < D; d += lanes * VE) {
                     float acc[VE] = {};
-                    if (more) Row::add(acc, *reinterpret_cast<const Raw*>(row + by));
                     for (int g = 0; g < n_grp; ++g) {
 #pragma unroll
                         for (int k = 0; k < VE; ++k) acc[k] += partial[g * D + d + k];
                     }
-                    *reinterpret_cast<Raw*>(row + by) = Row::pack(acc);
+                    out(r, d, acc);
                 }
             }
             __syncthreads();
         }
+    }
+};
+
+// The entries that found their bins full, up to 256 of a list at a time: rows are told apart in an LDS table, and each
+// distinct row's sum is added to its tile.  Bound by a group's trips to memory, one row after the other, so a short list
+// is spread over its workgroups; a long one is not cut finer, which would add a hub row to its tile more often (153,600
+// leaves of one row: 256 entries at a time 25 us, 75 56); without lists 1.7 us.
+constexpr int kRestTable = 2 * kDenseThreads;
+constexpr int kRestLeast = 32;                                       // entries a workgroup takes at least
+constexpr int kRestEach = 16;                                        // workgroups to a list
+template <typename GT, int VE, bool SLOT_GRADS>
+__global__ __launch_bounds__(kDenseThreads) void dense_rest_kernel(const DenseParams p, int group_shift) {
+    using Sums = RowSums<GT, VE, SLOT_GRADS>;
+    extern __shared__ __align__(16) float partial[];
+    __shared__ uint32_t tag[kRestTable];
+    __shared__ int seen[kRestTable], first[kRestTable];              // by table place: entries; the first one's place
+    __shared__ uint32_t row[kDenseThreads];                          // distinct rows, of all tiles
+    __shared__ int count[kDenseThreads], start[kDenseThreads];
+    __shared__ int4 sorted[kDenseThreads];
+    __shared__ int wave_total[kDenseThreads / kWave];
+    __shared__ int hubs[kDenseThreads / kHubEntries];
+    __shared__ int n_rows, n_hubs;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const Sums sums{p, group_shift, sorted, count, start, hubs, partial};
+    const int list = blockIdx.x % kRestLists;
+    const unsigned total = (unsigned)p.rest_count[list * kCountStride];
+    unsigned each = (total + kRestEach - 1) / kRestEach;
+    each = each < kRestLeast ? kRestLeast : each < kDenseThreads ? each : kDenseThreads;
+    for (unsigned i0 = blockIdx.x / kRestLists * each; i0 < total; i0 += kRestEach * each) {   // workgroup-uniform
+        const int n = (int)(total - i0 < each ? total - i0 : each);
+        Entry mine{0};
+        uint32_t to = ~0u;                                           // (no row's number: there are fewer than 2^24 bins)
+        if (tid < n) {
+            const int64_t i = list * p.rest_room + i0 + tid;
+            mine.v = p.rest[i];
+            to = (uint32_t)p.tile_of[p.rest_bin[i]] << p.row_shift | (uint32_t)mine.row();
+        }
+        for (int h = tid; h < kRestTable; h += kDenseThreads) { tag[h] = ~0u; seen[h] = 0; }
+        if (tid == 0) { n_rows = 0; n_hubs = 0; }
         __syncthreads();
-    };
+        int h = 0, place = 0;
+        bool owner = false;
+        if (tid < n) {                                               // twice as many places as rows: one is found
+            for (h = (int)((to * 2654435761u) >> 23);; h = (h + 1) & (kRestTable - 1)) {
+                const uint32_t was = atomicCAS(&tag[h], ~0u, to);
+                owner = was == ~0u;
+                if (owner || was == to) break;
+            }
+            place = atomicAdd(&seen[h], 1);
+        }
+        __syncthreads();
+        const int c = owner ? seen[h] : 0;
+        int at = wave_inclusive_scan(c, lane);
+        if (lane == kWave - 1) wave_total[wave] = at;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) at += wave_total[w];
+        if (owner) {
+            const int r = atomicAdd(&n_rows, 1);
+            row[r] = to; count[r] = c; start[r] = first[h] = at - c;
+            if (c > kHubEntries) hubs[atomicAdd(&n_hubs, 1)] = r;
+        }
+        __syncthreads();
+        if (tid < n) sorted[first[h] + place] = Sums::sorted_entry(mine, p.k1);
+        __syncthreads();
+        sums(n_rows, false, n_hubs, [&](int r, int d, const float (&acc)[VE]) {
+            // the lanes trade elements, so that each atomic instruction covers consecutive ones
+            const int lanes = 1 << group_shift, sl = tid & (lanes - 1), d0 = d - sl * VE;
+            const int on = (p.D - d0) / VE < lanes ? (p.D - d0) / VE : lanes;     // lanes that are here
+            float* const mine = partial + (tid >> group_shift) * p.D + d0;
+            float* const to = p.tiles + (size_t)row[r] * p.D + d0;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < VE; ++k) mine[sl * VE + k] = acc[k];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < VE; ++k) atomicAdd(to + sl + k * on, mine[sl + k * on]);
+        });
+        __syncthreads();
+    }
+}
+
+// A workgroup per bin.  Its entries are sorted by row in LDS, 256 at a time, by counting.  Entries beyond the first 256
+// of a bin are added to the rows that are written already, by the lanes that wrote them.
+// (Bound by instructions before it was by the rows written: with the sums in LDS, cleared, added to and copied out, 46 us for
+// 75,000 entries in 169,343 rows of 128 floats, and 110 us where LDS took them with atomics, at 3 to 7 clocks a lane.)
+template <typename GT, int VE, bool SLOT_GRADS>
+__global__ __launch_bounds__(kDenseThreads) void dense_write_kernel(const DenseParams p, int group_shift) {
+    using Sums = RowSums<GT, VE, SLOT_GRADS>;
+    using Row = typename Sums::Row;
+    using Raw = typename Sums::Raw;
+    extern __shared__ __align__(16) float partial[];
+    __shared__ int count[kDenseRowsMax], start[kDenseRowsMax];
+    __shared__ int4 sorted[kDenseThreads];
+    __shared__ int wave_total[kDenseThreads / kWave];
+    __shared__ int hubs[kDenseThreads / kHubEntries];
+    __shared__ int n_hubs;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const Sums sums{p, group_shift, sorted, count, start, hubs, partial};
+    const uint32_t row_bytes = (uint32_t)p.D * (uint32_t)(sizeof(Raw) / VE);
 
     const int bin = blockIdx.x;
     const int64_t row0 = (int64_t)bin << p.row_shift;
@@ -280,36 +382,53 @@ __global__ __launch_bounds__(kDenseThreads) void dense_write_kernel(const DenseP
         return;
     }
     const int held = asked < p.room ? asked : p.room;
+    const float* const tile = asked > p.room ? p.tiles + (((size_t)p.tile_of[bin] << p.row_shift) * p.D) : nullptr;
     for (int i0 = 0; i0 < held; i0 += kDenseThreads) {               // workgroup-uniform, as every branch below
+        const bool more = i0 > 0;                                    // the rows are written already
         const int n = held - i0 < kDenseThreads ? held - i0 : kDenseThreads;
-        if (i0 > 0 && tid < n) key = entries[i0 + tid];
-        add(n, Entry{key}, out, rows, i0 > 0);
+        if (more && tid < n) key = entries[i0 + tid];
+        const Entry mine{key};
+        if (tid < rows) count[tid] = 0;
+        if (tid == 0) n_hubs = 0;
+        __syncthreads();
+        const int place = tid < n ? atomicAdd(&count[mine.row()], 1) : 0;
+        __syncthreads();
+        const int c = tid < rows ? count[tid] : 0;
+        int at = wave_inclusive_scan(c, lane);
+        if (lane == kWave - 1) wave_total[wave] = at;
+        if (c > kHubEntries) hubs[atomicAdd(&n_hubs, 1)] = tid;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) at += wave_total[w];
+        if (tid < rows) start[tid] = at - c;
+        __syncthreads();
+        if (tid < n) sorted[start[mine.row()] + place] = Sums::sorted_entry(mine, p.k1);
+        __syncthreads();
+        sums(rows, !more, n_hubs, [&](int r, int d, float (&acc)[VE]) {
+            Raw* const to = reinterpret_cast<Raw*>(out + ((uint32_t)r * row_bytes + (uint32_t)d * (uint32_t)(sizeof(Raw) / VE)));
+            if (more) Row::add(acc, *to);
+            if (!more && tile) {
+#pragma unroll
+                for (int k = 0; k < VE; ++k) acc[k] += tile[r * p.D + d + k];
+            }
+            *to = Row::pack(acc);
+        });
+        __syncthreads();
     }
-    if (asked <= p.room) return;
-    const int n_over = *p.overflow_count;
-    for (int i0 = 0; i0 < n_over; i0 += kDenseThreads) {
-        if (tid == 0) picked = 0;
-        __syncthreads();
-        if (i0 + tid < n_over && p.overflow_bin[i0 + tid] == bin) chosen[atomicAdd(&picked, 1)] = p.overflow[i0 + tid];
-        __syncthreads();
-        const int n = picked;
-        if (tid < n) key = chosen[tid];
-        __syncthreads();
-        if (n > 0) add(n, Entry{key}, out, rows, true);
-    }
+}
+
+static DensePlan dense_plan_of(int64_t B, int k1, int k2, int64_t D, int64_t N) {
+    return k2 > 0 ? dense_plan(B * k1, k2, k1, D, N) : dense_plan(B, k1, kDenseThreads / k1, D, N);
 }
 
 static bool dense_shape_ok(int64_t B, int k1, int k2, int64_t D, int64_t N) {
     const int64_t leaves = B * k1 * (k2 > 0 ? k2 : 1);
     if (B <= 0 || D > kDenseMaxD || N <= 0 || leaves > INT32_MAX) return false;
     if (k2 > 0 && B * kDenseThreads > (int64_t)UINT32_MAX) return false;             // a workgroup per root
-    const DensePlan q = k2 > 0 ? dense_plan(B * k1, k2, D, N) : dense_plan(B, k1, D, N);
-    return q.bins * kDenseThreads <= (int64_t)UINT32_MAX;
+    return dense_plan_of(B, k1, k2, D, N).bins * kDenseThreads <= (int64_t)UINT32_MAX;
 }
 
 size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
-    if (!dense_shape_ok(B, k1, k2, D, N)) return 0;
-    return (k2 > 0 ? dense_plan(B * k1, k2, D, N) : dense_plan(B, k1, D, N)).total;
+    return dense_shape_ok(B, k1, k2, D, N) ? dense_plan_of(B, k1, k2, D, N).total : 0;
 }
 
 // Against clearing and atomics, which take 48 ps per 64-byte segment of a leaf's row (20.8 G/s), with the dearer launches of
@@ -334,6 +453,9 @@ template <typename GT> static hipError_t launch_dense(const DenseParams& p, hipS
     while (group_shift < 6 && (1 << group_shift) < units) ++group_shift;
     const size_t lds = sizeof(float) * (size_t)(kDenseThreads >> group_shift) * p.D;
     auto go = [&](auto ve, auto slots) {
+        if (p.rest_room > 0)                                         // else no bin is ever full
+            hipLaunchKernelGGL((dense_rest_kernel<GT, decltype(ve)::value, decltype(slots)::value>), dim3(kRestLists * kRestEach),
+                               dim3(kDenseThreads), lds, stream, p, group_shift);
         hipLaunchKernelGGL((dense_write_kernel<GT, decltype(ve)::value, decltype(slots)::value>), dim3((unsigned)p.bins), dim3(kDenseThreads),
                            lds, stream, p, group_shift);
     };
@@ -351,16 +473,19 @@ hipError_t launch_backward_dense(const BwdArgs& a, int64_t N, void* workspace, s
     p.grad_x = a.grad_x; p.slots = two ? a.B * a.k1 : a.B; p.N = N; p.D = (int)a.D;
     p.k1 = two ? a.k1 : 1; p.k2 = two ? a.k2 : a.k1;
     p.slots_per_wg = two ? a.k1 : kDenseThreads / a.k1;
-    const DensePlan q = dense_plan(p.slots, p.k2, a.D, N);
+    const DensePlan q = dense_plan_of(a.B, a.k1, two ? a.k2 : 0, a.D, N);
     if (workspace_bytes < q.total) return hipErrorInvalidValue;
     char* w = static_cast<char*>(workspace);
-    p.row_shift = q.row_shift; p.bins = (int)q.bins; p.room = q.room; p.stride = q.stride;
+    p.row_shift = q.row_shift; p.bins = (int)q.bins; p.room = q.room; p.stride = q.stride; p.rest_room = q.rest_room;
     p.counter = reinterpret_cast<int*>(w + q.off[0]);
-    p.overflow_count = reinterpret_cast<int*>(w + q.off[1]);
+    p.rest_count = reinterpret_cast<int*>(w + q.off[1]);
+    p.tile_count = p.rest_count + kRestLists * kCountStride;
     p.entries = reinterpret_cast<unsigned long long*>(w + q.off[2]);
-    p.overflow = reinterpret_cast<unsigned long long*>(w + q.off[3]);
-    p.overflow_bin = reinterpret_cast<int*>(w + q.off[4]);
-    hipLaunchKernelGGL(dense_clear_kernel, dim3((p.bins + 255) / 256), dim3(256), 0, stream, p.counter, p.bins, p.stride, p.overflow_count);
+    p.rest = reinterpret_cast<unsigned long long*>(w + q.off[3]);
+    p.rest_bin = reinterpret_cast<int*>(w + q.off[4]);
+    p.tile_of = reinterpret_cast<int*>(w + q.off[5]);
+    p.tiles = reinterpret_cast<float*>(w + q.off[6]);
+    hipLaunchKernelGGL(dense_clear_kernel, dim3((p.bins + 255) / 256), dim3(256), 0, stream, p.counter, p.bins, p.stride, p.rest_count, p.tile_count);
     hipLaunchKernelGGL(dense_bin_kernel, dim3((unsigned)((p.slots + p.slots_per_wg - 1) / p.slots_per_wg)), dim3(kDenseThreads), 0, stream, p);
     if (hipError_t e = hipGetLastError()) return e;
     switch (a.grad_kind) {

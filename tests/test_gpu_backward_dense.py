@@ -144,3 +144,66 @@ def test_dense_gradient_through_python_and_without_room_for_its_workspace(monkey
         # two orders of up to a few dozen fp32 additions a row
         assert torch.allclose(binding.grad_dense(g, ids1, ids2, None, n), native, rtol=1e-5, atol=1e-6)
     assert binding.grad_dense(g[:1], ids1[:1], ids2[:1], None, n) is None      # too small to pay
+
+
+def test_16bit_rows_of_full_bins_are_rounded_once_in_256_entries():
+    """Every bin holds far more entries than it has room for.  A row of m equal terms, whose sum is exact in fp32, is off
+    by half a unit in the last place of the running sum for each rounding, and there is one per 256 entries of its bin; a
+    row rounded at every addition would stop growing at 256 terms."""
+    from paper_2511_13645_amd import binding
+    n, D, B, k1 = 2048, 256, 48000, 64                                  # 32 rows to a bin, about 48,000 entries in each
+    rows_of_bin = 32
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    ids1 = torch.randint(0, n, (B, k1), generator=gen, device=DEV, dtype=torch.int32)
+    g = torch.ones((B, D), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(binding.fsa_mean_bwd_dense_workspace_bytes(B, k1, 0, D, n), dtype=torch.uint8, device=DEV)
+    grad = binding.fsa_mean_bwd_dense(g, ids1, grad_x=torch.empty((n, D), dtype=torch.bfloat16, device=DEV), workspace=ws)
+    terms = torch.bincount(ids1.flatten(), minlength=n).double().cpu().numpy()
+    roundings = int(1.05 * B * k1 / (n // rows_of_bin) / 256)            # (bins differ by 0.5 %)
+    # the i-th of r roundings meets a sum of about i/r of the whole: half a unit is 2^-8 of the power of two below it
+    sums = (terms / k1)[:, None] * (np.arange(1, roundings + 1) / roundings)
+    bound = (2.0 ** (np.floor(np.log2(sums)) - 8)).sum(1)
+    err = np.abs(to_f64(grad) - (terms / k1)[:, None]).max(1)
+    assert (err <= bound).all(), (err / bound).max()
+    assert bound.max() < 0.5 * (terms / k1).max()                       # and the bound says something
+
+
+def _skewed(name, n, shape):
+    """Leaf IDs, none of them a hole: `hub` a tenth on one row."""
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    leaf = torch.randint(0, n, shape, generator=gen, device=DEV, dtype=torch.int32)
+    if name == "hub":
+        leaf[torch.rand(shape, generator=gen, device=DEV) < 0.1] = n // 2
+    return leaf
+
+
+def _least_us(call, turns=7):
+    """Least time of a call on the GPU, the queue being full."""
+    call()
+    best = float("inf")
+    for _ in range(turns):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(1_000_000)                                    # the host is ahead when the timed part starts
+        start.record()
+        call()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end) * 1e3)
+    return best
+
+
+# Batches that once took 2 to 100 times as long on this route as clearing and adding with atomics, and now take less time:
+# a bound half-way between, far from what runs of either differ by.
+@pytest.mark.parametrize("skew,n,D,B,k1,k2", [
+    ("hub", 50000, 1000, 1024, 15, 10),
+])
+def test_skewed_batches_are_not_slower_than_clearing_and_adding(skew, n, D, B, k1, k2):
+    from paper_2511_13645_amd import binding
+    ids2 = _skewed(skew, n, (B, k1, k2))
+    ids1 = torch.zeros((B, k1), dtype=torch.int32, device=DEV)
+    g = torch.randn((B, D), generator=torch.Generator(device=DEV).manual_seed(8), device=DEV)
+    grad = torch.empty((n, D), device=DEV)
+    ws = torch.empty(binding.fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, n), dtype=torch.uint8, device=DEV)
+    dense = _least_us(lambda: binding.fsa_mean_bwd_dense(g, ids1, ids2, grad_x=grad, workspace=ws))
+    added = _least_us(lambda: binding.fsa_mean_bwd(g, ids1, ids2, grad_x=grad.zero_()))
+    assert dense <= 1.3 * added, "%.0f us against %.0f" % (dense, added)
