@@ -24,6 +24,8 @@
 namespace fsa {
 
 constexpr int kDenseThreads = 256;
+constexpr int kBinTile = 1024;
+constexpr int kBinWorkgroups = 256;                                  // one to a compute unit
 // Elements of a bin, and its rows: enough entries per workgroup to pay for its steps (clear counter to last store, 75,000
 // entries in 169,343 rows of 128 floats: 4096 elements 38.6 us, 8192 33.2, 16384 33.9; 590,000 entries 174 / 157 / 182),
 // and several rows per group of lanes where rows are wide (49,000 in 30,000 rows of 301 floats: 8 / 16 / 32 rows
@@ -107,21 +109,27 @@ __global__ __launch_bounds__(256) void dense_clear_kernel(int* counter, int bins
     if (i == 0) *tile_count = 0;
 }
 
-// A workgroup takes whole roots (one with two hops, as many seeds as have 256 leaf slots with one hop).  Bound by the
-// chain IDs -> place (a returning atomic) -> entry; four leaf slots per thread go through it together, and the slots are
-// counted while the places are on their way.
+// A workgroup takes whole roots, as many as have kBinTile leaf slots while there are workgroups enough.  Bound by the chain
+// IDs -> place (a returning atomic) -> entry, which four leaf slots per thread go through together; the slots are counted
+// on the way.  Leaf slots of one bin are merged in LDS before they ask for places: atomics on one address go through at
+// one per 11 ns, and a hub's bin is asked by every root (153,600 leaves of one row, the kernel alone: 1720 -> 11 us; without
+// hubs 9 us either way).  A bin that finds its two places of the table taken by others is asked directly.
+constexpr int kBinTable = 2048;
 __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DenseParams p) {
-    __shared__ int on[kDenseThreads];                                // slots_per_wg <= kDenseThreads
-    __shared__ int cnt[kDenseThreads];
+    __shared__ int on[kBinTile], cnt[kBinTile];                      // by slot: takes part; leaf slots that do
+    __shared__ int live[kBinTile];                                   // by root: slots that take part
+    __shared__ int tag[kBinTable], asked[kBinTable], got[kBinTable]; // bin; entries of it; the first one's place
     const int tid = threadIdx.x;
     const int64_t slot0 = (int64_t)blockIdx.x * p.slots_per_wg;
     const int n_slots = (int)(p.slots - slot0 < p.slots_per_wg ? p.slots - slot0 : p.slots_per_wg);
     const int32_t* leaf = p.leaf + slot0 * p.k2;
-    const int n_ent = n_slots * p.k2;                                // at most 64 * 64
-    if (tid < n_slots) on[tid] = p.ids1 ? p.ids1[slot0 + tid] : 0;
-    cnt[tid] = 0;
+    const int n_ent = n_slots * p.k2;                                // at most kBinTile, or one root's 64 * 64
+    for (int s = tid; s < n_slots; s += kDenseThreads) {
+        on[s] = p.ids1 ? p.ids1[slot0 + s] : 0;
+        cnt[s] = live[s] = 0;
+    }
     __syncthreads();
-    constexpr int U = 4;
+    constexpr int U = kBinTile / kDenseThreads;
     int id[U], slot[U], at[U];
     auto look = [&](int e0) {
 #pragma unroll
@@ -132,12 +140,42 @@ __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DensePar
             if (e >= n_ent || on[slot[k]] < 0) id[k] = -1;
         }
     };
-    auto place = [&] {
+    // the places of these entries, in two halves between which the table is complete
+    int h[U];
+    auto ask = [&] {
+        for (int i = tid; i < kBinTable; i += kDenseThreads) { tag[i] = -1; asked[i] = 0; }
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < U; ++k) at[k] = id[k] >= 0 ? atomicAdd(&p.counter[(size_t)(id[k] >> p.row_shift) * p.stride], 1) : 0;
+        for (int k = 0; k < U; ++k) {
+            h[k] = -1;
+            at[k] = 0;
+            if (id[k] < 0) continue;
+            const int bin = id[k] >> p.row_shift;
+            int t = (int)(((uint32_t)bin * 2654435761u) >> 21), was = atomicCAS(&tag[t], -1, bin);
+            if (was != -1 && was != bin) { t ^= 1; was = atomicCAS(&tag[t], -1, bin); }
+            if (was != -1 && was != bin) {
+                at[k] = atomicAdd(&p.counter[(size_t)bin * p.stride], 1);
+            } else {
+                h[k] = was == -1 ? t | kBinTable : t;                // the one that claimed it asks for all
+                at[k] = atomicAdd(&asked[t], 1);
+            }
+        }
+    };
+    auto place = [&] {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (h[k] >= kBinTable) {
+                const int t = h[k] & (kBinTable - 1);
+                got[t] = atomicAdd(&p.counter[(size_t)(id[k] >> p.row_shift) * p.stride], asked[t]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < U; ++k) { if (h[k] >= 0) at[k] += got[h[k] & (kBinTable - 1)]; }
     };
     look(tid);
-    place();
+    ask();
 #pragma unroll
     for (int k = 0; k < U; ++k) { if (id[k] >= 0) atomicAdd(&cnt[slot[k]], 1); }
     for (int e = tid + U * kDenseThreads; e < n_ent; e += kDenseThreads) {
@@ -145,14 +183,16 @@ __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DensePar
         if (on[j] >= 0 && leaf[e] >= 0) atomicAdd(&cnt[j], 1);
     }
     __syncthreads();
-    const int lane = tid & (kWave - 1);                              // two hops: the root's slots that take part (k1 <= 64)
-    const int c1 = p.ids1 ? __popcll(__ballot(lane < n_slots && cnt[lane] > 0)) : 1;
+    for (int s = tid; s < n_slots; s += kDenseThreads) { if (cnt[s] > 0) atomicAdd(&live[s / p.k1], 1); }
+    place();
+    const int lane = tid & (kWave - 1);
+    const int64_t root0 = slot0 / p.k1;
     for (int e0 = tid;;) {
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int bin = id[k] >> p.row_shift;
-            const int64_t root = p.ids1 ? (int64_t)blockIdx.x : slot0 + slot[k];
-            const Entry e = Entry::of(id[k] & ((1 << p.row_shift) - 1), root, p.ids1 ? slot[k] : 0, c1, cnt[slot[k]]);
+            const int of = slot[k] / p.k1;                           // its root
+            const Entry e = Entry::of(id[k] & ((1 << p.row_shift) - 1), root0 + of, slot[k] - of * p.k1, live[of], cnt[slot[k]]);
             if (id[k] >= 0 && at[k] < p.room) p.entries[(size_t)bin * p.room + at[k]] = e.v;
             const bool over = id[k] >= 0 && at[k] >= p.room;
             const uint64_t all = __ballot(over);
@@ -179,6 +219,8 @@ __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DensePar
         e0 += U * kDenseThreads;
         if (e0 - tid >= n_ent) break;                                // workgroup-uniform
         look(e0);
+        __syncthreads();                                             // the table's last readers
+        ask();
         place();
     }
 }
@@ -416,8 +458,14 @@ __global__ __launch_bounds__(kDenseThreads) void dense_write_kernel(const DenseP
     }
 }
 
+// Slots that a binning workgroup takes: those of whole roots (one hop: k1 = 1, a seed is a slot).
+static int slots_of_workgroup(int64_t B, int k1, int k2) {
+    const int64_t most = kBinTile / (k1 * k2), fair = B / kBinWorkgroups, roots = most < fair ? most : fair;
+    return k1 * (int)(roots > 1 ? roots : 1);
+}
+
 static DensePlan dense_plan_of(int64_t B, int k1, int k2, int64_t D, int64_t N) {
-    return k2 > 0 ? dense_plan(B * k1, k2, k1, D, N) : dense_plan(B, k1, kDenseThreads / k1, D, N);
+    return k2 > 0 ? dense_plan(B * k1, k2, slots_of_workgroup(B, k1, k2), D, N) : dense_plan(B, k1, slots_of_workgroup(B, 1, k1), D, N);
 }
 
 static bool dense_shape_ok(int64_t B, int k1, int k2, int64_t D, int64_t N) {
@@ -472,7 +520,7 @@ hipError_t launch_backward_dense(const BwdArgs& a, int64_t N, void* workspace, s
     p.ids1 = two ? a.ids1 : nullptr; p.leaf = two ? a.ids2 : a.ids1;
     p.grad_x = a.grad_x; p.slots = two ? a.B * a.k1 : a.B; p.N = N; p.D = (int)a.D;
     p.k1 = two ? a.k1 : 1; p.k2 = two ? a.k2 : a.k1;
-    p.slots_per_wg = two ? a.k1 : kDenseThreads / a.k1;
+    p.slots_per_wg = two ? slots_of_workgroup(a.B, a.k1, a.k2) : slots_of_workgroup(a.B, 1, a.k1);
     const DensePlan q = dense_plan_of(a.B, a.k1, two ? a.k2 : 0, a.D, N);
     if (workspace_bytes < q.total) return hipErrorInvalidValue;
     char* w = static_cast<char*>(workspace);

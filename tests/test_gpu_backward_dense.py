@@ -169,9 +169,11 @@ def test_16bit_rows_of_full_bins_are_rounded_once_in_256_entries():
 
 
 def _skewed(name, n, shape):
-    """Leaf IDs, none of them a hole: `hub` a tenth on one row."""
+    """Leaf IDs, none of them a hole: `hub` a tenth on one row, `star` all."""
     gen = torch.Generator(device=DEV).manual_seed(7)
     leaf = torch.randint(0, n, shape, generator=gen, device=DEV, dtype=torch.int32)
+    if name == "star":
+        leaf.fill_(n // 2)
     if name == "hub":
         leaf[torch.rand(shape, generator=gen, device=DEV) < 0.1] = n // 2
     return leaf
@@ -196,6 +198,8 @@ def _least_us(call, turns=7):
 # a bound half-way between, far from what runs of either differ by.
 @pytest.mark.parametrize("skew,n,D,B,k1,k2", [
     ("hub", 50000, 1000, 1024, 15, 10),
+    ("star", 100000, 128, 1024, 15, 10),
+    ("hub", 200000, 20, 4096, 15, 10),
 ])
 def test_skewed_batches_are_not_slower_than_clearing_and_adding(skew, n, D, B, k1, k2):
     from paper_2511_13645_amd import binding
