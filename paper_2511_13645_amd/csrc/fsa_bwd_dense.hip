@@ -31,8 +31,15 @@ constexpr int kBinWorkgroups = 256;                                  // one to a
 // and several rows per group of lanes where rows are wide (49,000 in 30,000 rows of 301 floats: 8 / 16 / 32 rows
 // 77 / 54 / 38).  Several bins per workgroup, the next one's entries requested ahead: 2 to 8 % slower on large tables.
 constexpr int kDenseBinElements = 8192;
-constexpr int kDenseRowsMin = 32;                                    // (bins start at multiples of 16 bytes of grad_x, whatever D)
+constexpr int kDenseRowsMin = 32;
 constexpr int kDenseRowsMax = 256;
+// Fewer rows where a bin would have more leaf slots: a workgroup's 256 entries are one pass, and rows that meet again in
+// the next one are read back, one trip to memory after the other.  20,000 rows of 64 floats, 256,000 slots (68 % live): 128 rows
+// to a bin 65 us, 16 28; 1.25 M slots 270, 89; 8 rows are slower where hub rows lie side by side (169,343 rows sorted by
+// degree, 2 M slots: 146 us with 16, 209 with 8).  With half the line nearly empty tables lose: 2 M rows of 64 floats, 2 M
+// slots, a tenth live: 150 us at 64 rows to a bin, 182 at 32.
+constexpr int64_t kDenseLoad = 128;
+constexpr int kDenseRowsLoaded = 16;
 // Room of a bin at most: longer is a longer chain for one workgroup, shorter leaves more of an evenly loaded batch to the
 // lists (16 M leaf slots, 28 % live, on 169,343 rows of 128 floats: 512 1260 us, 1024 974, 2048 788, the longest bin 82 us).
 constexpr int kDenseMostRoom = 2048;
@@ -80,6 +87,7 @@ static DensePlan dense_plan(int64_t slots, int k2, int slots_per_wg, int64_t D, 
     DensePlan q{};
     while ((2ll << q.row_shift) <= kDenseRowsMax && (2ll << q.row_shift) * D <= kDenseBinElements) ++q.row_shift;
     while ((1 << q.row_shift) < kDenseRowsMin) ++q.row_shift;
+    while ((1 << q.row_shift) > kDenseRowsLoaded && slots * k2 / ((N >> q.row_shift) + 1) > kDenseLoad) --q.row_shift;
     q.bins = (N + (1ll << q.row_shift) - 1) >> q.row_shift;
     // room for four times the mean with every slot full, while that is no long chain for the bin's workgroup
     const int64_t leaves = slots * k2, mean = leaves / q.bins;
@@ -211,7 +219,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_bin_kernel(const DensePar
                     p.tile_of[bin] = t;
                 }
                 t = __shfl(t, from);
-                const size_t n = (size_t)p.D << p.row_shift;         // a multiple of 32
+                const size_t n = (size_t)p.D << p.row_shift;         // a multiple of 16
                 float4* const tile = reinterpret_cast<float4*>(p.tiles + (size_t)t * n);
                 for (size_t i = lane; i < n / 4; i += kWave) tile[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }

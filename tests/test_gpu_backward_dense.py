@@ -169,9 +169,11 @@ def test_16bit_rows_of_full_bins_are_rounded_once_in_256_entries():
 
 
 def _skewed(name, n, shape):
-    """Leaf IDs, none of them a hole: `hub` a tenth on one row, `star` all."""
+    """Leaf IDs, none of them a hole: `hub` a tenth on one row, `star` all, `front` nine tenths on the first hundredth."""
     gen = torch.Generator(device=DEV).manual_seed(7)
     leaf = torch.randint(0, n, shape, generator=gen, device=DEV, dtype=torch.int32)
+    if name == "front":
+        leaf = torch.where(torch.rand(shape, generator=gen, device=DEV) < 0.9, leaf // 100, leaf)
     if name == "star":
         leaf.fill_(n // 2)
     if name == "hub":
@@ -200,6 +202,9 @@ def _least_us(call, turns=7):
     ("hub", 50000, 1000, 1024, 15, 10),
     ("star", 100000, 128, 1024, 15, 10),
     ("hub", 200000, 20, 4096, 15, 10),
+    ("even", 20000, 64, 5000, 25, 10),
+    ("even", 10000, 64, 8192, 15, 10),
+    ("front", 20000, 128, 2048, 25, 10),
 ])
 def test_skewed_batches_are_not_slower_than_clearing_and_adding(skew, n, D, B, k1, k2):
     from paper_2511_13645_amd import binding
