@@ -493,9 +493,12 @@ size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
 // 256,000 slots (29 %) 58 -> 33 us, 16,000 21.4 / 20-22, 2 M 320 -> 157; of 128 bf16 elements 256,000 slots 38 -> 30; 500,000 rows of
 // 64 floats, 300,000 slots (80 %) 79 -> 47; 2.4 M rows of 100 floats, 153,600 slots 233 -> 203; not taken: 10,000 rows of 64 floats,
 // 10,240 slots 9 / 15; 1 M rows of 640 floats, 30,720 slots 428 / 496; of 32 fp16 elements, 307,200 slots 31 / 35.
+// One hop is left to the atomics, which sum the rows that seeds of a workgroup share in LDS: 15,000 entities x 128 floats,
+// 16,384 x 15 leaf slots of a knowledge graph (46 % live) 57 us that way and 85 this, all leaves on one row 35 / 49, where a
+// graph without such hubs (500,000 x 64, 30,000 x 10, 80 % live) would be 79 / 49.
 bool dense_pays(int64_t B, int k1, int k2, int64_t D, int elem_bytes, int64_t N) {
-    if (!dense_shape_ok(B, k1, k2, D, N)) return false;
-    const int64_t leaves = B * k1 * (k2 > 0 ? k2 : 1);
+    if (k2 == 0 || !dense_shape_ok(B, k1, k2, D, N)) return false;
+    const int64_t leaves = B * k1 * k2;
     const int64_t segments = leaves * ((D * elem_bytes + 63) / 64);
     return segments >= kDenseMinSegments && leaves * kDenseMaxRowsPerSlot >= N;
 }

@@ -1,0 +1,26 @@
+"""Which calls the autograd function's table gradient takes row by row: the rule's lines (fsa_mean_bwd_dense_pays), from both
+sides.  The library's host code answers; no GPU."""
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def pays():
+    from paper_2511_13645_amd import binding, build
+    if build.is_stale():
+        build.build_hip()
+    return lambda B, k1, k2, D, dtype, n: binding.fsa_mean_bwd_dense_pays(B, k1, k2, D, dtype, n)
+
+
+F32, BF16 = torch.float32, torch.bfloat16
+
+
+def test_two_hops_on_a_table_that_the_batch_covers(pays):
+    assert pays(1024, 25, 10, 128, F32, 169343) and pays(1024, 25, 10, 128, BF16, 169343)
+    assert pays(65536, 25, 10, 128, F32, 169343) and pays(8192, 15, 10, 100, F32, 2449029)
+    assert not pays(64, 25, 10, 128, F32, 169343)
+
+
+@pytest.mark.parametrize("B,k,D,n", [(16384, 15, 128, 15000), (65536, 30, 16, 10000), (30000, 10, 64, 500000)])
+def test_one_hop_is_left_to_the_atomics(pays, B, k, D, n):
+    assert not pays(B, k, 0, D, F32, n)
