@@ -47,7 +47,7 @@ constexpr int kRestLists = 32;                                       // of entri
                                                                      // atomic on its list's length, one per 11 ns on one address
 constexpr int kCountStride = 2 * kSegment;                           // ints between their lengths: a 128-byte line each
 constexpr int64_t kDenseMinSegments = 768 * 1024;                   // see dense_pays
-constexpr int64_t kDenseMaxRowsPerSlot = 16;
+constexpr int64_t kDenseMaxRowsPerSlot = 2;
 constexpr int64_t kDenseMaxD = 1024;                                 // 16 KB of LDS at four groups
 
 struct DenseParams {
@@ -490,9 +490,11 @@ size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
 // Against clearing and atomics, which take 48 ps per 64-byte segment of a leaf's row (20.8 G/s), with the dearer launches of
 // this one to be made up for, and the rows of a table that is hardly touched, which a fill writes at 6.6 TB/s and this
 // at 5.2.  Both ways, backward alone, by leaf slots and the share of them that has an ID: 169,343 rows of 128 floats,
-// 256,000 slots (29 %) 58 -> 33 us, 16,000 21.4 / 20-22, 2 M 320 -> 157; of 128 bf16 elements 256,000 slots 38 -> 30; 500,000 rows of
-// 64 floats, 300,000 slots (80 %) 79 -> 47; 2.4 M rows of 100 floats, 153,600 slots 233 -> 203; not taken: 10,000 rows of 64 floats,
-// 10,240 slots 9 / 15; 1 M rows of 640 floats, 30,720 slots 428 / 496; of 32 fp16 elements, 307,200 slots 31 / 35.
+// 256,000 slots (29 %) 57 / 37 us, 100,000 33 / 27, 2 M 305 / 114; as bf16 256,000 36 / 34; 2.4 M rows of 100 floats, 1.2 M slots
+// (96 %) 599 / 380; not taken: 50,000 slots on the 169,343 rows 26 / 25.
+// Rows that nothing names are the line of the rows: with 256,000 slots on rows of 128 floats and 13 / 30 / 100 % of them live,
+// two rows a slot 52 / 70 / 140 against 51 / 57 / 66 us, four 105 / 124 / 191 against 121 / 121 / 121.  (Below a tenth live
+// it is behind whatever the rows: 5 % on half a row, one and two rows a slot 22 / 29 / 45 against 23 / 32 / 53.)
 // One hop is left to the atomics, which sum the rows that seeds of a workgroup share in LDS: 15,000 entities x 128 floats,
 // 16,384 x 15 leaf slots of a knowledge graph (46 % live) 57 us that way and 85 this, all leaves on one row 35 / 49, where a
 // graph without such hubs (500,000 x 64, 30,000 x 10, 80 % live) would be 79 / 49.

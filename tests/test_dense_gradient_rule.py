@@ -24,3 +24,8 @@ def test_two_hops_on_a_table_that_the_batch_covers(pays):
 @pytest.mark.parametrize("B,k,D,n", [(16384, 15, 128, 15000), (65536, 30, 16, 10000), (30000, 10, 64, 500000)])
 def test_one_hop_is_left_to_the_atomics(pays, B, k, D, n):
     assert not pays(B, k, 0, D, F32, n)
+
+
+@pytest.mark.parametrize("rows_per_slot,taken", [(0.5, True), (2, True), (2.5, False), (10, False)])
+def test_tables_of_mostly_unnamed_rows_are_left_to_the_fill(pays, rows_per_slot, taken):
+    assert pays(1024, 25, 10, 128, F32, int(256000 * rows_per_slot)) == taken
