@@ -212,7 +212,8 @@ int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype
  * Requires a workspace (contents irrelevant on entry, overwritten) of fsa_mean_bwd_dense_workspace_bytes
  * (k2 = 0 for one hop), 256-byte aligned, and grad_x 16-byte aligned.  That size is 0 where the call is not
  * available (more than 1024 elements to a row, for one) and answers FSA_ERR_ARG; ..._pays is 1 where it is expected to
- * be faster than clearing grad_x and fsa_mean_bwd or fsa_mean_bwd_lp: large batches on tables not much larger.
+ * be faster than clearing grad_x and fsa_mean_bwd or fsa_mean_bwd_lp: large 2-hop batches, tables of thousands of rows and
+ * not many more than leaf slots.
  */
 int64_t fsa_mean_bwd_dense_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int64_t num_nodes);
 int fsa_mean_bwd_dense_pays(int64_t B, int32_t k1, int32_t k2, int64_t D, int dtype, int64_t num_nodes);

@@ -48,6 +48,9 @@ constexpr int kRestLists = 32;                                       // of entri
 constexpr int kCountStride = 2 * kSegment;                           // ints between their lengths: a 128-byte line each
 constexpr int64_t kDenseMinSegments = 768 * 1024;                   // see dense_pays
 constexpr int64_t kDenseMaxRowsPerSlot = 2;
+constexpr int64_t kDenseMinRowBytes = 256;
+constexpr int64_t kDenseMinBins = 512;
+constexpr int64_t kDenseMostLoad = 4096;                            // leaf slots to a bin
 constexpr int64_t kDenseMaxD = 1024;                                 // 16 KB of LDS at four groups
 
 struct DenseParams {
@@ -495,6 +498,9 @@ size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
 // Rows that nothing names are the line of the rows: with 256,000 slots on rows of 128 floats and 13 / 30 / 100 % of them live,
 // two rows a slot 52 / 70 / 140 against 51 / 57 / 66 us, four 105 / 124 / 191 against 121 / 121 / 121.  (Below a tenth live
 // it is behind whatever the rows: 5 % on half a row, one and two rows a slot 22 / 29 / 45 against 23 / 32 / 53.)
+// Few bins leave the chip idle, long ones are a chain, and narrow rows cost the atomics least: 300 rows of 128 floats, 153,600
+// slots (80 %) 59 / 81 us, 2100 of 64, 256,000 65 / 67; 4000 of 32, 2 M slots, 8192 to a bin, 260 / 404, at 4096 8000 rows 265 / 261,
+// of 64 floats 449 / 255; 200,000 rows of 16 floats, 1.2 M slots 57 / 74, 1 M of 24, 512,000 34 / 45.
 // One hop is left to the atomics, which sum the rows that seeds of a workgroup share in LDS: 15,000 entities x 128 floats,
 // 16,384 x 15 leaf slots of a knowledge graph (46 % live) 57 us that way and 85 this, all leaves on one row 35 / 49, where a
 // graph without such hubs (500,000 x 64, 30,000 x 10, 80 % live) would be 79 / 49.
@@ -502,7 +508,9 @@ bool dense_pays(int64_t B, int k1, int k2, int64_t D, int elem_bytes, int64_t N)
     if (k2 == 0 || !dense_shape_ok(B, k1, k2, D, N)) return false;
     const int64_t leaves = B * k1 * k2;
     const int64_t segments = leaves * ((D * elem_bytes + 63) / 64);
-    return segments >= kDenseMinSegments && leaves * kDenseMaxRowsPerSlot >= N;
+    const int64_t bins = dense_plan_of(B, k1, k2, D, N).bins;
+    return segments >= kDenseMinSegments && leaves * kDenseMaxRowsPerSlot >= N && D * elem_bytes >= kDenseMinRowBytes &&
+           bins >= kDenseMinBins && leaves <= bins * kDenseMostLoad;
 }
 
 template <typename GT> static hipError_t launch_dense(const DenseParams& p, hipStream_t stream) {

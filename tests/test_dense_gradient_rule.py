@@ -29,3 +29,16 @@ def test_one_hop_is_left_to_the_atomics(pays, B, k, D, n):
 @pytest.mark.parametrize("rows_per_slot,taken", [(0.5, True), (2, True), (2.5, False), (10, False)])
 def test_tables_of_mostly_unnamed_rows_are_left_to_the_fill(pays, rows_per_slot, taken):
     assert pays(1024, 25, 10, 128, F32, int(256000 * rows_per_slot)) == taken
+
+
+@pytest.mark.parametrize("B,k1,k2,D,n,taken", [
+    (1024, 15, 10, 128, 300, False),                                    # nineteen bins
+    (1024, 25, 10, 64, 2100, False),
+    (1024, 25, 10, 64, 20000, True),
+    (8192, 25, 10, 64, 20000, True),
+    (65536, 25, 10, 64, 20000, False),                                  # 13,000 slots to a bin
+    (8192, 15, 10, 32, 20000, False),                                   # rows of 128 bytes
+    (65536, 30, 10, 16, 10000, False),
+])
+def test_small_tables_and_narrow_rows_are_left_to_the_atomics(pays, B, k1, k2, D, n, taken):
+    assert pays(B, k1, k2, D, F32, n) == taken
