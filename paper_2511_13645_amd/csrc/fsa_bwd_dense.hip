@@ -47,6 +47,7 @@ constexpr int kRestLists = 32;                                       // of entri
                                                                      // atomic on its list's length, one per 11 ns on one address
 constexpr int kCountStride = 2 * kSegment;                           // ints between their lengths: a 128-byte line each
 constexpr int64_t kDenseMinSegments = 768 * 1024;                   // see dense_pays
+constexpr int64_t kDenseMinSegmentsSingles = 8 * 1024 * 1024;
 constexpr int64_t kDenseMaxRowsPerSlot = 2;
 constexpr int64_t kDenseMinRowBytes = 256;
 constexpr int64_t kDenseMinBins = 512;
@@ -501,6 +502,10 @@ size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
 // Few bins leave the chip idle, long ones are a chain, and narrow rows cost the atomics least: 300 rows of 128 floats, 153,600
 // slots (80 %) 59 / 81 us, 2100 of 64, 256,000 65 / 67; 4000 of 32, 2 M slots, 8192 to a bin, 260 / 404, at 4096 8000 rows 265 / 261,
 // of 64 floats 449 / 255; 200,000 rows of 16 floats, 1.2 M slots 57 / 74, 1 M of 24, 512,000 34 / 45.
+// Rows that are not made of quads go through the write kernel one element a lane, so a bin of hub rows is a chain four times as
+// long, which only a large call hides.  With rows sorted by degree, 301 floats on 30,000 rows, 1.6 / 3.4 / 13.5 M segments
+// 65 / 116 / 386 against 121 / 112 / 416 us; 602 floats on 60,000 1.5 / 6.4 / 12.8 M 75 / 202 / 358 against 135 / 276 / 307;
+// in no order (602 on 232,965, 9.5 M) 590 / 258.
 // One hop is left to the atomics, which sum the rows that seeds of a workgroup share in LDS: 15,000 entities x 128 floats,
 // 16,384 x 15 leaf slots of a knowledge graph (46 % live) 57 us that way and 85 this, all leaves on one row 35 / 49, where a
 // graph without such hubs (500,000 x 64, 30,000 x 10, 80 % live) would be 79 / 49.
@@ -509,7 +514,7 @@ bool dense_pays(int64_t B, int k1, int k2, int64_t D, int elem_bytes, int64_t N)
     const int64_t leaves = B * k1 * k2;
     const int64_t segments = leaves * ((D * elem_bytes + 63) / 64);
     const int64_t bins = dense_plan_of(B, k1, k2, D, N).bins;
-    return segments >= kDenseMinSegments && leaves * kDenseMaxRowsPerSlot >= N && D * elem_bytes >= kDenseMinRowBytes &&
+    return segments >= (D % 4 == 0 ? kDenseMinSegments : kDenseMinSegmentsSingles) && leaves * kDenseMaxRowsPerSlot >= N && D * elem_bytes >= kDenseMinRowBytes &&
            bins >= kDenseMinBins && leaves <= bins * kDenseMostLoad;
 }
 

@@ -42,3 +42,8 @@ def test_tables_of_mostly_unnamed_rows_are_left_to_the_fill(pays, rows_per_slot,
 ])
 def test_small_tables_and_narrow_rows_are_left_to_the_atomics(pays, B, k1, k2, D, n, taken):
     assert pays(B, k1, k2, D, F32, n) == taken
+
+
+@pytest.mark.parametrize("B,D,n,taken", [(555, 300, 30000, True), (555, 301, 30000, False), (1024, 602, 232965, True), (270, 602, 60000, False)])
+def test_rows_that_are_not_made_of_quads_need_a_larger_call(pays, B, D, n, taken):
+    assert pays(B, 25, 10, D, F32, n) == taken
