@@ -259,7 +259,7 @@ int fsa_mean_bwd_lp_ws(const void* grad_out, const void* grad_h1, int grad_dtype
 }
 
 int64_t fsa_mean_bwd_dense_workspace_bytes(int64_t B, int32_t k1, int32_t k2, int64_t D, int64_t num_nodes) {
-    if (B <= 0 || D <= 0 || num_nodes <= 0 || !fanout_ok(k1) || k2 < 0 || (k2 > 0 && !fanout_ok(k2))) return 0;
+    if (B <= 0 || check_common(FSA_F32, D, num_nodes, B) != FSA_OK || !fanout_ok(k1) || k2 < 0 || (k2 > 0 && !fanout_ok(k2))) return 0;
     return (int64_t)fsa::dense_workspace_bytes(B, k1, k2, D, num_nodes);
 }
 

@@ -47,3 +47,11 @@ def test_small_tables_and_narrow_rows_are_left_to_the_atomics(pays, B, k1, k2, D
 @pytest.mark.parametrize("B,D,n,taken", [(555, 300, 30000, True), (555, 301, 30000, False), (1024, 602, 232965, True), (270, 602, 60000, False)])
 def test_rows_that_are_not_made_of_quads_need_a_larger_call(pays, B, D, n, taken):
     assert pays(B, 25, 10, D, F32, n) == taken
+
+
+@pytest.mark.parametrize("B,k1,k2,n", [(2 ** 60, 64, 64, 1000), (2 ** 62, 4, 0, 1000), (2 ** 63 - 1, 1, 1, 1), (16, 4, 4, 2 ** 31), (16, 4, 4, 2 ** 62)])
+def test_no_workspace_for_sizes_that_the_call_refuses(pays, B, k1, k2, n):
+    """Products of such sizes leave 64 bits; the call itself answers FSA_ERR_ARG."""
+    from paper_2511_13645_amd import binding
+    assert binding.fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, 8, n) == 0
+    assert not pays(B, k1, k2, 64, F32, n)
