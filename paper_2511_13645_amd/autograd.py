@@ -69,6 +69,8 @@ class _FusedSampleMean(torch.autograd.Function):
         else:
             owned = d % 2 != 0
         if not owned:
+            if ctx.workspace is not None and ctx.x_dtype == torch.float32:
+                binding.check_workspace(ctx.workspace, g_out)       # unused here, and refused all the same if it is no workspace
             if g_out.dtype is not ctx.x_dtype:
                 g_out = g_out.to(ctx.x_dtype)
             if gh is not None and gh.dtype is not ctx.x_dtype:

@@ -199,12 +199,17 @@ def _taken(r, name: str) -> bool:
     return True
 
 
+def check_workspace(workspace: torch.Tensor, like: torch.Tensor) -> None:
+    """Raises unless `workspace` can serve a call on `like`'s device."""
+    _need(workspace, "workspace")
+    _same_device(like, (workspace, "workspace"))
+
+
 def _room(workspace: Optional[torch.Tensor], like: torch.Tensor) -> Tuple[Optional[int], int]:
     """(address, bytes) of the workspace a caller hands to a backward call; (None, 0) without one."""
     if workspace is None:
         return None, 0
-    _need(workspace, "workspace")
-    _same_device(like, (workspace, "workspace"))
+    check_workspace(workspace, like)
     return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 

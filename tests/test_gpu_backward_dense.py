@@ -216,3 +216,23 @@ def test_skewed_batches_are_not_slower_than_clearing_and_adding(skew, n, D, B, k
     dense = _least_us(lambda: binding.fsa_mean_bwd_dense(g, ids1, ids2, grad_x=grad, workspace=ws))
     added = _least_us(lambda: binding.fsa_mean_bwd(g, ids1, ids2, grad_x=grad.zero_()))
     assert dense <= 1.3 * added, "%.0f us against %.0f" % (dense, added)
+
+
+@pytest.mark.parametrize("workspace", [lambda: torch.empty(1 << 20, dtype=torch.uint8),
+                                       lambda: torch.empty((1 << 10, 1 << 10), dtype=torch.uint8, device=DEV).t()])
+def test_autograd_refuses_what_is_no_workspace_on_every_route(workspace):
+    """A host tensor and one that is not contiguous, with a call for the dense route and one for the atomics."""
+    from paper_2511_13645_amd import binding
+    from paper_2511_13645_amd.autograd import fused_sample_mean
+    n, D, fan = 20000, 64, [25, 10]
+    assert binding.fsa_mean_bwd_workspace_bytes(1024, *fan, D) == 0    # else the sorted route takes the call
+    indptr = torch.arange(0, 5 * n + 1, 5, dtype=torch.int32, device=DEV)
+    indices = torch.randint(0, n, (5 * n,), dtype=torch.int32, device=DEV)
+    for B in (1024, 8):
+        assert binding.fsa_mean_bwd_dense_pays(B, *fan, D, torch.float32, n) == (B > 8)
+        x = torch.nn.Parameter(torch.randn((n, D), device=DEV))
+        seeds = torch.arange(B, dtype=torch.int32, device=DEV)
+        out, _, _, _ = fused_sample_mean(x, indptr, indices, seeds, fan, 1, workspace=workspace())
+        with pytest.raises(ValueError):
+            out.sum().backward()
+        assert x.grad is None
