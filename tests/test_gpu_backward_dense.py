@@ -4,13 +4,24 @@ import numpy as np
 import pytest
 import torch
 
-from parity_util import assert_close, to_f64
+from parity_util import assert_close, marked_workspace, to_f64, workspace_route
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 # fp32: sums of fp32 terms (the other backwards' bound); 16 bits: the same sum rounded, by 2^-8 or 2^-11 at most, once per
-# 256 leaves of the row's bin (the hub's row is the only one here whose bin has more than 256)
+# 256 leaves of the row's bin (_roundings)
 TOL = {torch.float32: 1e-5, torch.bfloat16: 2.0 ** -8 + 1e-5, torch.float16: 2.0 ** -11 + 1e-5}
+
+
+def _roundings(ids1, ids2, n, D):
+    """How often a 16-bit row is rounded at most, [n,1]: a bin is a run of rows that starts at a multiple of its length, this
+    one or a half, a quarter ... of it."""
+    rows = 256
+    while rows > 32 and rows * D > 8192:
+        rows //= 2
+    leaf = ids1 if ids2 is None else np.where(ids1[..., None] >= 0, ids2, -1)
+    in_bin = np.bincount(leaf[leaf >= 0].ravel() // rows, minlength=-(-n // rows))
+    return np.maximum(1, -(-in_bin // 256)).repeat(rows)[:n, None]
 
 
 def _ids(rng, n, B, k1, k2, hub):
@@ -25,21 +36,26 @@ def _ids(rng, n, B, k1, k2, hub):
     return ids1, ids2
 
 
-@pytest.mark.parametrize("n,D,B,k1,k2,dtype,slot_grads,hub", [
-    (1, 1, 1, 1, 0, torch.float32, False, 0.0),
-    (2000, 128, 300, 15, 10, torch.float32, False, 0.05),
-    (2000, 128, 300, 15, 10, torch.float32, True, 0.05),
-    (5001, 37, 257, 7, 3, torch.float32, True, 0.3),                   # odd rows, a last bin that is not full
-    (5001, 300, 64, 64, 5, torch.float32, False, 0.9),                 # a bin far beyond its room
-    (70001, 17, 9, 3, 2, torch.float32, True, 0.0),                    # nearly every bin empty, many counters
-    (999, 1024, 40, 5, 4, torch.float32, True, 0.1),                   # the widest row, eight to a bin
-    (1000, 64, 1024, 10, 0, torch.float32, False, 0.1),
-    (777, 5, 1001, 64, 0, torch.float32, False, 0.5),
-    (2000, 128, 300, 15, 10, torch.bfloat16, True, 0.05),
-    (3003, 33, 130, 6, 64, torch.float16, True, 0.1),
-    (3003, 601, 130, 25, 0, torch.bfloat16, False, 0.1),
+@pytest.mark.parametrize("n,D,B,k1,k2,dtype,slot_grads,hub,single_rounding", [
+    (1, 1, 1, 1, 0, torch.float32, False, 0.0, None),
+    (2000, 128, 300, 15, 10, torch.float32, False, 0.05, None),
+    (2000, 128, 300, 15, 10, torch.float32, True, 0.05, None),
+    (5001, 37, 257, 7, 3, torch.float32, True, 0.3, None),             # odd rows, a last bin that is not full
+    (5001, 300, 64, 64, 5, torch.float32, False, 0.9, None),           # a bin far beyond its room
+    (70001, 17, 9, 3, 2, torch.float32, True, 0.0, None),              # nearly every bin empty, many counters
+    (999, 1024, 40, 5, 4, torch.float32, True, 0.1, None),             # the widest row, 32 to a bin
+    (1000, 64, 1024, 10, 0, torch.float32, False, 0.1, None),
+    (777, 5, 1001, 64, 0, torch.float32, False, 0.5, None),            # every bin beyond its room
+    (40000, 12, 2500, 3, 2, torch.float32, True, 0.02, None),          # workgroups of the binning that take many roots
+    (150, 20, 40, 64, 64, torch.float32, True, 0.2, None),             # and of one root of 4096 leaf slots
+    (20000, 128, 300, 15, 10, torch.bfloat16, True, 0.0, True),
+    (20011, 33, 300, 6, 3, torch.float16, True, 0.0, True),
+    (2000, 128, 300, 15, 10, torch.bfloat16, True, 0.05, False),
+    (3003, 33, 130, 6, 64, torch.float16, True, 0.1, False),
+    (3003, 601, 130, 25, 0, torch.bfloat16, False, 0.1, False),
+    (777, 5, 1001, 64, 0, torch.bfloat16, False, 0.5, False),
 ])
-def test_dense_backward_matches_the_oracle(orc, n, D, B, k1, k2, dtype, slot_grads, hub):
+def test_dense_backward_matches_the_oracle(orc, n, D, B, k1, k2, dtype, slot_grads, hub, single_rounding):
     from paper_2511_13645_amd import binding
     rng = np.random.default_rng(n + D)
     ids1, ids2 = _ids(rng, n, B, k1, k2, hub)
@@ -57,11 +73,9 @@ def test_dense_backward_matches_the_oracle(orc, n, D, B, k1, k2, dtype, slot_gra
     ref = orc.mean_bwd(to_f64(g), ids1, ids2, None if gh is None else to_f64(gh), num_nodes=n)
     scale = orc.mean_bwd(np.abs(to_f64(g)), ids1, ids2, None if gh is None else np.abs(to_f64(gh)), num_nodes=n)
     if dtype != torch.float32:
-        leaf = ids1 if ids2 is None else np.where(ids1[..., None] >= 0, ids2, -1)
-        per_row = np.bincount(leaf[leaf >= 0].ravel(), minlength=n)
-        near = max(32, min(256, 8192 // D))                              # rows that can share a bin with it
-        in_bin = np.convolve(per_row, np.ones(2 * near + 1, dtype=np.int64), "same")
-        scale = scale * (1 + in_bin // 256 + (in_bin > 256))[:, None]
+        roundings = _roundings(ids1, ids2, n, D)
+        assert single_rounding is None or (roundings.max() == 1) == single_rounding
+        scale = scale * roundings
     # fp16: results below the smallest normal number are spaced 2^-24
     assert_close(to_f64(whole[:n * D].view(n, D)), ref, scale + (2.0 ** -12 if dtype == torch.float16 else 0.0), TOL[dtype],
                  "dense backward n=%d D=%d" % (n, D))
@@ -236,3 +250,118 @@ def test_autograd_refuses_what_is_no_workspace_on_every_route(workspace):
         with pytest.raises(ValueError):
             out.sum().backward()
         assert x.grad is None
+
+
+def test_gradients_off_a_quads_alignment_give_the_same(orc):
+    """Rows of whole quads at an odd address: one element a lane instead of four."""
+    from paper_2511_13645_amd import binding
+    n, D, B, k1, k2 = 3000, 64, 200, 6, 5
+    rng = np.random.default_rng(4)
+    ids1, ids2 = _ids(rng, n, B, k1, k2, 0.2)
+    off = lambda *shape: torch.randn(int(np.prod(shape)) + 1, device=DEV)[1:].view(shape)
+    g, gh = off(B, D), off(B, k1, D)
+    assert g.data_ptr() % 16 == 4 and gh.data_ptr() % 16 == 4
+    ws = torch.empty(binding.fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, n), dtype=torch.uint8, device=DEV)
+    d = lambda a: torch.from_numpy(a).to(DEV)
+    got = binding.fsa_mean_bwd_dense(g, d(ids1), d(ids2), gh, grad_x=torch.empty((n, D), device=DEV), workspace=ws)
+    ref = orc.mean_bwd(to_f64(g), ids1, ids2, to_f64(gh), num_nodes=n)
+    scale = orc.mean_bwd(np.abs(to_f64(g)), ids1, ids2, np.abs(to_f64(gh)), num_nodes=n)
+    assert_close(to_f64(got), ref, scale, 1e-5, "gradients off alignment")
+
+
+def _table_case(n, D, B, dtype, seed, skew=3):
+    """A graph, a table and seeds of two hops with fanouts 25 and 10; with a skew some rows are named often."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 30, size=n)
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    indices = (n * rng.random(int(indptr[-1])) ** skew).astype(np.int32)
+    d = lambda a: torch.from_numpy(a).to(DEV)
+    x = torch.nn.Parameter(torch.randn((n, D), device=DEV).to(dtype))
+    return x, (d(indptr), d(indices), d(rng.integers(0, n, B).astype(np.int32)), [25, 10], 7)
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("dtype,D", [(torch.float32, 64), (torch.bfloat16, 128), (torch.float16, 128)])
+@pytest.mark.parametrize("outputs", ["out", "both", "h1"])
+def test_autograd_on_the_dense_route_in_every_form(orc, monkeypatch, native, dtype, D, outputs):
+    from paper_2511_13645_amd import binding
+    from paper_2511_13645_amd.autograd import fused_sample_mean
+    n, B = 20000, 1024
+    x, args = _table_case(n, D, B, dtype, 6)
+    assert binding.fsa_mean_bwd_dense_pays(B, 25, 10, D, dtype, n)
+    if not native:
+        monkeypatch.setattr(binding, "_host", None)
+
+    def other(*a, **kw):
+        raise AssertionError("the other route")
+    monkeypatch.setattr(binding, "fsa_mean_bwd_ws", other)
+    monkeypatch.setattr(binding, "fsa_mean_bwd_lp", other)
+    out, h1, ids1, ids2 = fused_sample_mean(x, *args, want_h1=outputs != "out")
+    g = torch.randn((B, D), device=DEV).to(dtype) if outputs != "h1" else torch.zeros((B, D), dtype=dtype, device=DEV)
+    gh = torch.randn((B, 25, D), device=DEV).to(dtype) if outputs != "out" else None
+    torch.autograd.backward([t for t, w in ((out, "h1"), (h1, "out")) if outputs != w], [t for t, w in ((g, "h1"), (gh, "out")) if outputs != w])
+    a1, a2 = ids1.cpu().numpy(), ids2.cpu().numpy()
+    ref = orc.mean_bwd(to_f64(g), a1, a2, None if gh is None else to_f64(gh), num_nodes=n)
+    scale = orc.mean_bwd(np.abs(to_f64(g)), a1, a2, None if gh is None else np.abs(to_f64(gh)), num_nodes=n)
+    if dtype != torch.float32:
+        scale = scale * _roundings(a1, a2, n, D)
+    assert x.grad.dtype == dtype
+    assert_close(to_f64(x.grad), ref, scale + (2.0 ** -12 if dtype == torch.float16 else 0.0), TOL[dtype], "autograd, %s" % outputs)
+
+
+@pytest.mark.parametrize("with_workspace", [True, False])
+def test_a_workspace_of_the_sorted_route_keeps_autograd_on_it(orc, with_workspace):
+    """Where fsa_mean_bwd_workspace_bytes asks for one: its sums have a fixed order, so two passes agree to the last bit."""
+    from paper_2511_13645_amd import binding
+    from paper_2511_13645_amd.autograd import fused_sample_mean
+    n, D, B = 20000, 512, 1024
+    x, args = _table_case(n, D, B, torch.float32, 9, skew=1)
+    need = binding.fsa_mean_bwd_workspace_bytes(B, 25, 10, D)
+    assert need > 0 and binding.fsa_mean_bwd_dense_pays(B, 25, 10, D, torch.float32, n)
+    ws = marked_workspace(need)
+    g = torch.randn((B, D), device=DEV)
+    grads = []
+    for _ in range(2):
+        x.grad = None
+        out, _, ids1, ids2 = fused_sample_mean(x, *args, workspace=ws if with_workspace else None)
+        out.backward(g)
+        grads.append(x.grad)
+    assert workspace_route(ws) == ("sorted" if with_workspace else "atomic")    # "atomic": nobody wrote to it
+    if with_workspace:
+        assert torch.equal(*grads)
+    a1, a2 = ids1.cpu().numpy(), ids2.cpu().numpy()
+    ref = orc.mean_bwd(to_f64(g), a1, a2, None, num_nodes=n)
+    scale = orc.mean_bwd(np.abs(to_f64(g)), a1, a2, None, num_nodes=n)
+    assert_close(to_f64(grads[1]), ref, scale, 1e-5, "autograd with a workspace")
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_without_memory_for_the_workspace_the_gradient_is_cleared_and_added_to(monkeypatch, native):
+    """The allocator's limit leaves room for the gradient and not for the workspace beside it."""
+    from paper_2511_13645_amd import binding
+    n, D, B, k1, k2 = 400000, 128, 2048, 25, 10
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    ids1 = torch.randint(0, n, (B, k1), generator=gen, device=DEV, dtype=torch.int32)
+    ids2 = torch.randint(0, n, (B, k1, k2), generator=gen, device=DEV, dtype=torch.int32)
+    g = torch.randn((B, D), generator=gen, device=DEV)
+    grad_bytes, need = n * D * 4, binding.fsa_mean_bwd_dense_workspace_bytes(B, k1, k2, D, n)
+    assert binding.fsa_mean_bwd_dense_pays(B, k1, k2, D, torch.float32, n) and need > 48 << 20
+    if not native:
+        monkeypatch.setattr(binding, "_host", None)
+    total = torch.cuda.get_device_properties(DEV).total_memory
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held, limit = [], torch.cuda.memory_reserved()
+    torch.cuda.set_per_process_memory_fraction(limit / total)
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):                # what the allocator has left over of earlier tests
+            for _ in range(limit // (16 << 20) + 2):
+                held.append(torch.empty(16 << 20, dtype=torch.uint8, device=DEV))
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + grad_bytes + (8 << 20)) / total)
+        assert binding.grad_dense(g, ids1, ids2, None, n) is None
+        room = torch.empty(grad_bytes, dtype=torch.uint8, device=DEV)   # the attempt holds nothing back
+        del room
+    finally:
+        held.clear()
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert binding.grad_dense(g, ids1, ids2, None, n) is not None
