@@ -24,12 +24,12 @@
 namespace fsa {
 
 constexpr int kDenseThreads = 256;
-constexpr int kBinTile = 1024;
-constexpr int kBinWorkgroups = 256;                                  // one to a compute unit
-// Elements of a bin, and its rows: enough entries per workgroup to pay for its steps (clear counter to last store, 75,000
-// entries in 169,343 rows of 128 floats: 4096 elements 38.6 us, 8192 33.2, 16384 33.9; 590,000 entries 174 / 157 / 182),
-// and several rows per group of lanes where rows are wide (49,000 in 30,000 rows of 301 floats: 8 / 16 / 32 rows
-// 77 / 54 / 38).  Several bins per workgroup, the next one's entries requested ahead: 2 to 8 % slower on large tables.
+constexpr int kBinTile = 1024;                                       // leaf slots of a binning workgroup, or one root's
+constexpr int kBinWorkgroups = 256;                                  // one to a compute unit before any takes more than a root
+// Elements of a bin, and its rows: enough entries per workgroup to pay for its steps (the whole call, 256,000 slots on 169,343
+// rows of 128 floats: 4096 elements 38.6 us, 8192 36.8, 16384 36.9; 300,000 on 500,000 of 64 46.7 / 44.3 / 44.3; 1.2 M on 2.4 M of
+// 100 441 / 380 / 330), and several rows per group of lanes where rows are wide (50,000 on 30,000 rows of 300 floats: 8 / 16 / 32
+// rows 35 / 36 / 29).  Several bins per workgroup, the next one's entries requested ahead: 2 to 8 % slower on large tables.
 constexpr int kDenseBinElements = 8192;
 constexpr int kDenseRowsMin = 32;
 constexpr int kDenseRowsMax = 256;
@@ -93,7 +93,8 @@ static DensePlan dense_plan(int64_t slots, int k2, int slots_per_wg, int64_t D, 
     while ((1 << q.row_shift) < kDenseRowsMin) ++q.row_shift;
     while ((1 << q.row_shift) > kDenseRowsLoaded && slots * k2 / ((N >> q.row_shift) + 1) > kDenseLoad) --q.row_shift;
     q.bins = (N + (1ll << q.row_shift) - 1) >> q.row_shift;
-    // room for four times the mean with every slot full, while that is no long chain for the bin's workgroup
+    // room for four times the mean with every slot full, while that is no long chain for the bin's workgroup (twice / four /
+    // eight times: 256,000 slots on 169,343 rows of 128 floats 39.8 / 36.8 / 36.9 us, 2 M 119 / 117 / 125)
     const int64_t leaves = slots * k2, mean = leaves / q.bins;
     q.room = 32;
     while (q.room < kDenseMostRoom && q.room < 4 * mean) q.room *= 2;
@@ -514,8 +515,8 @@ bool dense_pays(int64_t B, int k1, int k2, int64_t D, int elem_bytes, int64_t N)
     const int64_t leaves = B * k1 * k2;
     const int64_t segments = leaves * ((D * elem_bytes + 63) / 64);
     const int64_t bins = dense_plan_of(B, k1, k2, D, N).bins;
-    return segments >= (D % 4 == 0 ? kDenseMinSegments : kDenseMinSegmentsSingles) && leaves * kDenseMaxRowsPerSlot >= N && D * elem_bytes >= kDenseMinRowBytes &&
-           bins >= kDenseMinBins && leaves <= bins * kDenseMostLoad;
+    return segments >= (D % 4 == 0 ? kDenseMinSegments : kDenseMinSegmentsSingles) && leaves * kDenseMaxRowsPerSlot >= N &&
+           D * elem_bytes >= kDenseMinRowBytes && bins >= kDenseMinBins && leaves <= bins * kDenseMostLoad;
 }
 
 template <typename GT> static hipError_t launch_dense(const DenseParams& p, hipStream_t stream) {
