@@ -325,13 +325,21 @@ template <typename GT, int VE, bool SLOT_GRADS> struct RowSums {
     }
 };
 
-// The entries that found their bins full, up to 256 of a list at a time: rows are told apart in an LDS table, and each
-// distinct row's sum is added to its tile.  Bound by a group's trips to memory, one row after the other, so a short list
-// is spread over its workgroups; a long one is not cut finer, which would add a hub row to its tile more often (153,600
-// leaves of one row: 256 entries at a time 25 us, 75 56); without lists 1.7 us.
+// The entries that found their bins full.  The workgroups of a list read up to 4096 of them together and share them out by
+// row classes, so that a row's entries meet in one workgroup; a class that a hub fills is shared out by place instead.  Each
+// takes its share up to 256 entries at a time: rows are told apart in an LDS table, and each distinct row's sum is added to its
+// tile.  Bound by these adds (20.8 G 64-byte segments/s) where many rows take part, else by a group's trips to memory,
+// one row after the other.  Shares by place alone left rows of a dense front apart: nine tenths of 153,600 leaves on 1000 of
+// 100,000 rows of 128 floats 69 us, this way 35; all on one row 25 and 29.  Short lists have little to bring together
+// and reading all of them costs 2 us.
 constexpr int kRestTable = 2 * kDenseThreads;
-constexpr int kRestLeast = 32;                                       // entries a workgroup takes at least
+constexpr int kRestLeast = 32;                                       // entries a workgroup takes at least, in the mean; at most:
+constexpr int kRestMost = kDenseThreads;                             // (192 2 % ahead on some fronts, 4 % behind on hubs)
+constexpr int kRestShort = 64;                                       // up to this mean the shares go by place alone
 constexpr int kRestEach = 16;                                        // workgroups to a list
+constexpr int kRestClasses = 4 * kRestEach;
+constexpr int kRestLoads = kRestEach * kRestMost / kDenseThreads;    // entries that a thread reads of those shared out
+constexpr int kRestShare = (kRestClasses / kRestEach / 2 + 1) * kRestMost;   // classes of up to half a mean share, and places
 template <typename GT, int VE, bool SLOT_GRADS>
 __global__ __launch_bounds__(kDenseThreads) void dense_rest_kernel(const DenseParams p, int group_shift) {
     using Sums = RowSums<GT, VE, SLOT_GRADS>;
@@ -344,61 +352,112 @@ __global__ __launch_bounds__(kDenseThreads) void dense_rest_kernel(const DensePa
     __shared__ int wave_total[kDenseThreads / kWave];
     __shared__ int hubs[kDenseThreads / kHubEntries];
     __shared__ int n_rows, n_hubs;
+    __shared__ int of_class[kRestClasses];                           // entries
+    __shared__ unsigned long long share[kRestShare];
+    __shared__ int share_bin[kRestShare], n_share;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const Sums sums{p, group_shift, sorted, count, start, hubs, partial};
-    const int list = blockIdx.x % kRestLists;
+    const int list = blockIdx.x % kRestLists, turn = blockIdx.x / kRestLists;
     const unsigned total = (unsigned)p.rest_count[list * kCountStride];
     unsigned each = (total + kRestEach - 1) / kRestEach;
-    each = each < kRestLeast ? kRestLeast : each < kDenseThreads ? each : kDenseThreads;
-    for (unsigned i0 = blockIdx.x / kRestLists * each; i0 < total; i0 += kRestEach * each) {   // workgroup-uniform
-        const int n = (int)(total - i0 < each ? total - i0 : each);
-        Entry mine{0};
-        uint32_t to = ~0u;                                           // (no row's number: there are fewer than 2^24 bins)
-        if (tid < n) {
-            const int64_t i = list * p.rest_room + i0 + tid;
-            mine.v = p.rest[i];
-            to = (uint32_t)p.tile_of[p.rest_bin[i]] << p.row_shift | (uint32_t)mine.row();
-        }
-        for (int h = tid; h < kRestTable; h += kDenseThreads) { tag[h] = ~0u; seen[h] = 0; }
-        if (tid == 0) { n_rows = 0; n_hubs = 0; }
-        __syncthreads();
-        int h = 0, place = 0;
-        bool owner = false;
-        if (tid < n) {                                               // twice as many places as rows: one is found
-            for (h = (int)((to * 2654435761u) >> 23);; h = (h + 1) & (kRestTable - 1)) {
-                const uint32_t was = atomicCAS(&tag[h], ~0u, to);
-                owner = was == ~0u;
-                if (owner || was == to) break;
+    each = each < kRestLeast ? kRestLeast : each < kRestMost ? each : kRestMost;
+    for (unsigned i0 = 0; i0 < total; i0 += kRestEach * each) {      // workgroup-uniform, as the passes below
+        const unsigned here = total - i0 < kRestEach * each ? total - i0 : kRestEach * each;
+        const int64_t at0 = list * p.rest_room + i0;
+        int shared;
+        if (each <= kRestShort) {
+            const unsigned from = turn * each;
+            shared = here > from ? (int)(here - from < each ? here - from : each) : 0;
+            if (tid < shared) { share[tid] = p.rest[at0 + from + tid]; share_bin[tid] = p.rest_bin[at0 + from + tid]; }
+        } else {
+            for (int c = tid; c < kRestClasses; c += kDenseThreads) of_class[c] = 0;
+            if (tid == 0) n_share = 0;
+            __syncthreads();
+            Entry of[kRestLoads];
+            int bin[kRestLoads], cls[kRestLoads];
+#pragma unroll
+            for (int k = 0; k < kRestLoads; ++k) {
+                const unsigned i = k * kDenseThreads + tid;
+                of[k].v = p.rest[at0 + (i < here ? i : 0)];
+                bin[k] = p.rest_bin[at0 + (i < here ? i : 0)];
             }
-            place = atomicAdd(&seen[h], 1);
-        }
-        __syncthreads();
-        const int c = owner ? seen[h] : 0;
-        int at = wave_inclusive_scan(c, lane);
-        if (lane == kWave - 1) wave_total[wave] = at;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) at += wave_total[w];
-        if (owner) {
-            const int r = atomicAdd(&n_rows, 1);
-            row[r] = to; count[r] = c; start[r] = first[h] = at - c;
-            if (c > kHubEntries) hubs[atomicAdd(&n_hubs, 1)] = r;
-        }
-        __syncthreads();
-        if (tid < n) sorted[first[h] + place] = Sums::sorted_entry(mine, p.k1);
-        __syncthreads();
-        sums(n_rows, false, n_hubs, [&](int r, int d, const float (&acc)[VE]) {
-            // the lanes trade elements, so that each atomic instruction covers consecutive ones
-            const int lanes = 1 << group_shift, sl = tid & (lanes - 1), d0 = d - sl * VE;
-            const int on = (p.D - d0) / VE < lanes ? (p.D - d0) / VE : lanes;     // lanes that are here
-            float* const mine = partial + (tid >> group_shift) * p.D + d0;
-            float* const to = p.tiles + (size_t)row[r] * p.D + d0;
-            __builtin_amdgcn_wave_barrier();
+            int run = -1, n_run = 0;                                 // a hub's entries are counted once per thread
 #pragma unroll
-            for (int k = 0; k < VE; ++k) mine[sl * VE + k] = acc[k];
-            __builtin_amdgcn_wave_barrier();
+            for (int k = 0; k < kRestLoads; ++k) {
+                const uint32_t r = (uint32_t)bin[k] << p.row_shift | (uint32_t)of[k].row();
+                cls[k] = k * kDenseThreads + tid < here ? (int)((r * 0x9e3779b1u ^ r >> 3) * 0x85ebca6bu >> 26) : -1;
+                if (cls[k] != run) {
+                    if (run >= 0) atomicAdd(&of_class[run], n_run);
+                    run = cls[k];
+                    n_run = 0;
+                }
+                ++n_run;
+            }
+            if (run >= 0) atomicAdd(&of_class[run], n_run);
+            __syncthreads();
 #pragma unroll
-            for (int k = 0; k < VE; ++k) atomicAdd(to + sl + k * on, mine[sl + k * on]);
-        });
+            for (int k = 0; k < kRestLoads; ++k) {
+                const unsigned i = k * kDenseThreads + tid;
+                const bool mine = cls[k] >= 0 && (of_class[cls[k]] <= (int)each / 2 ? cls[k] % kRestEach == turn : i / each == (unsigned)turn);
+                const uint64_t all = __ballot(mine);
+                int n_before = 0;
+                if (lane == 0 && all) n_before = atomicAdd(&n_share, __popcll(all));
+                const int o = __shfl(n_before, 0) + __popcll(all & lanemask_lt(lane));   // < kRestShare
+                if (mine) { share[o] = of[k].v; share_bin[o] = bin[k]; }
+            }
+            __syncthreads();
+            shared = n_share;
+        }
+        for (int j0 = 0; j0 < shared; j0 += kDenseThreads) {
+            const int n = shared - j0 < kDenseThreads ? shared - j0 : kDenseThreads;
+            Entry mine{0};
+            uint32_t to = ~0u;                                       // (no row's number: there are fewer than 2^24 bins)
+            if (tid < n) {
+                mine.v = share[j0 + tid];
+                to = (uint32_t)p.tile_of[share_bin[j0 + tid]] << p.row_shift | (uint32_t)mine.row();
+            }
+            for (int h = tid; h < kRestTable; h += kDenseThreads) { tag[h] = ~0u; seen[h] = 0; }
+            if (tid == 0) { n_rows = 0; n_hubs = 0; }
+            __syncthreads();
+            int h = 0, place = 0;
+            bool owner = false;
+            if (tid < n) {                                           // twice as many places as rows: one is found
+                for (h = (int)((to * 2654435761u) >> 23);; h = (h + 1) & (kRestTable - 1)) {
+                    const uint32_t was = atomicCAS(&tag[h], ~0u, to);
+                    owner = was == ~0u;
+                    if (owner || was == to) break;
+                }
+                place = atomicAdd(&seen[h], 1);
+            }
+            __syncthreads();
+            const int c = owner ? seen[h] : 0;
+            int at = wave_inclusive_scan(c, lane);
+            if (lane == kWave - 1) wave_total[wave] = at;
+            __syncthreads();
+            for (int w = 0; w < wave; ++w) at += wave_total[w];
+            if (owner) {
+                const int r = atomicAdd(&n_rows, 1);
+                row[r] = to; count[r] = c; start[r] = first[h] = at - c;
+                if (c > kHubEntries) hubs[atomicAdd(&n_hubs, 1)] = r;
+            }
+            __syncthreads();
+            if (tid < n) sorted[first[h] + place] = Sums::sorted_entry(mine, p.k1);
+            __syncthreads();
+            sums(n_rows, false, n_hubs, [&](int r, int d, const float (&acc)[VE]) {
+                // the lanes trade elements, so that each atomic instruction covers consecutive ones
+                const int lanes = 1 << group_shift, sl = tid & (lanes - 1), d0 = d - sl * VE;
+                const int on = (p.D - d0) / VE < lanes ? (p.D - d0) / VE : lanes;     // lanes that are here
+                float* const mine = partial + (tid >> group_shift) * p.D + d0;
+                float* const to = p.tiles + (size_t)row[r] * p.D + d0;
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k = 0; k < VE; ++k) mine[sl * VE + k] = acc[k];
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k = 0; k < VE; ++k) atomicAdd(to + sl + k * on, mine[sl + k * on]);
+            });
+            __syncthreads();
+        }
         __syncthreads();
     }
 }
