@@ -10,8 +10,8 @@
 //   clear   zero the bins' counters (a fill kernel: a memset node must not end up in a captured graph);
 //   bin     grad_x is cut into bins of consecutive rows; every live leaf slot appends an entry to its row's bin.
 //           A full bin gets a tile, its rows in fp32, and further entries go to lists;
-//   rest    workgroups take up to 256 entries of a list each, sum them by rows and add one row per distinct row to its
-//           bin's tile: however a batch's leaves are skewed, these are no more row atomics than adding leaf by leaf;
+//   rest    the workgroups of a list share its entries out by rows, up to 4096 at a time, sum them and add one row per
+//           distinct row to its bin's tile: however a batch's leaves are skewed, no more row atomics than leaf by leaf;
 //   write   a workgroup per bin sums the gradients of its rows' entries in registers, in fp32, adds the tile if there
 //           is one, and writes every row.
 // The order of additions follows the places that the entries got, which varies from run to run, as with atomics.
@@ -558,7 +558,9 @@ size_t dense_workspace_bytes(int64_t B, int k1, int k2, int64_t D, int64_t N) {
 // (96 %) 599 / 380; not taken: 50,000 slots on the 169,343 rows 26 / 25.
 // Rows that nothing names are the line of the rows: with 256,000 slots on rows of 128 floats and 13 / 30 / 100 % of them live,
 // two rows a slot 52 / 70 / 140 against 51 / 57 / 66 us, four 105 / 124 / 191 against 121 / 121 / 121.  (Below a tenth live
-// it is behind whatever the rows: 5 % on half a row, one and two rows a slot 22 / 29 / 45 against 23 / 32 / 53.)
+// it is behind whatever the rows: 5 % on half a row, one and two rows a slot 22 / 29 / 45 against 23 / 32 / 53.  And the host
+// does not see a crowded run of the table so large that its rows seldom meet in a list: nine tenths of 300,000 slots, 80 %
+// live, on 5000 of 500,000 rows of 64 floats 73 / 102, where the same slots without order are 75 / 44.)
 // Few bins leave the chip idle, long ones are a chain, and narrow rows cost the atomics least: 300 rows of 128 floats, 153,600
 // slots (80 %) 59 / 81 us, 2100 of 64, 256,000 65 / 67; 4000 of 32, 2 M slots, 8192 to a bin, 260 / 404, at 4096 8000 rows 265 / 261,
 // of 64 floats 449 / 255; 200,000 rows of 16 floats, 1.2 M slots 57 / 74, 1 M of 24, 512,000 34 / 45.
